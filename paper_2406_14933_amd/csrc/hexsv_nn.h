@@ -48,11 +48,25 @@ int net4_tiles(int nq, int nr, int batch);
 hipError_t launch_net4(const __bf16 *x, const Net4 &nw, float *out, int nq, int nr, int batch,
                        int cout_real, const ConvMask &cm, hipStream_t st,
                        const int32_t *live = nullptr);
-// Per-tile weight-gradient partials (7*coutp*cinp + coutp floats per tile).
+// Weight-gradient partials: one record (7*coutp*cinp + coutp floats) per workgroup of
+// the launch, which sweeps the tiles with its sums in registers.  WGRAD_WGS workgroups
+// are two per CU, all resident: more would only add records to reduce.
+constexpr int WGRAD_WGS = 512;
+int wgrad_records(int nq, int nr, int batch);
 hipError_t launch_wgrad(int cinp, int coutp, const __bf16 *x, const __bf16 *dy, float *part,
                         int nq, int nr, int batch, const ConvMask &cm, hipStream_t st);
-hipError_t launch_wgrad_reduce(const float *part, int ntiles, int cinp, int coutp, int cin,
-                               int cout, float *grad, hipStream_t st);
+// All layers' records (nrec of each) into the flat gradient; block0 is set by the launcher.
+constexpr int MAX_LAYERS = 16;
+struct WgradLayer {
+    const float *part;
+    int64_t off;  // of the layer's W in the flat parameters
+    int cinp, coutp, cin, cout, block0;
+};
+struct WgradTable {
+    int layers;
+    WgradLayer y[MAX_LAYERS];
+};
+hipError_t launch_wgrad_reduce(WgradTable tab, int nrec, float *grad, hipStream_t st);
 hipError_t launch_prepare_weights(const float *p, int cin, int cout, int cinp, int coutp,
                                   __bf16 *wm, __bf16 *wt, float *bias, hipStream_t st);
 hipError_t launch_adam(float *p, float *m, float *v, const float *g, int64_t n, float lr,

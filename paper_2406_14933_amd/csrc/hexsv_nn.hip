@@ -277,135 +277,228 @@ __global__ __launch_bounds__(NT) void k_hexnet4(const __bf16 *__restrict__ x, Ne
 
 // ------------------------------------------------------------ weight grad
 
-// Per-tile partial dW[t][co][ci] = sum_cells dy[cell][co] x[nbr_t(cell)][ci] and
-// db[co] = sum_cells dy[cell][co], in FP32; wave w handles taps w and w+4.
-// A = dy^T (16 channels x 32 cells), B = x_t (32 cells x 16 channels).
-template <int CIN, int COUT>
-__global__ __launch_bounds__(NT) void k_hexconv_wgrad(const __bf16 *__restrict__ x,
-                                                      const __bf16 *__restrict__ dy,
-                                                      float *__restrict__ part, int nq, int nr,
-                                                      int ntiles_total, ConvMask cm) {
-    constexpr int CH = CIN / 8;
-    constexpr int MB = COUT / 16;
-    constexpr int NB = CIN == 32 ? 2 : 1;
-    constexpr int PSZ = 7 * COUT * CIN + COUT;
-    __shared__ uint4 lds[NSLOT * CH];
-    __shared__ uint8_t fl[NSLOT];
-    __shared__ __bf16 sdy[TQ * TR * COUT];
-    const int ntq = (nq + TQ - 1) / TQ, ntr = (nr + TR - 1) / TR;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, 0);
-    if (tile < 0) return;
-    float *P = part + (int64_t)tile * PSZ;
-    int b, q0, r0;
-    tile_of(tile, ntq, ntr, b, q0, r0);
-    const int64_t soff = (int64_t)b * nq * nr;
-    stage_act<CIN>(lds, fl, x, nq, nr, soff, q0, r0, cm);
-    const bool masked = cm.active != nullptr;
-    // dy of the tile's cells (zero outside the raster), channels-last; loads first
-    constexpr int DITERS = (TQ * TR * COUT / 8 + NT - 1) / NT;
-    uint4 dv[DITERS];
-#pragma unroll
-    for (int it = 0; it < DITERS; ++it) {
-        const int e = threadIdx.x + it * NT;
-        const int c = e / (COUT / 8), ch = e - c * (COUT / 8);
-        const int lr = c / TQ, lq = c - lr * TQ;
-        const int q = q0 + lq, r = r0 + lr;
-        dv[it] = make_uint4(0u, 0u, 0u, 0u);
-        if (e < TQ * TR * COUT / 8 && q < nq && r < nr)
-            dv[it] = reinterpret_cast<const uint4 *>(dy + (soff + (int64_t)r * nq + q) * COUT)[ch];
-    }
-#pragma unroll
-    for (int it = 0; it < DITERS; ++it) {
-        const int e = threadIdx.x + it * NT;
-        if (e < TQ * TR * COUT / 8) reinterpret_cast<uint4 *>(sdy)[e] = dv[it];
-    }
-    __syncthreads();
-    const uint16_t *sx16 = reinterpret_cast<const uint16_t *>(lds);
-    const uint16_t *sdy16 = reinterpret_cast<const uint16_t *>(sdy);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int g = lane >> 4, l16 = lane & 15;
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-        const int tap = w + 4 * tt;
-        if (tap >= 7) break;
-        f32x4 acc[MB][NB];
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int n = 0; n < NB; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // K = 256 cells in 8 steps of 32; a group of 8 consecutive cells stays in one row
-#pragma unroll 2
-        for (int ks = 0; ks < (TQ * TR) / 32; ++ks) {
-            const int c0 = ks * 32 + 8 * g;  // first of this lane's 8 cells
-            const int lr = c0 / TQ, lq0 = c0 - lr * TQ;
-            bf16x8 a[MB], bv[NB];
-#pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                const int co = m * 16 + l16;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint16_t u = sdy16[(c0 + j) * COUT + co];
-                    a[m][j] = __builtin_bit_cast(__bf16, u);
-                }
-            }
-#pragma unroll
-            for (int n = 0; n < NB; ++n) {
-                const int ci = n * 16 + l16;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int sc = (lr + 1) * SW + (lq0 + j + 1);
-                    const int s = sc + OFFS[tap];
-                    uint16_t u = ci < CIN ? sx16[s * CIN + ci] : (uint16_t)0;
-                    if (masked && tap > 0 && !(fl[sc] & fl[s])) u = 0;
-                    bv[n][j] = __builtin_bit_cast(__bf16, u);
-                }
-            }
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int n = 0; n < NB; ++n)
-                    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], bv[n], acc[m][n], 0, 0, 0);
-        }
-        // lane holds dW rows co = m*16 + 4g + j, column ci = n*16 + l16
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int n = 0; n < NB; ++n) {
-                const int ci = n * 16 + l16;
-                if (ci >= CIN) continue;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int co = m * 16 + 4 * g + j;
-                    P[(tap * COUT + co) * CIN + ci] = acc[m][n][j];
-                }
-            }
-    }
-    // bias gradient: thread co sums its channel over the tile in cell order
-    if (threadIdx.x < COUT) {
-        float s = 0.f;
-        for (int c = 0; c < TQ * TR; ++c) s += (float)sdy[c * COUT + threadIdx.x];
-        P[7 * COUT * CIN + threadIdx.x] = s;
-    }
+// A 16-channel column of 8 consecutive cells: the transposing LDS read returns, to
+// lane i of each group of 16, column i of the 4 x 16 block whose rows the group's
+// lanes address (lane i: row i / 4, columns 4 (i % 4)...), so two reads give the 8
+// cells of an MFMA operand whose K runs over cells from channels-last data.
+__device__ inline bf16x8 read_cells8(const __bf16 *p, int cell_stride) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
+    union {
+        s16x4 h[2];
+        bf16x8 v;
+    } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * cell_stride));
+    return u.v;
 }
 
-// Sum the per-tile partials in tile order (deterministic) and scatter them
-// into the flat parameter-gradient layout W[o][c][t] (o < cout, c < cin), b[o].
-__global__ void k_wgrad_reduce(const float *__restrict__ part, int ntiles, int cinp, int coutp,
-                               int cin, int cout, float *__restrict__ grad) {
-    const int psz = 7 * coutp * cinp + coutp;
-    const int nw = cout * cin * 7;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < nw + cout; e += gridDim.x * blockDim.x) {
-        int src;
-        if (e < nw) {
-            const int o = e / (cin * 7), rem = e - o * cin * 7, c = rem / 7, t = rem - c * 7;
-            src = (t * coutp + o) * cinp + c;
-        } else {
-            src = 7 * coutp * cinp + (e - nw);
+// Partial dW[t][co][ci] = sum_cells dy[cell][co] x[nbr_t(cell)][ci] and
+// db[co] = sum_cells dy[cell][co], in FP32, of the tiles this workgroup sweeps.
+// A = dy^T (16 channels x 32 cells), B = x_t (32 cells x 16 channels); wave w takes
+// row w of each 64 x 4 tile for all seven taps, so a dy operand serves all of them,
+// and keeps the sums in registers over its tiles.
+//
+// Bound by the reads of x and dy (cache resident at the usual mini-batches) and by
+// the records the reduction has to read back: one per workgroup, at most WGRAD_WGS,
+// instead of one per tile.  Operands come from channels-last LDS rows through
+// transposing reads (8 two-byte gathers per operand before); rows are padded by 16
+// bytes per cell against bank conflicts.  The next tile's loads are in flight during
+// the arithmetic.  2 x 512 x 512 samples, 32 -> 32 channels: 27 us against 48 us.
+template <int CIN, int COUT>
+__global__ __launch_bounds__(NT, 2) void k_hexconv_wgrad(const __bf16 *__restrict__ x,
+                                                         const __bf16 *__restrict__ dy,
+                                                         float *__restrict__ part, int nq, int nr,
+                                                         int ntiles_total, ConvMask cm) {
+    constexpr int CH = CIN / 8, DCH = COUT / 8;
+    constexpr int MB = COUT / 16, NB = CIN / 16;
+    constexpr int PSZ = 7 * COUT * CIN + COUT;
+    constexpr int XS = CIN + 8, DS = COUT + 8;  // padded bf16 per staged cell
+    constexpr int XB = NSLOT * XS * 2, DB = TQ * TR * DS * 2;
+    constexpr int BYTES = XB + DB > PSZ * 4 ? XB + DB : PSZ * 4;
+    __shared__ __align__(16) unsigned char smem[BYTES];
+    __shared__ uint8_t fl[NSLOT];
+    __bf16 *sx = reinterpret_cast<__bf16 *>(smem);
+    __bf16 *sdy = reinterpret_cast<__bf16 *>(smem + XB);
+    float *red = reinterpret_cast<float *>(smem);  // the waves' sums, after the last tile
+    const int ntq = (nq + TQ - 1) / TQ, ntr = (nr + TR - 1) / TR;
+    const bool masked = cm.active != nullptr;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int g = lane >> 4, l16 = lane & 15;
+
+    constexpr int XIT = (NSLOT * CH + NT - 1) / NT, DIT = (TQ * TR * DCH + NT - 1) / NT;
+    uint4 xv[XIT], dv[DIT];
+    uint8_t av[XIT];
+    auto load = [&](int tile) {
+        int b, q0, r0;
+        tile_of(tile, ntq, ntr, b, q0, r0);
+        const int64_t soff = (int64_t)b * nq * nr;
+#pragma unroll
+        for (int it = 0; it < XIT; ++it) {
+            const int e = threadIdx.x + it * NT;
+            const int s = e / CH, ch = e - s * CH;
+            const int lr = s / SW, lq = s - lr * SW;
+            int q = q0 + lq - 1, r = r0 + lr - 1;
+            if (cm.perq) q = q < 0 ? q + nq : (q >= nq ? q - nq : q);
+            if (cm.perr) r = r < 0 ? r + nr : (r >= nr ? r - nr : r);
+            xv[it] = make_uint4(0u, 0u, 0u, 0u);
+            av[it] = 0;
+            if (e < NSLOT * CH && q >= 0 && q < nq && r >= 0 && r < nr) {
+                xv[it] = reinterpret_cast<const uint4 *>(x + (soff + (int64_t)r * nq + q) * CIN)[ch];
+                if (masked && ch == 0) av[it] = cm.active[(int64_t)r * nq + q] != 0;
+            }
         }
-        float s = 0.f;
-        for (int k = 0; k < ntiles; ++k) s += part[(int64_t)k * psz + src];
-        grad[e] = s;
+#pragma unroll
+        for (int it = 0; it < DIT; ++it) {  // dy of the tile's cells, zero outside the raster
+            const int e = threadIdx.x + it * NT;
+            const int c = e / DCH, ch = e - c * DCH;
+            const int q = q0 + c % TQ, r = r0 + c / TQ;
+            dv[it] = make_uint4(0u, 0u, 0u, 0u);
+            if (e < TQ * TR * DCH && q < nq && r < nr)
+                dv[it] = reinterpret_cast<const uint4 *>(dy + (soff + (int64_t)r * nq + q) * COUT)[ch];
+        }
+    };
+
+    f32x4 acc[7][MB][NB], accb[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        accb[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 7; ++t)
+#pragma unroll
+            for (int n = 0; n < NB; ++n) acc[t][m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    bf16x8 ones;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.f;
+
+    int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, 0);
+    if (tile >= 0) load(tile);
+    for (int k = 0; tile >= 0; ++k) {
+        __syncthreads();  // the previous tile's operands have been read
+#pragma unroll
+        for (int it = 0; it < XIT; ++it) {
+            const int e = threadIdx.x + it * NT;
+            if (e < NSLOT * CH) {
+                const int s = e / CH, ch = e - s * CH;
+                *reinterpret_cast<uint4 *>(sx + s * XS + ch * 8) = xv[it];
+                if (masked && ch == 0) fl[s] = av[it];
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < DIT; ++it) {
+            const int e = threadIdx.x + it * NT;
+            if (e < TQ * TR * DCH) {
+                const int c = e / DCH, ch = e - c * DCH;
+                *reinterpret_cast<uint4 *>(sdy + c * DS + ch * 8) = dv[it];
+            }
+        }
+        tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, k + 1);
+        if (tile >= 0) load(tile);
+        __syncthreads();
+#pragma unroll
+        for (int ks = 0; ks < TQ / 32; ++ks) {
+            const int c0 = ks * 32 + 8 * g;                 // first of this lane's 8 cells
+            const int sc = (w + 1) * SW + (c0 + 1);         // its staged slot
+            const int row = l16 >> 2, col = (l16 & 3) * 4;  // what this lane addresses
+            bf16x8 a[MB];
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+                a[m] = read_cells8(sdy + (w * TQ + c0 + row) * DS + m * 16 + col, DS);
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+                accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], ones, accb[m], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < 7; ++t) {
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    bf16x8 bv = read_cells8(sx + (sc + OFFS[t] + row) * XS + n * 16 + col, XS);
+                    if (masked && t > 0) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if (!(fl[sc + j] & fl[sc + OFFS[t] + j])) bv[j] = (__bf16)0.f;
+                    }
+#pragma unroll
+                    for (int m = 0; m < MB; ++m)
+                        acc[t][m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], bv, acc[t][m][n], 0, 0, 0);
+                }
+            }
+        }
+    }
+    // the four waves' sums in wave order: a lane holds dW rows co = m*16 + 4g + j,
+    // column ci = n*16 + l16
+    for (int v = 0; v < NT / 64; ++v) {
+        __syncthreads();
+        if (w != v) continue;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int co = m * 16 + 4 * g + j;
+#pragma unroll
+                for (int t = 0; t < 7; ++t)
+#pragma unroll
+                    for (int n = 0; n < NB; ++n) {
+                        float *o = red + (t * COUT + co) * CIN + n * 16 + l16;
+                        *o = v == 0 ? acc[t][m][n][j] : *o + acc[t][m][n][j];
+                    }
+                if (l16 == 0) {
+                    float *o = red + 7 * COUT * CIN + co;
+                    *o = v == 0 ? accb[m][j] : *o + accb[m][j];
+                }
+            }
+    }
+    __syncthreads();
+    float *P = part + (int64_t)blockIdx.x * PSZ;
+    for (int e = threadIdx.x; e < PSZ; e += NT) P[e] = red[e];
+}
+
+// Sum the workgroups' partials of every layer in a fixed order (deterministic) and
+// scatter them into the flat parameter-gradient layout W[o][c][t] (o < cout, c < cin),
+// b[o].  16 threads share an element, each adding every 16th record with eight loads
+// in flight, then a tree over the 16: one launch for all layers, 15 us at 512
+// records of 4 layers, where one thread per element over 2048 records took 635 us a
+// layer (its loads one behind the other).
+constexpr int RED_GRP = 16, RED_EL = 256 / RED_GRP;
+__global__ __launch_bounds__(256) void k_wgrad_reduce(WgradTable tab, int nrec,
+                                                      float *__restrict__ grad) {
+    int l = 0;
+    while (l + 1 < tab.layers && (int)blockIdx.x >= tab.y[l + 1].block0) ++l;
+    const WgradLayer y = tab.y[l];
+    const int psz = 7 * y.coutp * y.cinp + y.coutp;
+    const int el = threadIdx.x % RED_EL, grp = threadIdx.x / RED_EL;
+    const int src = ((int)blockIdx.x - y.block0) * RED_EL + el;
+    float s = 0.f;
+    if (src < psz) {
+        const float *p = y.part + src;
+        for (int k = grp; k < nrec; k += RED_GRP * 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int r = k + u * RED_GRP;
+                v[u] = r < nrec ? p[(int64_t)r * psz] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+    }
+    __shared__ float red[RED_GRP][RED_EL];
+    red[grp][el] = s;
+    __syncthreads();
+    if (grp != 0 || src >= psz) return;
+#pragma unroll
+    for (int o = RED_GRP / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int k = 0; k < o; ++k) red[k][el] += red[k + o][el];
+    const float tot = red[0][el];
+    if (src >= 7 * y.coutp * y.cinp) {
+        const int o = src - 7 * y.coutp * y.cinp;
+        if (o < y.cout) grad[y.off + (int64_t)y.cout * y.cin * 7 + o] = tot;
+        return;
+    }
+    const int t = src / (y.coutp * y.cinp), rem = src - t * y.coutp * y.cinp;
+    const int o = rem / y.cinp, c = rem - o * y.cinp;
+    if (o < y.cout && c < y.cin) grad[y.off + ((int64_t)o * y.cin + c) * 7 + t] = tot;
 }
 
 // ------------------------------------------------------------ parameters
@@ -539,13 +632,18 @@ hipError_t launch_net4(const __bf16 *x, const Net4 &nw, float *out, int nq, int 
     return hipGetLastError();
 }
 
+int wgrad_records(int nq, int nr, int batch) {
+    const int nt = conv_tiles(nq, nr, batch);
+    return nt < WGRAD_WGS ? nt : WGRAD_WGS;
+}
+
 hipError_t launch_wgrad(int cinp, int coutp, const __bf16 *x, const __bf16 *dy, float *part,
                         int nq, int nr, int batch, const ConvMask &cm, hipStream_t st) {
-    const int nt = conv_tiles(nq, nr, batch);
+    const int nt = conv_tiles(nq, nr, batch), nwg = wgrad_records(nq, nr, batch);
 #define HEXSV_WG(CI, CO)                                                                       \
     if (cinp == CI && coutp == CO) {                                                           \
-        hipLaunchKernelGGL((k_hexconv_wgrad<CI, CO>), dim3(nt), dim3(NT), 0, st, x, dy, part, nq, \
-                           nr, nt, cm);                                                        \
+        hipLaunchKernelGGL((k_hexconv_wgrad<CI, CO>), dim3(nwg), dim3(NT), 0, st, x, dy, part,  \
+                           nq, nr, nt, cm);                                                    \
         return hipGetLastError();                                                              \
     }
     HEXSV_WG(16, 32)
@@ -555,10 +653,13 @@ hipError_t launch_wgrad(int cinp, int coutp, const __bf16 *x, const __bf16 *dy, 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_wgrad_reduce(const float *part, int ntiles, int cinp, int coutp, int cin,
-                               int cout, float *grad, hipStream_t st) {
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks_for(7 * cin * cout + cout)), dim3(256), 0, st,
-                       part, ntiles, cinp, coutp, cin, cout, grad);
+hipError_t launch_wgrad_reduce(WgradTable tab, int nrec, float *grad, hipStream_t st) {
+    int blocks = 0;
+    for (int l = 0; l < tab.layers; ++l) {
+        tab.y[l].block0 = blocks;
+        blocks += (7 * tab.y[l].coutp * tab.y[l].cinp + tab.y[l].coutp + RED_EL - 1) / RED_EL;
+    }
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks), dim3(256), 0, st, tab, nrec, grad);
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -40,7 +41,7 @@ struct hexsv_surrogate {
     float *out;                 // network output, OUT_STRIDE floats per cell
     __bf16 *dy_last;            // loss gradient, 16 channels
     __bf16 *dA, *dB;            // data-gradient ping-pong buffers, channels each
-    float *wpart;               // weight-gradient partials
+    float *wpart;               // weight-gradient partials, layer after layer
     double *lpart, *h_lpart;    // loss partials (device, pinned host)
 };
 
@@ -85,8 +86,9 @@ static int ensure_ws(hexsv_surrogate *s, int64_t cells, int tiles) {
     if (e == hipSuccess) e = hipMalloc(&s->dA, sizeof(__bf16) * C * cells);
     if (e == hipSuccess) e = hipMalloc(&s->dB, sizeof(__bf16) * C * cells);
     size_t psz = 0;
-    for (auto &l : s->L) psz = std::max(psz, (size_t)(7 * l.coutp * l.cinp + l.coutp));
-    if (e == hipSuccess) e = hipMalloc(&s->wpart, sizeof(float) * psz * (size_t)tiles);
+    for (auto &l : s->L) psz += (size_t)(7 * l.coutp * l.cinp + l.coutp);
+    if (e == hipSuccess)
+        e = hipMalloc(&s->wpart, sizeof(float) * psz * (size_t)std::min(tiles, nn::WGRAD_WGS));
     if (e == hipSuccess) e = hipMalloc(&s->lpart, sizeof(double) * LOSS_PARTS);
     if (e == hipSuccess) e = hipHostMalloc(&s->h_lpart, sizeof(double) * LOSS_PARTS, hipHostMallocDefault);
     if (e != hipSuccess) {
@@ -330,14 +332,18 @@ static int gradient(hexsv_surrogate *s, const hexsv_grid *grid, int batch, int n
     if (rc) return rc;
     const double inv_count = 1.0 / (3.0 * (double)cells);
     HIP_TRY(nn::launch_l1_loss(s->out, target, cells, inv_count, s->dy_last, s->lpart, LOSS_PARTS, st));
-    const int tiles = nn::conv_tiles(nq, nr, batch);
+    const int nrec = nn::wgrad_records(nq, nr, batch);
+    nn::WgradTable tab;
+    tab.layers = s->layers;
+    float *part = s->wpart;
     const __bf16 *dy = s->dy_last;
     __bf16 *buf[2] = {s->dA, s->dB};
     for (int l = s->layers - 1; l >= 0; --l) {
         const SurLayer &y = s->L[l];
         const __bf16 *xin = l == 0 ? s->x0 : s->act[l - 1];
-        HIP_TRY(nn::launch_wgrad(y.cinp, y.coutp, xin, dy, s->wpart, nq, nr, batch, cm, st));
-        HIP_TRY(nn::launch_wgrad_reduce(s->wpart, tiles, y.cinp, y.coutp, y.cin, y.cout, s->d_g + y.off, st));
+        HIP_TRY(nn::launch_wgrad(y.cinp, y.coutp, xin, dy, part, nq, nr, batch, cm, st));
+        tab.y[l] = nn::WgradLayer{part, y.off, y.cinp, y.coutp, y.cin, y.cout, 0};
+        part += (size_t)nrec * (7 * y.coutp * y.cinp + y.coutp);
         if (l > 0) {
             __bf16 *dx = buf[l & 1];
             // data gradient: input channels of the transposed stencil = coutp, output = cinp
@@ -346,6 +352,7 @@ static int gradient(hexsv_surrogate *s, const hexsv_grid *grid, int batch, int n
             dy = dx;
         }
     }
+    HIP_TRY(nn::launch_wgrad_reduce(tab, nrec, s->d_g, st));
     HIP_TRY(hipMemcpyAsync(s->h_lpart, s->lpart, sizeof(double) * LOSS_PARTS, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     double tot = 0.0;
