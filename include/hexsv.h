@@ -253,9 +253,13 @@ int hexsv_sim_set_state(hexsv_sim *sim, double t0, const double *d_h, const doub
 /* Advance to t_end, or until max_steps more steps were taken (max_steps <= 0:
  * no limit).  Each step: dt = min(dt_max, CFL*phi_min/c_max, t_end - t),
  * then eq. fvm_2D_eq_frac.07 on every active cell, then c_max and the FP64
- * books of the new state; the last step lands on t_end exactly.  Runs as
- * replays of captured graphs of steps_per_graph (and of 8) steps on `stream`,
- * batched by the steps expected to remain, reading the 256-byte control block
+ * books of the new state; the last step lands on t_end exactly.  A raster
+ * whose tiles (or stacks of 2 or 4 of them) number no more than the device's
+ * compute units, with no periodic side, runs as launches that each hold it on
+ * chip for up to steps_per_graph steps; others, and what such a launch gave
+ * up, run as replays of captured graphs of steps_per_graph (and of 8) steps.
+ * Both give the same state and books bit for bit, go to `stream` in batches
+ * sized by the steps expected to remain, and read the 256-byte control block
  * back after each batch.  EDOMAIN: t_end < t.
  * ENUMERIC: a non-finite value appeared (state left at the failing step). */
 int hexsv_sim_run(hexsv_sim *sim, double t_end, int64_t max_steps, hipStream_t stream);
@@ -271,12 +275,12 @@ int hexsv_sim_get_books(hexsv_sim *sim, hexsv_books *out, hipStream_t stream);
  * (checkpoint/resume).  The time t and step count are restored too. */
 int hexsv_sim_set_books(hexsv_sim *sim, const hexsv_books *books, hipStream_t stream);
 
-/* Device timing of run(): while enabled, run() brackets every graph replay
- * with hipEvents on its stream and accumulates the replays' GPU time and the
- * steps they took.  Reads the totals since the last reset; enable >= 0
+/* Device timing of run(): while enabled, run() brackets every batch of graph
+ * replays (or of launches of many steps, counted as replays) with hipEvents on
+ * its stream and accumulates their GPU time and the steps they took.  Reads the totals since the last reset; enable >= 0
  * switches timing on (1) or off (0) and resets the totals, enable < 0 only
- * reads.  Each step is one kernel launch, so gpu_ms/steps is the step
- * kernel's average duration including launch gaps inside the graph. */
+ * reads.  In a graph each step is one kernel launch, so gpu_ms/steps is the
+ * step kernel's average duration including launch gaps inside the graph. */
 int hexsv_sim_timing(hexsv_sim *sim, int32_t enable, double *gpu_ms, int64_t *steps,
                      int64_t *replays);
 
@@ -309,8 +313,11 @@ int hexsv_sim_info(const hexsv_sim *sim, int32_t *workgroups, int32_t *tile, int
  * taken largest first, params->steps_per_graph steps per scenario per launch,
  * 0: 50) or batched steps (a graph of steps_per_graph steps, each a tile
  * kernel over the tiles of every live scenario plus a per-scenario close);
- * AUTO means batched unless the tuning cache says otherwise.  params->tile
- * selects the tile variant of the chosen mode (< 0: tuned or default).  The
+ * AUTO means batched unless the tuning cache says otherwise.  In batched mode
+ * an ensemble without periodic rasters whose tiles number no more than the
+ * device's compute units runs as launches that hold it on chip for many steps
+ * (as hexsv_sim_run; the same results bit for bit).  params->tile selects the
+ * tile variant of the chosen mode (< 0: tuned or default).  The
  * grids must outlive the ensemble. */
 int hexsv_ensemble_create(int32_t n, const hexsv_grid *const *grids, const hexsv_params *params,
                           hexsv_ensemble **out);
@@ -332,8 +339,8 @@ int hexsv_ensemble_set_scenario(hexsv_ensemble *ens, int32_t s, const double *d_
 int hexsv_ensemble_set_viscosity(hexsv_ensemble *ens, int32_t on);
 
 /* Advance every scenario s to t_end[s] (host array of n), or by at most
- * max_steps steps (<= 0: no limit).  Replays a captured graph of one
- * persistent launch until every scenario is done.  EDOMAIN: t_end[s] before
+ * max_steps steps (<= 0: no limit): launches of the mode's kernel, or replays
+ * of its captured graph, until every scenario is done.  EDOMAIN: t_end[s] before
  * the scenario's time.  ENUMERIC: a non-finite value appeared. */
 int hexsv_ensemble_run(hexsv_ensemble *ens, const double *t_end, int64_t max_steps,
                        hipStream_t stream);

@@ -29,6 +29,8 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 UNITS = [
     ("hexsv_f64.hip", ["-ffp-contract=off"]),
     ("hexsv_f32.hip", ["-ffp-contract=fast-honor-pragmas"]),
+    ("hexsv_res64.hip", ["-ffp-contract=off"]),
+    ("hexsv_res32.hip", ["-ffp-contract=fast-honor-pragmas"]),
     ("hexsv_common.hip", ["-ffp-contract=off"]),
     ("hexsv_capi.hip", ["-ffp-contract=off"]),
     ("hexsv_ens.hip", ["-ffp-contract=off"]),

@@ -212,6 +212,13 @@ struct hexsv_sim {
     int32_t *h_chk;  // pinned
     int tile, ntq, ntiles, nwg;
     int gsteps;
+    int ncu;  // compute units: the most workgroups of a resident launch
+    // resident steps (k_resident): exchange memory sized for the current tiling, and the
+    // next launch's tag
+    char *d_res;
+    size_t res_bytes;
+    ResSync res;
+    uint32_t res_tag;
     hipStream_t cap;
     hipGraph_t graph[2];    // gsteps steps, starting from buffer parity 0 / 1
     hipGraphExec_t gexec[2];
@@ -337,6 +344,9 @@ extern "C" int hexsv_sim_create(const hexsv_grid *grid, const hexsv_params *para
     s->rn.t_a = 0.0;
     s->rn.T_d = INFINITY;
     s->nwg = s->ntiles;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&s->ncu, hipDeviceAttributeMultiprocessorCount, dev);
     hipError_t e = hipMalloc(&s->buf, s->esz * 9 * (size_t)grid->n);
     if (e == hipSuccess) e = hipMalloc(&s->d_ctl, 2 * sizeof(Ctl));  // two control slots
     if (e == hipSuccess) e = hipMalloc(&s->d_part, sizeof(Part) * PRIME_BLOCKS);
@@ -369,6 +379,7 @@ extern "C" void hexsv_sim_destroy(hexsv_sim *s) {
     if (s->d_ring) (void)hipFree(s->d_ring);
     if (s->d_slots) (void)hipFree(s->d_slots);
     if (s->d_acc) (void)hipFree(s->d_acc);
+    if (s->d_res) (void)hipFree(s->d_res);
     if (s->d_chk) (void)hipFree(s->d_chk);
     if (s->h_ctl) (void)hipHostFree(s->h_ctl);
     if (s->h_chk) (void)hipHostFree(s->h_chk);
@@ -671,6 +682,74 @@ static int short_plan(int n, int *plan, int cap) {
     return m;
 }
 
+// Tiling of the resident steps: workgroups of `sub` stacked tiles of the current variant,
+// the fewest per workgroup that leave at most one workgroup per compute unit (all of them
+// then fit on the device at once, which the launch needs).  False: the raster is too large,
+// or periodic (a seam's ring cells need not lie on the rim of a ragged tile), or the tile
+// is not one of the 64-wide, 256-thread variants the kernel stacks.
+struct ResPlan {
+    int sub, ntq, nwg;
+};
+static bool resident_plan(const hexsv_sim *s, ResPlan *p) {
+    const KGrid &g = s->grid->kg;
+    if (s->tile > 2 || g.perq || g.perr) return false;
+    for (int sub = 1; sub <= RES_MAX_SUB; sub *= 2) {
+        const int tr = TILES[s->tile].tr * sub;
+        const int64_t nwg = (int64_t)s->ntq * ((g.nr + tr - 1) / tr);
+        if (nwg > s->ncu) continue;
+        if (!resident_fits(s->esz, s->tile, sub, s->kc.visc != 0)) return false;
+        *p = ResPlan{sub, s->ntq, (int)nwg};
+        return true;
+    }
+    return false;
+}
+
+// Exchange memory for a plan; all words zero (no tag is) before its first use.
+static int ensure_resident(hexsv_sim *s, const ResPlan &p, hipStream_t st) {
+    const size_t halo = sizeof(unsigned long long) * p.nwg * resident_halo_words(s->esz, s->tile, p.sub);
+    const size_t flags = sizeof(unsigned long long) * 2 * (s->esz / 4) * p.nwg;
+    const size_t bytes = halo + flags + sizeof(uint32_t) * (64 + p.nwg);
+    const bool wrap = s->res_tag > 0xffff0000u;
+    if (s->d_res && s->res_bytes == bytes && s->res.flag_cap == p.nwg && !wrap) return HEXSV_OK;
+    if (s->res_bytes != bytes) {
+        if (s->d_res) HIP_TRY(hipFree(s->d_res));
+        s->d_res = nullptr;
+        s->res_bytes = 0;
+        if (hipMalloc(&s->d_res, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            s->d_res = nullptr;
+            return HEXSV_ENOMEM;  // the caller steps without
+        }
+        s->res_bytes = bytes;
+    }
+    HIP_TRY(hipMemsetAsync(s->d_res, 0, bytes, st));
+    s->res.halo = (unsigned long long *)s->d_res;
+    s->res.flags = (unsigned long long *)(s->d_res + halo);
+    s->res.abort_word = (uint32_t *)(s->d_res + halo + flags);
+    s->res.done = s->res.abort_word + 64;
+    s->res.flag_cap = p.nwg;
+    s->res_tag = 1;
+    return HEXSV_OK;
+}
+
+// One resident launch of up to ring_len steps and its commit.
+static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, hipStream_t st) {
+    const KClose cl = close_of(s);
+    const uint32_t tag0 = s->res_tag;
+    s->res_tag += (uint32_t)s->ring_len + 1;
+    hipError_t e =
+        s->prec == HEXSV_FP64
+            ? launch_resident<double>(s->tile, p.sub, dom_of<double>(s), s->grid->kg, s->kc, s->rn,
+                                      s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles, s->ring_len,
+                                      tag0, st)
+            : launch_resident<float>(s->tile, p.sub, dom_of<float>(s), s->grid->kg, s->kc, s->rn,
+                                     s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles, s->ring_len,
+                                     tag0, st);
+    if (e != hipSuccess) return e;
+    return launch_fold_resident(s->d_ctl, cl, s->ntiles, s->kc, s->rn, s->ring_len, s->res, p.nwg,
+                                tag0, st);
+}
+
 static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, bool ctl_fresh,
                    hipStream_t stream);
 
@@ -695,13 +774,24 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
     c.step_limit = max_steps > 0 ? c.steps + max_steps : INT64_MAX;
     const int64_t limit = c.step_limit;
     HIP_TRY(hipMemcpyAsync(s->d_ctl, s->h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, stream));
-    if (!s->graph_ok) {
-        int rc = capture(s);
+    // a raster that fits on the chip steps in resident launches; one that was given up
+    // (see k_resident) leaves the rest of the run to single launches
+    ResPlan plan_r;
+    bool resident = resident_plan(s, &plan_r);
+    if (resident) {
+        int rc = ensure_ring(s);
         if (rc) return rc;
+        rc = ensure_resident(s, plan_r, stream);
+        if (rc == HEXSV_ENOMEM) resident = false;
+        else if (rc) return rc;
     }
     int64_t last_steps = -1;
     for (;;) {
         const int64_t before = c.steps;
+        if (!resident && !s->graph_ok) {
+            int rc = capture(s);
+            if (rc) return rc;
+        }
         // A launch past the end of the run still issues its tile loads before it
         // finds out, so each batch of replays is sized from the steps expected to
         // remain (the current dt bound, or the step limit): whole long graphs
@@ -717,7 +807,9 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         const bool use_short = !exact && (shortg || need < 2.0 * s->gsteps);
         int reps;
         int plan[48];  // short graphs of this batch
-        if (exact) {
+        if (resident) {  // a launch stops where the run does
+            reps = (int)fmin(64.0, ceil(fmax(need, 1.0) / s->ring_len));
+        } else if (exact) {
             reps = (int)(by_limit / s->gsteps < 64 ? by_limit / s->gsteps : 64);
         } else if (use_short) {
             const double n = ceil(fmin(need, 512.0));
@@ -732,7 +824,9 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         int64_t launched = 0;
         for (int k = 0; k < reps; ++k) {
             const int p = (int)((c.parity + launched) & 1);
-            if (use_short) {
+            if (resident) {
+                HIP_TRY(resident_launch(s, plan_r, stream));
+            } else if (use_short) {
                 HIP_TRY(hipGraphLaunch(s->sexec[plan[k]][p], stream));
                 launched += SHORT_LEN[plan[k]];
             } else {
@@ -753,7 +847,12 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         if (c.err)
             return fail(HEXSV_ENUMERIC, "run: non-finite value at cell %d in step %lld (t=%g)",
                         c.err_cell, (long long)c.steps + 1, c.t);
-        if (c.t >= t_end || c.steps >= limit || c.steps == last_steps) break;
+        if (c.t >= t_end || c.steps >= limit) break;
+        if (resident && c.steps == before) {
+            resident = false;
+            continue;
+        }
+        if (c.steps == last_steps) break;
         last_steps = c.steps;
     }
     return HEXSV_OK;

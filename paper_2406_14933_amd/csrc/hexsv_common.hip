@@ -47,21 +47,43 @@ __global__ __launch_bounds__(1024) void k_fold_slots(const Ctl *ctl, KClose cl, 
 }
 
 // The pending step of slot `in` closed into ctl[0], the slots' books added in
-// step order, the ring emptied and every accumulator cleared.  One wave.
+// step order, the ring emptied and every accumulator cleared.  One wave.  done: the
+// marks of a resident launch; unless all nwg of them hold tag0, nothing is committed.
 __global__ __launch_bounds__(64) void k_fold_close(Ctl *ctl, KClose cl, KConst kc, KRain rn,
-                                                   int in, int set) {
+                                                   int in, int set, const uint32_t *done, int nwg,
+                                                   uint32_t tag0) {
+    if (done) {
+        bool all = true;
+        for (int i = threadIdx.x; i < nwg; i += 64) all = all && done[i] == tag0;
+        if (!__all(all)) return;
+    }
     const OpenStep o = open_step(ctl, in, cl.acc + set * ACC_SET_WORDS, kc);
+    // the slots' totals come in with one load per lane (one thread reading them one behind
+    // the other took 14 us for 100 slots, against 5 us), and one thread adds them in order
+    const int n = o.open < cl.ring_len ? o.open : cl.ring_len;
+    __shared__ double so[64], sc[64];
+    double stored = ctl[in].stored, outflow = ctl[in].outflow, clamp = ctl[in].clamp;
+    for (int base = 0; base < n; base += 64) {
+        const int j = base + threadIdx.x;
+        Part p{0.0, 0.0, 0.0, 0.0};
+        if (j < n) p = cl.slots[j];
+        so[threadIdx.x] = p.outflow;
+        sc[threadIdx.x] = p.clamp;
+        __syncthreads();
+        const int m = n - base < 64 ? n - base : 64;
+        if (threadIdx.x == m - 1) stored = p.stored;
+        stored = __shfl(stored, m - 1, 64);
+        if (threadIdx.x == 0) {
+#pragma unroll 8
+            for (int i = 0; i < m; ++i) {
+                outflow += so[i];
+                clamp += sc[i];
+            }
+        }
+        __syncthreads();
+    }
     if (threadIdx.x == 0) {
         write_slot(ctl, ctl + in, o, kc, rn, false);
-        const int n = o.open < cl.ring_len ? o.open : cl.ring_len;
-        // in registers: stores to ctl inside the loop would serialise its loads
-        double stored = ctl->stored, outflow = ctl->outflow, clamp = ctl->clamp;
-        for (int j = 0; j < n; ++j) {
-            const Part p = cl.slots[j];
-            stored = p.stored;
-            outflow += p.outflow;
-            clamp += p.clamp;
-        }
         ctl->stored = stored;
         ctl->outflow = outflow;
         ctl->clamp = clamp;
@@ -78,7 +100,19 @@ hipError_t launch_fold(Ctl *ctl, const KClose &cl, int ntiles, const KConst &kc,
     hipLaunchKernelGGL(k_fold_slots, dim3(slots), dim3(1024), 0, stream, ctl, cl, ntiles, in);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fold_close, dim3(1), dim3(64), 0, stream, ctl, cl, kc, rn, in, set);
+    hipLaunchKernelGGL(k_fold_close, dim3(1), dim3(64), 0, stream, ctl, cl, kc, rn, in, set,
+                       nullptr, 0, 0u);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_resident(Ctl *ctl, const KClose &cl, int ntiles, const KConst &kc,
+                                const KRain &rn, int slots, const ResSync &rs, int nwg,
+                                uint32_t tag0, hipStream_t stream) {
+    hipLaunchKernelGGL(k_fold_slots, dim3(slots), dim3(1024), 0, stream, ctl, cl, ntiles, 1);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_fold_close, dim3(1), dim3(64), 0, stream, ctl, cl, kc, rn, 1, 0, rs.done,
+                       nwg, tag0);
     return hipGetLastError();
 }
 
@@ -226,6 +260,64 @@ hipError_t launch_ens_finalize(const EnsScen *scen, Ctl *ctl, const Part *part, 
     return hipGetLastError();
 }
 
+// Commit of an ensemble's resident launch, one workgroup per scenario: nothing unless all
+// workgroups of its group (groups[s]: first, count) reached the end, else the proposed control
+// block with the steps' water books added in order.  A wave sums a step's records in
+// reduce_parts' order (64 consecutive records at a time, the totals in turn; a scenario has
+// at most 1024, one per thread there).
+constexpr int ENS_FOLD_STEPS = 128;
+__global__ __launch_bounds__(256) void k_ens_fold(const EnsScen *scen, Ctl *ctl, const Ctl *out,
+                                                  const Part *ring, const uint32_t *done,
+                                                  const int2 *groups, int btotal, uint32_t tag0) {
+    const int s = blockIdx.x;
+    const int2 grp = groups[s];
+    bool all = true;
+    for (int i = threadIdx.x; i < grp.y; i += 256) all = all && done[grp.x + i] == tag0;
+    if (!__syncthreads_and(all)) return;
+    const Ctl o = out[s];
+    const int n = o.open < ENS_FOLD_STEPS ? o.open : ENS_FOLD_STEPS;
+    if (n <= 0) return;
+    __shared__ double st[ENS_FOLD_STEPS], so[ENS_FOLD_STEPS], sc[ENS_FOLD_STEPS];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nt = scen[s].bntiles;
+    for (int j = wave; j < n; j += 4) {
+        const Part *p = ring + (size_t)j * btotal + scen[s].bbase;
+        double a = 0.0, b = 0.0, c = 0.0;
+        for (int base = 0; base < nt; base += 64) {
+            Part x{0.0, 0.0, 0.0, 0.0};
+            if (base + lane < nt) x = p[base + lane];
+            const double ws = wave_sum(x.stored), wo = wave_sum(x.outflow), wc = wave_sum(x.clamp);
+            a = base == 0 ? ws : a + ws;
+            b = base == 0 ? wo : b + wo;
+            c = base == 0 ? wc : c + wc;
+        }
+        if (lane == 0) {
+            st[j] = a;
+            so[j] = b;
+            sc[j] = c;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    Ctl r = o;
+    r.open = 0;
+    r.stored = st[n - 1];
+    for (int j = 0; j < n; ++j) {
+        r.outflow += so[j];
+        r.clamp += sc[j];
+    }
+    r.err = ctl[s].err;
+    r.err_cell = ctl[s].err_cell;
+    ctl[s] = r;
+}
+
+hipError_t launch_ens_fold(const EnsScen *scen, Ctl *ctl, const Ctl *out, const Part *ring,
+                           const ResSync &rs, const int2 *groups, int nscen, int btotal,
+                           uint32_t tag0, hipStream_t stream) {
+    hipLaunchKernelGGL(k_ens_fold, dim3(nscen), dim3(256), 0, stream, scen, ctl, out, ring, rs.done,
+                       groups, btotal, tag0);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------ surrogate windows
 
 __global__ void k_win_reset(SurWin *sw) {
@@ -278,13 +370,13 @@ __device__ inline void reduce_window_parts(const Part *part, int n_part, const P
         }
     }
     __shared__ double red[5][NT / 64];
-    c = wave_max(c);
+    c = wave_max_last(c);
     s = wave_sum(s);
     o = wave_sum(o);
     cl = wave_sum(cl);
     s0 = wave_sum(s0);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) {
+    if (lane == 63) {
         red[0][w] = c;
         red[1][w] = s;
         red[2][w] = o;

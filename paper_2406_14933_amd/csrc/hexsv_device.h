@@ -215,18 +215,72 @@ __device__ inline double p_sqrt(double x) { return __builtin_sqrt(x); }
 __device__ inline float p_div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 __device__ inline double p_div(double a, double b) { return a / b; }
 
-template <typename T>
-__device__ inline T wave_max(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        T u = __shfl_xor(v, o, 64);
-        v = u > v ? u : v;
-    }
+// Lane permutations of a double, both halves alike: DPP within rows of 16 lanes, and the
+// gfx950 swaps of rows and of half waves.  Reductions built on them stay off the LDS
+// permute unit, whose six dependent round trips per value were most of a small tile's tail.
+template <int CTRL, int ROWS = 0xf>
+__device__ inline double dpp64(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, true);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// v[i] + v[i ^ 32] and v[i] + v[i ^ 16] in every lane: a swap of a register with itself
+// leaves the two addends in its two results.
+__device__ inline double add_xor32(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto hi =
+        __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+__device__ inline double add_xor16(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto hi =
+        __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+// Sum over the wave in every lane, as a butterfly over lane ^ 32, 16, 8, 4, 2, 1 adds it
+// (within a row, once lanes i and i ^ 8 hold the same value, a rotation by 4 reads what
+// i ^ 4 holds, and so on).
+__device__ inline double wave_sum(double v) {
+    v = add_xor32(v);
+    v = add_xor16(v);
+    v += dpp64<0x128>(v);  // row_ror 8, 4, 2, 1
+    v += dpp64<0x124>(v);
+    v += dpp64<0x122>(v);
+    v += dpp64<0x121>(v);
     return v;
 }
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// Largest of non-negative values over the wave, in lane 63.
+__device__ inline double wave_max_last(double v) {
+    double u;
+    u = dpp64<0x111>(v), v = u > v ? u : v;  // row_shr 1, 2, 4, 8: lane 15 of each row
+    u = dpp64<0x112>(v), v = u > v ? u : v;
+    u = dpp64<0x114>(v), v = u > v ? u : v;
+    u = dpp64<0x118>(v), v = u > v ? u : v;
+    u = dpp64<0x142, 0xa>(v), v = u > v ? u : v;  // lanes 15 and 47 to the rows above
+    u = dpp64<0x143, 0xc>(v), v = u > v ? u : v;  // lane 31 to the upper half
+    return v;
+}
+template <int CTRL, int ROWS = 0xf>
+__device__ inline float dpp32(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                 CTRL, ROWS, 0xf, true));
+}
+__device__ inline float wave_max_last(float v) {
+    float u;
+    u = dpp32<0x111>(v), v = u > v ? u : v;
+    u = dpp32<0x112>(v), v = u > v ? u : v;
+    u = dpp32<0x114>(v), v = u > v ? u : v;
+    u = dpp32<0x118>(v), v = u > v ? u : v;
+    u = dpp32<0x142, 0xa>(v), v = u > v ? u : v;
+    u = dpp32<0x143, 0xc>(v), v = u > v ? u : v;
     return v;
 }
 
@@ -235,12 +289,12 @@ template <int NT>
 __device__ inline Part block_reduce(double c, double s, double o, double cl) {
     constexpr int NW = NT / 64;
     __shared__ double red[4][NW];
-    c = wave_max(c);
+    c = wave_max_last(c);
     s = wave_sum(s);
     o = wave_sum(o);
     cl = wave_sum(cl);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) {
+    if (lane == 63) {
         red[0][w] = c;
         red[1][w] = s;
         red[2][w] = o;

@@ -28,6 +28,17 @@ struct hexsv_ensemble {
     Part *d_bpart;              // batched mode: one record per global tile
     uint8_t *d_tpar;            // batched mode: parity offset of every global tile
     std::vector<uint8_t> h_tpar;  // what d_tpar holds (empty: not set)
+    // resident steps (k_ens_resident), batched mode only: stacked tiles per workgroup (0: the
+    // ensemble does not fit) and workgroups; exchange memory, step ring, group tables and the
+    // proposed control blocks (allocated when first used), and the next launch's tag
+    int res_sub, res_nwg, ncu;
+    char *d_res;
+    ResSync res;
+    Part *d_ring;
+    ResEnsWg *d_wgs;
+    int2 *d_groups;
+    Ctl *d_out;
+    uint32_t res_tag;
     double dt_max;
     std::vector<const hexsv_grid *> grids;
     std::vector<EnsScen> scen;  // host copy
@@ -90,6 +101,111 @@ static void ens_drop_graph(hexsv_ensemble *e) {
     }
 }
 
+// Steps of one resident launch of an ensemble.
+constexpr int ENS_RES_STEPS = 100;
+
+// Workgroups of a resident launch with `sub` stacked tiles of variant v each.
+static int64_t ens_res_wgs(const hexsv_ensemble *e, int v, int sub) {
+    int64_t n = 0;
+    for (const EnsScen &sc : e->scen)
+        n += (int64_t)((sc.g.nq + TILES[v].tq - 1) / TILES[v].tq) *
+             ((sc.g.nr + TILES[v].tr * sub - 1) / (TILES[v].tr * sub));
+    return n;
+}
+
+// Resident tiling for the batched tile in use: all workgroups of all scenarios resident at
+// once (at most one per compute unit), no periodic raster, and one of the tilings that
+// k_ens_resident is built for.
+static void ens_plan_resident(hexsv_ensemble *e) {
+    e->res_sub = 0;
+    e->res_nwg = 0;
+    for (const EnsScen &sc : e->scen)
+        if (sc.g.perq || sc.g.perr) return;
+    for (int sub = 1; sub <= RES_MAX_SUB; sub *= 2) {
+        if (!(e->btile == 0 || (e->btile == 2 && sub == 1))) return;
+        const int64_t n = ens_res_wgs(e, e->btile, sub);
+        if (n > e->ncu) continue;
+        e->res_sub = sub;
+        e->res_nwg = (int)n;
+        return;
+    }
+}
+
+static void ens_free_resident(hexsv_ensemble *e) {
+    if (e->d_res) (void)hipFree(e->d_res);
+    if (e->d_ring) (void)hipFree(e->d_ring);
+    if (e->d_wgs) (void)hipFree(e->d_wgs);
+    if (e->d_groups) (void)hipFree(e->d_groups);
+    if (e->d_out) (void)hipFree(e->d_out);
+    e->d_res = nullptr;
+    e->d_ring = nullptr;
+    e->d_wgs = nullptr;
+    e->d_groups = nullptr;
+    e->d_out = nullptr;
+}
+
+// Memory and tables of the resident launches; the words are zero (no tag is) before use.  *ok
+// is false where there is no memory for them: single launches do without.
+static hipError_t ens_ensure_resident(hexsv_ensemble *e, hipStream_t st, bool *ok) {
+    const size_t halo = sizeof(unsigned long long) * e->res_nwg *
+                        resident_halo_words(e->esz, e->btile, e->res_sub);
+    const size_t flags = sizeof(unsigned long long) * 2 * (e->esz / 4) * e->res_nwg;
+    const size_t bytes = halo + flags + sizeof(uint32_t) * ((size_t)e->n + e->res_nwg);
+    if (e->d_res && e->res_tag > 0xffff0000u) {  // tags start over on clean words
+        const hipError_t err = hipMemsetAsync(e->d_res, 0, bytes, st);
+        if (err != hipSuccess) return err;
+        e->res_tag = 1;
+    }
+    if (e->d_res) return hipSuccess;
+    std::vector<ResEnsWg> wgs;
+    std::vector<int2> groups;
+    for (int s = 0; s < e->n; ++s) {
+        const EnsScen &sc = e->scen[s];
+        const int tr = TILES[e->btile].tr * e->res_sub;
+        const int cnt = sc.bntq * ((sc.g.nr + tr - 1) / tr), first = (int)wgs.size();
+        for (int i = 0; i < cnt; ++i) wgs.push_back(ResEnsWg{s, first, cnt});
+        groups.push_back(make_int2(first, cnt));
+    }
+    hipError_t err = hipMalloc(&e->d_res, bytes);
+    if (err == hipSuccess) err = hipMalloc(&e->d_ring, sizeof(Part) * (size_t)e->btotal * ENS_RES_STEPS);
+    if (err == hipSuccess) err = hipMalloc(&e->d_wgs, sizeof(ResEnsWg) * wgs.size());
+    if (err == hipSuccess) err = hipMalloc(&e->d_groups, sizeof(int2) * groups.size());
+    if (err == hipSuccess) err = hipMalloc(&e->d_out, sizeof(Ctl) * e->n);
+    if (err == hipSuccess) err = hipMemsetAsync(e->d_res, 0, bytes, st);
+    if (err == hipSuccess)
+        err = hipMemcpy(e->d_wgs, wgs.data(), sizeof(ResEnsWg) * wgs.size(), hipMemcpyHostToDevice);
+    if (err == hipSuccess)
+        err = hipMemcpy(e->d_groups, groups.data(), sizeof(int2) * groups.size(), hipMemcpyHostToDevice);
+    if (err != hipSuccess) {
+        ens_free_resident(e);
+        *ok = false;
+        if (err != hipErrorOutOfMemory) return err;
+        (void)hipGetLastError();
+        return hipSuccess;
+    }
+    e->res.halo = (unsigned long long *)e->d_res;
+    e->res.flags = (unsigned long long *)(e->d_res + halo);
+    e->res.abort_word = (uint32_t *)(e->d_res + halo + flags);
+    e->res.done = e->res.abort_word + e->n;
+    e->res.flag_cap = e->res_nwg;
+    e->res_tag = 1;
+    return hipSuccess;
+}
+
+// One resident launch and its commit.
+template <typename T>
+static hipError_t ens_resident_launch(hexsv_ensemble *e, hipStream_t st) {
+    const uint32_t tag0 = e->res_tag;
+    e->res_tag += ENS_RES_STEPS + 1;
+    hipError_t err = launch_ens_resident<T>(e->btile, e->res_sub, e->visc != 0, e->bc != 0,
+                                            ens_base<T>(e), e->d_scen, e->d_wgs, e->d_ctl, e->d_out,
+                                            e->d_ring, e->res, e->res_nwg, e->btotal, ENS_RES_STEPS,
+                                            tag0, st);
+    if (err != hipSuccess) return err;
+    return launch_ens_fold(e->d_scen, e->d_ctl, e->d_out, e->d_ring, e->res, e->d_groups, e->n,
+                           e->btotal, tag0, st);
+}
+
 static void ens_set_tile(hexsv_ensemble *e, int v) {
     e->tile = v;
     const TileShape ts = ENS_TILES[v];
@@ -129,6 +245,8 @@ static int ens_set_btile(hexsv_ensemble *e, int v) {
         }
     }
     e->btotal = base;
+    ens_free_resident(e);  // sized for the tiling
+    ens_plan_resident(e);
     e->h_tpar.clear();
     ens_drop_graph(e);
     if (e->d_tiles) HIP_TRY(hipMemcpy(e->d_tiles, map.data(), sizeof(EnsTile) * map.size(),
@@ -152,6 +270,7 @@ extern "C" void hexsv_ensemble_destroy(hexsv_ensemble *e) {
     if (e->d_tiles) (void)hipFree(e->d_tiles);
     if (e->d_bpart) (void)hipFree(e->d_bpart);
     if (e->d_tpar) (void)hipFree(e->d_tpar);
+    ens_free_resident(e);
     if (e->h_ctl) (void)hipHostFree(e->h_ctl);
     if (e->h_chk) (void)hipHostFree(e->h_chk);
     delete e;
@@ -210,6 +329,9 @@ extern "C" int hexsv_ensemble_create(int32_t n, const hexsv_grid *const *grids,
         off = (off + 63) / 64 * 64;  // keep every scenario 64 cells aligned
     }
     e->total = off;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&e->ncu, hipDeviceAttributeMultiprocessorCount, dev);
     // mode and tile: explicit, else from the tuning cache (encoded as
     // 100 * mode + tile), else batched steps with the default step tile
     {
@@ -220,6 +342,12 @@ extern "C" int hexsv_ensemble_create(int32_t n, const hexsv_grid *const *grids,
         if (e->mode != HEXSV_ENS_PERSISTENT && e->mode != HEXSV_ENS_BATCHED) e->mode = HEXSV_ENS_BATCHED;
         int v = p.tile >= 0 ? p.tile : (p.ensemble_mode == HEXSV_ENS_AUTO ? tuned % 100 : 0);
         if (p.tile < 0 && p.ensemble_mode == HEXSV_ENS_BATCHED) v = DEFAULT_TILE;
+        // a small FP64 ensemble takes 64 x 4 tiles if four of them per workgroup then fit on the
+        // chip at once: one cell per thread, where 64 x 16 tiles leave four to each thread of a
+        // quarter of the waves.  FP32 keeps the default tile, whose rounding its runs have.
+        if (p.tile < 0 && e->mode == HEXSV_ENS_BATCHED && v == DEFAULT_TILE &&
+            p.precision == HEXSV_FP64 && ens_res_wgs(e, 0, RES_MAX_SUB) <= e->ncu)
+            v = 0;
         const int lim = e->mode == HEXSV_ENS_PERSISTENT ? NUM_ENS_TILES : NUM_TILES;
         if (v < 0 || v >= lim) {
             delete e;
@@ -235,10 +363,7 @@ extern "C" int hexsv_ensemble_create(int32_t n, const hexsv_grid *const *grids,
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(),
                      [&](int32_t x, int32_t y) { return grids[x]->n > grids[y]->n; });
-    int dev = 0, ncu = 1;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    e->nwg = std::min(n, std::max(ncu, 1));
+    e->nwg = std::min(n, std::max(e->ncu, 1));
     hipError_t err = hipMalloc(&e->buf, e->esz * 9 * (size_t)e->total);
     if (err == hipSuccess) err = hipMalloc(&e->d_scen, sizeof(EnsScen) * n);
     if (err == hipSuccess) err = hipMalloc(&e->d_ctl, sizeof(Ctl) * n);
@@ -440,16 +565,46 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
         steps0[s] = c.steps;
     }
     HIP_TRY(hipMemcpyAsync(e->d_ctl, e->h_ctl, sizeof(Ctl) * e->n, hipMemcpyHostToDevice, stream));
-    if (!e->gexec[0]) {
-        int rc = ens_capture(e);
-        if (rc) return rc;
-    }
-    if (e->mode == HEXSV_ENS_BATCHED) HIP_TRY(ens_set_parities(e, e->h_ctl, stream));
+    // an ensemble that fits on the chip steps in resident launches; scenarios whose part of
+    // one was given up (see k_resident) are left to single launches
+    bool resident = e->mode == HEXSV_ENS_BATCHED && e->res_sub > 0 &&
+                    resident_fits(e->esz, e->btile, e->res_sub, e->visc != 0);
+    if (resident) HIP_TRY(ens_ensure_resident(e, stream, &resident));
+    bool prepared = false;
     int64_t launched = 0;  // batched launches since the parities were set
     for (;;) {
+        if (!resident && !prepared) {
+            if (!e->gexec[0]) {
+                int rc = ens_capture(e);
+                if (rc) return rc;
+            }
+            if (e->mode == HEXSV_ENS_BATCHED) HIP_TRY(ens_set_parities(e, e->h_ctl, stream));
+            prepared = true;
+        }
+        std::vector<int64_t> before;
+        int reps = 1;
+        if (resident) {  // as many launches as the slowest scenario is expected to need
+            double need = 1.0;
+            before.resize(e->n);
+            for (int s = 0; s < e->n; ++s) {
+                const Ctl &c = e->h_ctl[s];
+                before[s] = c.steps;
+                const double dt = c.tau < c.dt_max ? c.tau : c.dt_max;
+                double m = dt > 0.0 ? (c.t_end - c.t) / dt : 1.0;
+                m = fmin(m, (double)(c.step_limit - c.steps));
+                need = fmax(need, m);
+            }
+            reps = (int)fmin(32.0, ceil(need / ENS_RES_STEPS));
+        }
         if (e->timing) HIP_TRY(hipEventRecord(e->ev0, stream));
-        HIP_TRY(hipGraphLaunch(e->gexec[launched & 1], stream));
-        launched += e->ksteps;
+        if (resident) {
+            for (int k = 0; k < reps; ++k)
+                HIP_TRY(e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, stream)
+                                              : ens_resident_launch<float>(e, stream));
+        } else {
+            HIP_TRY(hipGraphLaunch(e->gexec[launched & 1], stream));
+            launched += e->ksteps;
+        }
         if (e->timing) HIP_TRY(hipEventRecord(e->ev1, stream));
         HIP_TRY(hipMemcpyAsync(e->h_ctl, e->d_ctl, sizeof(Ctl) * e->n, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
@@ -457,16 +612,18 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
             float ms = 0.f;
             HIP_TRY(hipEventElapsedTime(&ms, e->ev0, e->ev1));
             e->timed_ms += ms;
-            e->timed_launches += 1;
+            e->timed_launches += reps;
         }
-        bool all = true;
+        bool all = true, stuck = false;
         for (int s = 0; s < e->n; ++s) {
             if (e->h_ctl[s].err)
                 return fail(HEXSV_ENUMERIC, "ensemble_run: non-finite value in scenario %d at cell %d",
                             s, e->h_ctl[s].err_cell);
             all = all && ens_done(e->h_ctl[s]);
+            stuck = stuck || (resident && !ens_done(e->h_ctl[s]) && e->h_ctl[s].steps == before[s]);
         }
         if (all) break;
+        if (stuck) resident = false;
     }
     if (e->timing)
         for (int s = 0; s < e->n; ++s) e->timed_updates += (e->h_ctl[s].steps - steps0[s]) * e->active[s];

@@ -84,6 +84,64 @@ hipError_t launch_step(int variant, const KDom<T> &d, const KGrid &g, const KCon
                        const KRain &rn, Ctl *ctl, const KClose &cl, int ntq, int ntiles, int nwg,
                        int par_hint, int in, int set, hipStream_t stream);
 
+// Exchange memory of the resident steps (k_resident): halo words of every tile and
+// wave-speed words of every workgroup (both twice, by the tag's parity), the word
+// that gives a launch up, and each workgroup's mark that it reached the end.
+struct ResSync {
+    unsigned long long *halo, *flags;
+    uint32_t *abort_word, *done;
+    int flag_cap;  // workgroups the flags and marks are sized for
+};
+// The workgroups of a resident launch that advance one domain together: the first one's
+// index in the launch, their number, this one's index among them, tiles per row, records per
+// ring slot and the word that gives their part of the launch up.
+struct ResGroup {
+    int first, count, wg, ntq, ring_stride;
+    uint32_t *abort_word;
+};
+// A workgroup of an ensemble's resident launch: its scenario and that scenario's group.
+struct ResEnsWg {
+    int s, first, count;
+};
+constexpr int RES_MAX_SUB = 4;
+// Does a resident workgroup fit a CU: its LDS (records, codes, with the viscous flux wave
+// speeds, and the reduction scratch) the 160 KB, and its cells the registers?  The FP64 viscous
+// edge sums of four cells per thread do not: 344 to 487 registers spill, with the sums in
+// scratch memory, and the 64 x 32 tiles then lost some of them; single launches do those.
+constexpr bool resident_fits(size_t esz, int variant, int sub, bool visc) {
+    if (visc && esz == 8 && !(variant == 0 || (variant == 1 && sub <= 2))) return false;
+    const size_t ns = (size_t)(TILES[variant].tq + 2) * (TILES[variant].tr * sub + 2);
+    return ns * (4 * esz + 1 + (visc ? esz : 0)) + 2048 <= 160 * 1024;
+}
+// 64-bit halo words of one tile (both parities).
+inline size_t resident_halo_words(size_t esz, int variant, int sub) {
+    return (size_t)2 * 3 * (esz / 4) * 2 * (TILES[variant].tq + TILES[variant].tr * sub);
+}
+// Up to max_steps steps in one launch of nwg workgroups, each a stack of `sub` tiles of
+// `variant` (0, 1 or 2); the launch_fold_resident that follows commits them.
+template <typename T>
+hipError_t launch_resident(int variant, int sub, const KDom<T> &d, const KGrid &g,
+                           const KConst &kc, const KRain &rn, Ctl *ctl, const KClose &cl,
+                           const ResSync &rs, int ntq, int nwg, int ntiles, int max_steps,
+                           uint32_t tag0, hipStream_t stream);
+// The same for the scenarios of an ensemble, side by side: nwg workgroups (`wgs`, grouped by
+// scenario), control blocks in `ctl` and proposed ones in `out`, btotal records per ring slot;
+// variant 0 with any sub, or variant 2 with one.  launch_ens_fold commits the scenarios all of
+// whose workgroups reached the end.
+template <typename T>
+hipError_t launch_ens_resident(int variant, int sub, bool visc, bool bc, const KDom<T> &base,
+                               const EnsScen *scen, const ResEnsWg *wgs, const Ctl *ctl, Ctl *out,
+                               Part *ring, const ResSync &rs, int nwg, int btotal, int max_steps,
+                               uint32_t tag0, hipStream_t stream);
+hipError_t launch_ens_fold(const EnsScen *scen, Ctl *ctl, const Ctl *out, const Part *ring,
+                           const ResSync &rs, const int2 *groups, int nscen, int btotal,
+                           uint32_t tag0, hipStream_t stream);
+// Commit the resident launch of tag0 (control slot 1, up to `slots` steps in the ring)
+// if all nwg workgroups reached its end; otherwise change nothing.
+hipError_t launch_fold_resident(Ctl *ctl, const KClose &cl, int ntiles, const KConst &kc,
+                                const KRain &rn, int slots, const ResSync &rs, int nwg,
+                                uint32_t tag0, hipStream_t stream);
+
 // After a run of `launches` step launches since the previous fold, the last of
 // which read slot `in` with accumulator set `set`: close its pending step, add
 // the books of every closed step in the ring to ctl[0] in step order, empty the

@@ -66,9 +66,25 @@ __device__ inline void ring_slot(int t, int &lq, int &lr) {
 // through the halo (or a periodic wrap), or outside the raster.
 enum : uint8_t { POS_OWN = 0, POS_NEIGHBOUR = 1, POS_OUTSIDE = 2 };
 
-template <typename T, int TQ, int TR, int NT>
+// SUB > 1: the tile is a stack of SUB sub-tiles of TQ x TR/SUB cells; each belongs to 256
+// threads (real ones, or a second set that the same NT threads stand for), which own the
+// cells that a workgroup of 256 threads with that tile alone would give them.
+template <typename T, int TQ, int TR, int NT, int SUB = 1>
 struct TileRegs {
     static constexpr int CPT = (TQ * TR) / NT;
+    static constexpr int M = SUB == 1 ? NT : 256;        // threads of a sub-tile
+    static constexpr int CPS = TQ * (TR / SUB) / M;      // cells of one of them
+    // sub-tile of thread tid's k-th cell, and the cell's column and row in the tile
+    __device__ static inline int sub_of(int tid, int k) {
+        return SUB == 1 ? 0 : tid / M + (k / CPS) * (NT / M);
+    }
+    __device__ static inline void cell(int tid, int k, int &lq, int &lr) {
+        const int sub = sub_of(tid, k);
+        const int cc = (SUB == 1 ? tid : tid % M) + (k % CPS) * M;
+        lr = cc / TQ;
+        lq = cc - lr * TQ;
+        lr += sub * (TR / SUB);
+    }
     static constexpr int NRING = 2 * (TQ + 2) + 2 * TR;
     static constexpr int RPT = (NRING + NT - 1) / NT;
     static_assert(CPT * NT == TQ * TR, "tile must be a multiple of the workgroup");
@@ -105,10 +121,10 @@ __device__ inline bool tile_inner(const KGrid &g, int q0, int r0, int TQ, int TR
 
 // ------------------------------------------------------------------ load
 
-template <typename T, int TQ, int TR, int NT>
-__device__ inline void tile_load(TileRegs<T, TQ, TR, NT> &R, const KDom<T> &d, const KGrid &g,
-                                 int par, int tq, int tr) {
-    using Regs = TileRegs<T, TQ, TR, NT>;
+template <typename T, int TQ, int TR, int NT, int SUB = 1>
+__device__ inline void tile_load(TileRegs<T, TQ, TR, NT, SUB> &R, const KDom<T> &d,
+                                 const KGrid &g, int par, int tq, int tr) {
+    using Regs = TileRegs<T, TQ, TR, NT, SUB>;
     const int q0 = tq * TQ, r0 = tr * TR;
     const T *__restrict__ hin = d.buf(par, 0);
     const T *__restrict__ v1in = d.buf(par, 1);
@@ -121,8 +137,8 @@ __device__ inline void tile_load(TileRegs<T, TQ, TR, NT> &R, const KDom<T> &d, c
     constexpr bool STREAM = TQ >= 128;
 #pragma unroll
     for (int k = 0; k < Regs::CPT; ++k) {
-        const int cc = threadIdx.x + k * NT;
-        const int lr = cc / TQ, lq = cc - lr * TQ;
+        int lq, lr;
+        Regs::cell(threadIdx.x, k, lq, lr);
         int q = q0 + lq, r = r0 + lr;
         uint8_t pos = POS_OWN;
         if (!(inner || (q < g.nq && r < g.nr)))
@@ -162,14 +178,52 @@ __device__ inline void tile_load(TileRegs<T, TQ, TR, NT> &R, const KDom<T> &d, c
 
 // ----------------------------------------------------------------- stage
 
+// The staged record of a raster cell, {mass, w, v1/2, v2/2} (see the file's head).
+// EXT: the cell may be a boundary cell: Dirichlet (-theta: |theta| h) or given flux
+// (-2: the discharge's depth, and the bed only, as the edge adds the cell's depth).
+template <typename T, bool EXT>
+__device__ inline typename Rec<T>::type cell_rec(T h, T th, T z, T v1, T v2, T G, T mscale) {
+    if constexpr (EXT) {
+        const bool fl = th < T(-1.5);
+        const T m = fl ? h : __builtin_fabs(th) * h;
+        const T w = fl ? z : G * (z + h);
+        return make_rec<T>(mscale * m, w, v1 * T(0.5), v2 * T(0.5));
+    } else {
+        const T m = th * h;
+        return make_rec<T>(mscale * m, G * (z + h), v1 * T(0.5), v2 * T(0.5));
+    }
+}
+
+// Its edge code as its neighbours see it.
+template <typename T, bool EXT>
+__device__ inline uint8_t cell_code(T th, const KGrid &g) {
+    if constexpr (EXT)
+        return th > T(0) ? (uint8_t)CODE_INTERIOR
+                         : (th < T(-1.5) ? (uint8_t)CODE_FLUX
+                                         : th < T(0) ? (uint8_t)CODE_DIRICHLET
+                                                     : (uint8_t)g.mask_bc);
+    else
+        return th > T(0) ? (uint8_t)CODE_INTERIOR : (uint8_t)g.mask_bc;
+}
+
+// Its wave speed for the viscous flux.
+template <typename T>
+__device__ inline T cell_wave(T h, T v1, T v2, T G) {
+    T vv;  // the fused square is named, so that every kernel rounds c alike
+    if constexpr (sizeof(T) == 4) vv = __builtin_fmaf(v1, v1, v2 * v2);
+    else vv = v1 * v1 + v2 * v2;
+    return p_sqrt(vv) + p_sqrt(G * h);
+}
+
 // Write the LDS records; returns true if a staged raster cell is inactive.
 // EXT: the extended scheme: the raster may hold Dirichlet or given-flux cells
 // (theta < 0), and the mass source may lose infiltration; the plain instance keeps
 // the plain records and mass update.
-template <typename T, int TQ, int TR, int NT, bool EXT = false, bool V>
-__device__ inline bool tile_stage(TileLDS<T, TQ, TR, V> &L, const TileRegs<T, TQ, TR, NT> &R,
-                                  const KGrid &g, const KConst &kc, int tq, int tr) {
-    using Regs = TileRegs<T, TQ, TR, NT>;
+template <typename T, int TQ, int TR, int NT, bool EXT = false, bool V, int SUB>
+__device__ inline bool tile_stage(TileLDS<T, TQ, TR, V> &L,
+                                  const TileRegs<T, TQ, TR, NT, SUB> &R, const KGrid &g,
+                                  const KConst &kc, int tq, int tr) {
+    using Regs = TileRegs<T, TQ, TR, NT, SUB>;
     constexpr int W = TQ + 2;
     constexpr bool F32 = sizeof(T) == 4;
     const int q0 = tq * TQ, r0 = tr * TR;
@@ -178,41 +232,25 @@ __device__ inline bool tile_stage(TileLDS<T, TQ, TR, V> &L, const TileRegs<T, TQ
     const T G = (T)kc.g;
     const T mscale = F32 ? (T)kc.a : T(1);
     bool bad = false;
-#pragma unroll
-    for (int k = 0; k < Regs::CPT; ++k) {
-        const int cc = threadIdx.x + k * NT;
-        const int lr = cc / TQ, lq = cc - lr * TQ;
-        const int s = (lr + 1) * W + (lq + 1);
-        if (R.pos[k] != POS_OUTSIDE) {
-            const bool act = R.th[k] > T(0);
-            if constexpr (EXT) {
-                // boundary cells: Dirichlet (-theta: |theta| h) or given flux (-2: the
-                // discharge's depth, and the bed only, as the edge adds the cell's depth)
-                const bool fl = R.th[k] < T(-1.5);
-                const T m = fl ? R.h[k] : __builtin_fabs(R.th[k]) * R.h[k];
-                const T w = fl ? R.z[k] : G * (R.z[k] + R.h[k]);
-                L.rec[s] = make_rec<T>(mscale * m, w, R.v1[k] * T(0.5), R.v2[k] * T(0.5));
-                if (need_codes)
-                    L.code[s] = act ? (uint8_t)CODE_INTERIOR
-                                    : (fl ? (uint8_t)CODE_FLUX
-                                          : R.th[k] < T(0) ? (uint8_t)CODE_DIRICHLET
-                                                           : (uint8_t)g.mask_bc);
-            } else {
-                const T m = R.th[k] * R.h[k];
-                L.rec[s] = make_rec<T>(mscale * m, G * (R.z[k] + R.h[k]), R.v1[k] * T(0.5),
-                                       R.v2[k] * T(0.5));
-                if (need_codes) L.code[s] = act ? (uint8_t)CODE_INTERIOR : (uint8_t)g.mask_bc;
-            }
-            if constexpr (V)
-                L.c[s] = p_sqrt(R.v1[k] * R.v1[k] + R.v2[k] * R.v2[k]) + p_sqrt(G * R.h[k]);
-            bad |= !act;
+    auto put_cell = [&](int s, uint8_t pos, T h, T th, T z, T v1, T v2, int q, int r) {
+        if (pos != POS_OUTSIDE) {
+            L.rec[s] = cell_rec<T, EXT>(h, th, z, v1, v2, G, mscale);
+            if (need_codes) L.code[s] = cell_code<T, EXT>(th, g);
+            if constexpr (V) L.c[s] = cell_wave(h, v1, v2, G);
+            bad |= !(th > T(0));
         } else {
-            int q = q0 + lq, r = r0 + lr;
             wrap_pos(g, q, r);
             L.rec[s] = make_rec<T>(T(0), T(0), T(0), T(0));
             if constexpr (V) L.c[s] = T(0);
             L.code[s] = (uint8_t)side_code(g, q, r);
         }
+    };
+#pragma unroll
+    for (int k = 0; k < Regs::CPT; ++k) {
+        int lq, lr;
+        Regs::cell(threadIdx.x, k, lq, lr);
+        put_cell((lr + 1) * W + (lq + 1), R.pos[k], R.h[k], R.th[k], R.z[k], R.v1[k], R.v2[k],
+                 q0 + lq, r0 + lr);
     }
 #pragma unroll
     for (int k = 0; k < Regs::RPT; ++k) {
@@ -220,91 +258,113 @@ __device__ inline bool tile_stage(TileLDS<T, TQ, TR, V> &L, const TileRegs<T, TQ
         if (t >= Regs::NRING) continue;
         int lq, lr;
         ring_slot<TQ, TR>(t, lq, lr);
-        const int s = lr * W + lq;
-        if (R.rpos[k] != POS_OUTSIDE) {
-            const bool act = R.rth[k] > T(0);
-            if constexpr (EXT) {
-                const bool fl = R.rth[k] < T(-1.5);
-                const T m = fl ? R.rh[k] : __builtin_fabs(R.rth[k]) * R.rh[k];
-                const T w = fl ? R.rz[k] : G * (R.rz[k] + R.rh[k]);
-                L.rec[s] = make_rec<T>(mscale * m, w, R.rv1[k] * T(0.5), R.rv2[k] * T(0.5));
-                if (need_codes)
-                    L.code[s] = act ? (uint8_t)CODE_INTERIOR
-                                    : (fl ? (uint8_t)CODE_FLUX
-                                          : R.rth[k] < T(0) ? (uint8_t)CODE_DIRICHLET
-                                                            : (uint8_t)g.mask_bc);
-            } else {
-                const T m = R.rth[k] * R.rh[k];
-                L.rec[s] = make_rec<T>(mscale * m, G * (R.rz[k] + R.rh[k]), R.rv1[k] * T(0.5),
-                                       R.rv2[k] * T(0.5));
-                if (need_codes) L.code[s] = act ? (uint8_t)CODE_INTERIOR : (uint8_t)g.mask_bc;
-            }
-            if constexpr (V)
-                L.c[s] = p_sqrt(R.rv1[k] * R.rv1[k] + R.rv2[k] * R.rv2[k]) + p_sqrt(G * R.rh[k]);
-            bad |= !act;
-        } else {
-            int q = q0 + lq - 1, r = r0 + lr - 1;
-            wrap_pos(g, q, r);
-            L.rec[s] = make_rec<T>(T(0), T(0), T(0), T(0));
-            if constexpr (V) L.c[s] = T(0);
-            L.code[s] = (uint8_t)side_code(g, q, r);
-        }
+        put_cell(lr * W + lq, R.rpos[k], R.rh[k], R.rth[k], R.rz[k], R.rv1[k], R.rv2[k],
+                 q0 + lq - 1, r0 + lr - 1);
     }
     return bad;
 }
 
+// Where a step's results go: into the other buffer, with the first non-finite cell
+// of the step named in the control block.
+template <typename T, bool NT_STORE>
+struct StoreSink {
+    T *__restrict__ hout;
+    T *__restrict__ v1out;
+    T *__restrict__ v2out;
+    int32_t *err_flag, *err_cell;
+    __device__ inline void put_state(int, uint32_t i, T h, T v1, T v2) {
+        put<T, NT_STORE>(at(hout, i), h);
+        put<T, NT_STORE>(at(v1out, i), v1);
+        put<T, NT_STORE>(at(v2out, i), v2);
+    }
+    __device__ inline void nonfinite(uint32_t i) {
+        if (atomicOr(err_flag, 1) == 0) *err_cell = (int32_t)i;
+    }
+    // rare: was this one of the offending cells?  (the values this thread just stored)
+    __device__ inline void rescan(uint32_t i) {
+        if (!__builtin_isfinite(ld(hout, i)) || !__builtin_isfinite(ld(v1out, i)) ||
+            !__builtin_isfinite(ld(v2out, i)))
+            nonfinite(i);
+    }
+};
+
 // --------------------------------------------------------------- compute
 
-template <typename T, int TQ, int TR, int NT, bool NT_STORE, bool V, bool EXT = false>
-__device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRegs<T, TQ, TR, NT> &R,
-                                    bool general, const KDom<T> &d, const KGrid &g,
-                                    const KConst &kc, int par, int tq, int tr, double dt,
-                                    double r_next, Acc &acc, int32_t *err_flag,
-                                    int32_t *err_cell) {
-    using Regs = TileRegs<T, TQ, TR, NT>;
-    constexpr int W = TQ + 2;
-    constexpr bool F32 = sizeof(T) == 4;
-    const int q0 = tq * TQ, r0 = tr * TR;
-    T *__restrict__ hout = d.buf(par ^ 1, 0);
-    T *__restrict__ v1out = d.buf(par ^ 1, 1);
-    T *__restrict__ v2out = d.buf(par ^ 1, 2);
-    const T G = (T)kc.g;
-    const T mscale = F32 ? (T)kc.a : T(1);
-    const T l = (T)kc.a;
-    const T half_l = (T)(0.5 * kc.a);
-    const T dtT = (T)dt;
-    const T dts = (T)(dt / kc.sigma);
-    const T rT = (T)r_next;
-    const T alpha_s = (T)kc.alpha_s;
+// What a step's cells share.
+template <typename T>
+struct StepConst {
+    T dt, dts, r, alpha_s, ftau, h_dry;
+    bool lin;
+};
+template <typename T>
+__device__ inline StepConst<T> step_const(const KConst &kc, double dt, double r_next) {
+    StepConst<T> c;
+    c.dt = (T)dt;
+    c.dts = (T)(dt / kc.sigma);
+    c.r = (T)r_next;
+    c.alpha_s = (T)kc.alpha_s;
     // linear soil resistance theta tau h v, implicit in v^{n+1}: the coefficient of
     // v is m^{n+1} + dt tau m^{n+1} = m^{n+1} (1 + dt tau) (exactly m^{n+1} at tau = 0)
-    const bool lin = kc.tau_lin != 0.0;
-    const T ftau = T(1) + dtT * (T)kc.tau_lin;
-    const T h_dry = (T)kc.h_dry;
-    const T S3H = (T)0.86602540378443864676;
-    const T NX[6] = {T(1), T(0.5), T(-0.5), T(-1), T(-0.5), T(0.5)};
-    const T NY[6] = {T(0), S3H, S3H, T(0), -S3H, -S3H};
-    const T NXh[6] = {T(0.5), T(0.25), T(-0.25), T(-0.5), T(-0.25), T(0.25)};
-    const T NYh[6] = {T(0), T(0.5) * S3H, T(0.5) * S3H, T(0), -T(0.5) * S3H, -T(0.5) * S3H};
-    constexpr int OFF[6] = {1, W, W - 1, -1, -W, -W + 1};
+    c.lin = kc.tau_lin != 0.0;
+    c.ftau = T(1) + c.dt * (T)kc.tau_lin;
+    c.h_dry = (T)kc.h_dry;
+    return c;
+}
 
-    float cmax32 = 0.f, m32 = 0.f;  // FP32 path: c_max and sum theta h of this thread's cells
-    float wsum = 0.f;
-    auto cell = [&](int k, auto gen_tag) {
-        constexpr bool GEN = decltype(gen_tag)::value;
-        const int cc = threadIdx.x + k * NT;
-        const int lr = cc / TQ, lq = cc - lr * TQ;
+// Edge sums of a cell's step (what does not depend on dt): L, J (with V, J^v) + S, and
+// the outward flux of open edges; with them the cell's staged half velocity.
+template <typename T>
+struct EdgeSums {
+    T Ls, A1, A2, Fout, vh1, vh2;
+};
+
+// A thread's partial reductions that FP32 keeps in FP32 until its last cell: c_max, the sum
+// of theta h, and a sum that any non-finite h or v makes non-finite.
+struct Partial32 {
+    float cmax = 0.f, m = 0.f, any = 0.f;
+};
+
+// The step of thread tid's cells of the tile staged in L: edges, then finish.
+template <typename T, int TQ, int TR, int NT, bool V, bool EXT, int SUB>
+struct TileCells {
+    using Regs = TileRegs<T, TQ, TR, NT, SUB>;
+    static constexpr int W = TQ + 2;
+    static constexpr bool F32 = sizeof(T) == 4;
+    const TileLDS<T, TQ, TR, V> &L;
+    const Regs &R;
+    const KDom<T> &d;
+    const KGrid &g;
+    const KConst &kc;
+    int q0, r0;
+    T G, l, half_l;
+
+    __device__ inline TileCells(const TileLDS<T, TQ, TR, V> &L_, const Regs &R_, const KDom<T> &d_,
+                                const KGrid &g_, const KConst &kc_, int tq, int tr)
+        : L(L_), R(R_), d(d_), g(g_), kc(kc_), q0(tq * TQ), r0(tr * TR), G((T)kc_.g),
+          l((T)kc_.a), half_l((T)(0.5 * kc_.a)) {}
+
+    // GEN: edges may be walls, open, or lead to boundary cells (codes are staged)
+    template <bool GEN>
+    __device__ inline EdgeSums<T> edges(int tid, int k) const {
+        const T S3H = (T)0.86602540378443864676;
+        const T NX[6] = {T(1), T(0.5), T(-0.5), T(-1), T(-0.5), T(0.5)};
+        const T NY[6] = {T(0), S3H, S3H, T(0), -S3H, -S3H};
+        const T NXh[6] = {T(0.5), T(0.25), T(-0.25), T(-0.5), T(-0.25), T(0.25)};
+        const T NYh[6] = {T(0), T(0.5) * S3H, T(0.5) * S3H, T(0), -T(0.5) * S3H, -T(0.5) * S3H};
+        constexpr int OFF[6] = {1, W, W - 1, -1, -W, -W + 1};
+        int lq, lr;
+        Regs::cell(tid, k, lq, lr);
         const int s = (lr + 1) * W + (lq + 1);
         const int q = q0 + lq, r = r0 + lr;
-        const T hi = R.h[k], thi = R.th[k];
-        const T mi = thi * hi;
+        const T hi = R.h[k];
+        const T mi = R.th[k] * hi;
         // the cell's own staged record (the values its neighbours see, formed by the same
         // operations), so that the bed register is free after staging; FP32 also takes
         // its velocity as twice the staged half, FP64 keeps the loaded one
         const typename Rec<T>::type me = L.rec[s];
         const T Mi = me.x, wi = me.y, vh1i = me.z, vh2i = me.w;
         T Ls = T(0), A1 = T(0), A2 = T(0), S1 = T(0), S2 = T(0), Fout = T(0);
-        T V1 = T(0), V2 = T(0);  // viscous part of J^v (V only)
+        T V1 = T(0), V2 = T(0);
 #pragma unroll
         for (int e = 0; e < 6; ++e) {
             const int sn = s + OFF[e];
@@ -416,26 +476,49 @@ __device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRe
                 }
             }
         }
+        if constexpr (V) {
+            A1 = A1 + V1;
+            A2 = A2 + V2;
+        }
+        if constexpr (!F32) {  // FP32 sums the pressure part with J
+            A1 = A1 + S1;
+            A2 = A2 + S2;
+        }
+        return EdgeSums<T>{Ls, A1, A2, Fout, vh1i, vh2i};
+    }
+
+    // The new state from the sums: mass and depth, friction solve, reductions.
+    template <bool GEN, typename Sink>
+    __device__ inline void finish(int tid, int k, const EdgeSums<T> &es, const StepConst<T> &sc,
+                                  double dt, Acc &acc, Partial32 &p32, Sink &sink) const {
+        const T dtT = sc.dt, dts = sc.dts, rT = sc.r, ftau = sc.ftau, h_dry = sc.h_dry;
+        const T Ls = es.Ls, A1 = es.A1, A2 = es.A2, Fout = es.Fout;
+        int lq, lr;
+        Regs::cell(tid, k, lq, lr);
+        const int q = q0 + lq, r = r0 + lr;
+        const T hi = R.h[k], thi = R.th[k];
+        const T mi = thi * hi;
+        const T vh1i = es.vh1, vh2i = es.vh2;
         const T v1i = F32 ? vh1i + vh1i : R.v1[k], v2i = F32 ? vh2i + vh2i : R.v2[k];
         T m1, h1, g1, g2;
         if constexpr (F32) {
-            const T dm = dts * Ls + dtT * rT;
-            m1 = mi + dm;
+            // fused multiply-adds are written out where the compiler could place them
+            // otherwise from one kernel to the next (a factor formed outside the block, a
+            // product with one use or several), so that every kernel of a tile shape
+            // rounds alike; with one cell per thread the rain term is the fused one
+            const T dm = Regs::CPS == 1 ? __builtin_fmaf(dtT, rT, dts * Ls)
+                                        : __builtin_fmaf(dts, Ls, dtT * rT);
+            m1 = __builtin_fmaf(thi, hi, dm);
             if (m1 < T(0)) {
                 acc.cl += kc.sigma * (-(double)m1);
                 m1 = T(0);
                 h1 = T(0);
             } else {
-                h1 = hi + p_div(dm, thi);
+                h1 = __builtin_fmaf(dm, __builtin_amdgcn_rcpf(thi), hi);  // hi + p_div(dm, thi)
                 h1 = h1 > T(0) ? h1 : T(0);
             }
-            if constexpr (V) {
-                g1 = mi * v1i + dts * (A1 + V1);
-                g2 = mi * v2i + dts * (A2 + V2);
-            } else {
-                g1 = mi * v1i + dts * A1;
-                g2 = mi * v2i + dts * A2;
-            }
+            g1 = __builtin_fmaf(mi, v1i, dts * A1);
+            g2 = __builtin_fmaf(mi, v2i, dts * A2);
         } else {
             const T ms = mi + dts * Ls;
             m1 = ms + dtT * rT;
@@ -444,13 +527,8 @@ __device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRe
                 m1 = T(0);
             }
             h1 = p_div(m1, thi);
-            if constexpr (V) {  // J^v = J + viscous sums, then the pressure part
-                g1 = mi * v1i + dts * ((A1 + V1) + S1);
-                g2 = mi * v2i + dts * ((A2 + V2) + S2);
-            } else {
-                g1 = mi * v1i + dts * (A1 + S1);
-                g2 = mi * v2i + dts * (A2 + S2);
-            }
+            g1 = mi * v1i + dts * A1;
+            g2 = mi * v2i + dts * A2;
         }
         if constexpr (EXT) {
             if (kc.f_inf > 0.0 && m1 > T(0)) {
@@ -460,54 +538,112 @@ __device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRe
                 // increment) the loss e is the smaller root of theta e^2 - P e + dt f h1,
                 // P = theta (h1 + c) + dt f; the soil's water is booked with the outflow
                 const T c = (T)kc.h_inf, fd = dtT * (T)kc.f_inf, hs = h1;
-                const T P = thi * (hs + c) + fd;
-                const T Q = thi * (hs + c) - fd;
-                const T Dq = Q * Q + T(4) * thi * fd * c;
-                const T e = p_div(T(2) * fd * hs, P + p_sqrt(Dq));
-                const T x = hs - e;
+                T x, lost;
+                if constexpr (F32) {
+                    const T P = __builtin_fmaf(thi, hs + c, fd);
+                    const T Q = __builtin_fmaf(thi, hs + c, -fd);
+                    const T Dq = __builtin_fmaf(T(4) * thi * fd, c, Q * Q);
+                    x = __builtin_fmaf(-(T(2) * fd * hs), __builtin_amdgcn_rcpf(P + p_sqrt(Dq)), hs);
+                    lost = __builtin_fmaf(-thi, x, m1);
+                } else {
+                    const T P = thi * (hs + c) + fd;
+                    const T Q = thi * (hs + c) - fd;
+                    const T Dq = Q * Q + T(4) * thi * fd * c;
+                    const T e = p_div(T(2) * fd * hs, P + p_sqrt(Dq));
+                    x = hs - e;
+                    lost = m1 - thi * x;
+                }
                 const T mx = thi * x;
-                acc.o += kc.sigma * (double)(m1 - mx);
+                acc.o += kc.sigma * (double)lost;
                 m1 = mx;
                 h1 = x;
             }
         }
         const uint32_t i = (uint32_t)(r * g.pitch + q);
-        T as_i = alpha_s;
+        T as_i = sc.alpha_s;
         if constexpr (EXT) {
             if (d.as) as_i = ld(d.as, i);  // a soil coefficient per cell
         }
-        const T K = R.ap[k] * h1 * (T(1) - thi) + thi * as_i;
+        T K;
+        if constexpr (F32 && EXT) K = __builtin_fmaf(R.ap[k] * h1, T(1) - thi, thi * as_i);
+        else if constexpr (F32) K = __builtin_fmaf(thi, as_i, R.ap[k] * h1 * (T(1) - thi));
+        else K = R.ap[k] * h1 * (T(1) - thi) + thi * as_i;
         const T beta = dtT * K;
-        const T Gm = p_sqrt(g1 * g1 + g2 * g2);
+        T gg;
+        if constexpr (F32) gg = GEN ? __builtin_fmaf(g2, g2, g1 * g1) : __builtin_fmaf(g1, g1, g2 * g2);
+        else gg = g1 * g1 + g2 * g2;
+        const T Gm = p_sqrt(gg);
         T alpha = m1;
-        if (lin) alpha = m1 * ftau;
-        const T D = alpha + p_sqrt(alpha * alpha + T(4) * beta * Gm);
+        if (sc.lin) alpha = m1 * ftau;
+        T disc;
+        if constexpr (F32) disc = __builtin_fmaf(alpha, alpha, T(4) * beta * Gm);
+        else disc = alpha * alpha + T(4) * beta * Gm;
+        const T D = alpha + p_sqrt(disc);
         T mu = (D == T(0)) ? T(0) : p_div(T(2), D);
         if (h_dry > T(0) && h1 < h_dry) mu = T(0);
         const T v1n = mu * g1, v2n = mu * g2;
-        put<T, NT_STORE>(at(hout, i), h1);
-        put<T, NT_STORE>(at(v1out, i), v1n);
-        put<T, NT_STORE>(at(v2out, i), v2n);
+        sink.put_state(k, i, h1, v1n, v2n);
         // wave speed of the new state (eq. fvm_2D_eq_frac.13); FP32 takes |v^{n+1}| as
         // mu |gamma| (the same value up to rounding), FP64 the oracle's sqrt(v1^2 + v2^2)
-        const T vabs = F32 ? mu * Gm : p_sqrt(v1n * v1n + v2n * v2n);
-        const T cc2 = vabs + p_sqrt(G * h1);
+        T cc2;
+        if constexpr (F32) cc2 = __builtin_fmaf(Gm, mu, p_sqrt(G * h1));
+        else cc2 = p_sqrt(v1n * v1n + v2n * v2n) + p_sqrt(G * h1);
         if constexpr (F32) {
             // FP32 partials over this thread's cells, folded into the FP64 books below;
-            // wsum carries any non-finite h or v of the thread's cells to one check
-            cmax32 = cc2 > cmax32 ? cc2 : cmax32;
-            m32 += thi * h1;
-            wsum += cc2;
+            // p32.any carries any non-finite h or v of the thread's cells to one check
+            p32.cmax = cc2 > p32.cmax ? cc2 : p32.cmax;
+            p32.m = __builtin_fmaf(thi, h1, p32.m);
+            p32.any += cc2;
         } else {
             acc.c = (double)cc2 > acc.c ? (double)cc2 : acc.c;
             acc.s += kc.sigma * ((double)thi * (double)h1);
-            if (!__builtin_isfinite(h1) || !__builtin_isfinite(v1n) || !__builtin_isfinite(v2n)) {
-                if (atomicOr(err_flag, 1) == 0) *err_cell = (int32_t)i;
-            }
+            if (!__builtin_isfinite(h1) || !__builtin_isfinite(v1n) || !__builtin_isfinite(v2n))
+                sink.nonfinite(i);
         }
         if (GEN) acc.o += dt * (double)Fout;
-    };
+    }
 
+    // FP32: the thread's partials into the FP64 accumulators, after the last of the cells
+    // (k0 to k1) that they cover.
+    template <typename Sink>
+    __device__ inline void fold32(int tid, int k0, int k1, Acc &acc, const Partial32 &p32,
+                                  Sink &sink) const {
+        if constexpr (F32) {
+            acc.c = (double)p32.cmax > acc.c ? (double)p32.cmax : acc.c;
+            acc.s += kc.sigma * (double)p32.m;
+            if (!__builtin_isfinite(p32.m + p32.any)) {
+                // rare: find the offending cell among the thread's
+#pragma unroll
+                for (int k = k0; k < k1; ++k) {
+                    if (R.pos[k] != POS_OWN) continue;
+                    int lq, lr;
+                    Regs::cell(tid, k, lq, lr);
+                    sink.rescan((uint32_t)((r0 + lr) * g.pitch + q0 + lq));
+                }
+            }
+        }
+    }
+};
+
+// The step of a tile into the other buffer.
+template <typename T, int TQ, int TR, int NT, bool NT_STORE, bool V, bool EXT = false>
+__device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRegs<T, TQ, TR, NT> &R,
+                                    bool general, const KDom<T> &d, const KGrid &g,
+                                    const KConst &kc, int par, int tq, int tr, double dt,
+                                    double r_next, Acc &acc, int32_t *err_flag,
+                                    int32_t *err_cell) {
+    using Regs = TileRegs<T, TQ, TR, NT>;
+    StoreSink<T, NT_STORE> sink{d.buf(par ^ 1, 0), d.buf(par ^ 1, 1), d.buf(par ^ 1, 2), err_flag,
+                                err_cell};
+    const TileCells<T, TQ, TR, NT, V, EXT, 1> cells(L, R, d, g, kc, tq, tr);
+    const StepConst<T> sc = step_const<T>(kc, dt, r_next);
+    Partial32 p32;
+    const int tid = threadIdx.x;
+    auto cell = [&](int k, auto gen) {
+        constexpr bool GEN = decltype(gen)::value;
+        const EdgeSums<T> es = cells.template edges<GEN>(tid, k);
+        cells.template finish<GEN>(tid, k, es, sc, dt, acc, p32, sink);
+    };
     if (general) {
 #pragma unroll
         for (int k = 0; k < Regs::CPT; ++k)
@@ -516,39 +652,7 @@ __device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRe
 #pragma unroll
         for (int k = 0; k < Regs::CPT; ++k) cell(k, std::false_type{});
     }
-    if constexpr (F32) {
-        acc.c = (double)cmax32 > acc.c ? (double)cmax32 : acc.c;
-        acc.s += kc.sigma * (double)m32;
-        if (!__builtin_isfinite(m32 + wsum)) {
-            // rare: find the offending cell among the values this thread just stored
-#pragma unroll
-            for (int k = 0; k < Regs::CPT; ++k) {
-                if (R.pos[k] != POS_OWN) continue;
-                const int cc = threadIdx.x + k * NT;
-                const int lr = cc / TQ, lq = cc - lr * TQ;
-                const uint32_t i = (uint32_t)((r0 + lr) * g.pitch + q0 + lq);
-                if (!__builtin_isfinite(ld(hout, i)) || !__builtin_isfinite(ld(v1out, i)) ||
-                    !__builtin_isfinite(ld(v2out, i))) {
-                    if (atomicOr(err_flag, 1) == 0) *err_cell = (int32_t)i;
-                }
-            }
-        }
-    }
-}
-
-// All three phases for one tile (the caller separates consecutive tiles on
-// the same LDS with a barrier).
-template <typename T, int TQ, int TR, int NT, bool NT_STORE, bool V = false, bool EXT = false>
-__device__ inline void tile_step(TileLDS<T, TQ, TR, V> &L, const KDom<T> &d, const KGrid &g,
-                                 const KConst &kc, int par, int tq, int tr, double dt,
-                                 double r_next, Acc &acc, int32_t *err_flag, int32_t *err_cell) {
-    TileRegs<T, TQ, TR, NT> R;
-    tile_load<T, TQ, TR, NT>(R, d, g, par, tq, tr);
-    const bool bad = tile_stage<T, TQ, TR, NT, EXT>(L, R, g, kc, tq, tr);
-    const bool inner = tile_inner(g, tq * TQ, tr * TR, TQ, TR);
-    const bool general = __syncthreads_or((!inner) || bad) != 0;
-    tile_compute<T, TQ, TR, NT, NT_STORE, V, EXT>(L, R, general, d, g, kc, par, tq, tr, dt, r_next,
-                                             acc, err_flag, err_cell);
+    cells.fold32(tid, 0, Regs::CPT, acc, p32, sink);
 }
 
 }  // namespace hexsv
