@@ -403,10 +403,9 @@ int64_t hexsv_surrogate_num_params(const hexsv_surrogate *sur);
 /* k of create: the solver steps one window spans (EINVAL at create if k < 1).
  * The window calls below take it when their own k is <= 0.  -1 for a null handle. */
 int32_t hexsv_surrogate_steps(const hexsv_surrogate *sur);
-/* Forward of the 4-layer, 32-channel network as one fused kernel (on = 1:
- * activations stay on chip, 16 x 16 output cells per workgroup with a 4-cell
- * halo, 1.46x the MFMA work for the recomputed halo) or one launch per layer
- * (on = 0, the default, which measures faster on 512 x 512 rasters).  Both give
+/* Forward of the 4-layer, 32-channel network as one fused kernel (on = 1, the
+ * default: activations stay on chip, a workgroup sweeps 58 columns row by row
+ * with the layers two rows apart) or one launch per layer (on = 0).  Both give
  * the same outputs bit for bit; other depths always run per layer.  EINVAL:
  * null handle or on not 0/1. */
 int hexsv_surrogate_set_fused(hexsv_surrogate *sur, int32_t on);
@@ -432,11 +431,12 @@ int hexsv_surrogate_forward(hexsv_surrogate *sur, const hexsv_grid *grid, int32_
 /* hexsv_surrogate_forward for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * kernels and result (outputs 0..2 of each cell; the fourth float of d_out is
- * not written), with the packed input and the hidden activations in a static
- * device workspace of 40 MiB that every GPU the library runs on holds until the
- * process ends, instead of the surrogate's own workspace.  It calls no
- * hipMalloc, hipFree or allocating library routine.  The caller passes inputs
- * and outputs as for hexsv_surrogate_forward.  Every call on one GPU shares
+ * not written), where the network runs layer by layer with the packed input and
+ * the hidden activations in a static device workspace of 40 MiB that every GPU
+ * the library runs on holds until the process ends, instead of the surrogate's
+ * own workspace (the fused kernel needs neither).  It calls no hipMalloc,
+ * hipFree or allocating library routine.  The caller passes inputs and outputs
+ * as for hexsv_surrogate_forward.  Every call on one GPU shares
  * that GPU's workspace: calls that overlap on one GPU (other streams or host
  * threads) race; calls on one stream are ordered.  EINVAL: batch*nq*nr above
  * 262144 cells (one 512 x 512 sample), or the arguments hexsv_surrogate_forward

@@ -38,15 +38,15 @@ hipError_t launch_conv(int cinp, int coutp, int epi, const __bf16 *x, const __bf
                        const int32_t *live = nullptr);
 // The 4-layer network with 32 hidden channels in one launch (k_hexnet4): weights
 // and biases of each layer as for launch_conv (layer 0: 16 -> 32, layers 1-2:
-// 32 -> 32, layer 3: 32 -> 16 with cout_real outputs written, FP32, OUT_STRIDE
-// per cell); the output equals the layer-by-layer launch_conv chain bit for bit.
+// 32 -> 32, layer 3: 32 -> 16 with 3 outputs written, FP32, OUT_STRIDE per cell;
+// w4: and a zero); x: the FP32 features (f32in) or the packed bf16 input.  The
+// output equals the layer-by-layer launch_conv chain bit for bit.
 struct Net4 {
     const __bf16 *wm[4];
     const float *bias[4];
 };
-int net4_tiles(int nq, int nr, int batch);
-hipError_t launch_net4(const __bf16 *x, const Net4 &nw, float *out, int nq, int nr, int batch,
-                       int cout_real, const ConvMask &cm, hipStream_t st,
+hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bool w4, int nq,
+                       int nr, int batch, const ConvMask &cm, hipStream_t st,
                        const int32_t *live = nullptr);
 // Weight-gradient partials: one record (7*coutp*cinp + coutp floats) per workgroup of
 // the launch, which sweeps the tiles with its sums in registers.  WGRAD_WGS workgroups

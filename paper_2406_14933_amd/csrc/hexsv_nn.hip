@@ -91,188 +91,351 @@ __global__ __launch_bounds__(NT) void k_hexconv(const __bf16 *__restrict__ x,
 
 // ------------------------------------------------------- fused 4-layer forward
 //
-// The whole 4-layer network (16 -> 32 -> 32 -> 32 -> 16 channels) for a 16 x 16
-// tile of output cells in one workgroup.  The packed input features of the tile
-// and a 4-cell margin (24 x 24 positions) are staged once; layer l is evaluated on
-// the tile grown by 3 - l cells on each side and its activations stay in LDS for
-// layer l + 1, so hidden activations never leave the CU.  Each layer's arithmetic
-// is that of k_hexconv (the same MFMA, the same K order, bias and ReLU, the same
-// bf16 rounding of hidden activations), so the output equals the layer-by-layer
-// chain's bit for bit.  fl[p] is 1 where staged position p holds a cell of the
-// domain (wrapped through periodic sides); a tap t >= 1 reads its neighbour only
-// when the centre and the neighbour both are, which also zeroes every position
-// outside the raster, as the chain's zero staging does.
-namespace f4 {
-constexpr int OT = 16;        // output tile edge
-constexpr int WI = OT + 8;    // staged input frame edge (margin 4)
-constexpr int NG = 4;         // 16-cell column groups per wave pass
+// The whole 4-layer network (16 -> 32 -> 32 -> 32 -> 16 channels) in one kernel: a workgroup
+// sweeps a strip of columns row by row with the four layers two rows apart, so a hidden row
+// lives in LDS for one step and never leaves the CU.  The layer chain moves 540 bytes a cell,
+// most of them hidden activations, against the 56 this reads and writes; on 16 x 512 x 512
+// samples it takes 609 us, this 274 us (its MFMAs run at 0.9 PFLOP/s, where an 8192^3 library
+// product reaches 1.2 on the card).
+//
+// All layers share a frame of 64 columns (four MFMA columns of 16 cells); layer l's outermost
+// l columns lack a neighbour, so 58 columns come out, and 6 of 64 are computed twice (10 % of
+// the MFMA work; the 16 x 16 tiles with a 4-cell margin this replaces spent 46 %).  Sixteen
+// waves: four per layer, one MFMA column each, so every SIMD holds one wave of each layer and
+// has 43 MFMAs a row.  Weights and the operands that a layer's rows share stay in registers for
+// the whole strip.  A row is a chain of short phases (LDS reads, seven dependent MFMAs,
+// epilogue, barrier): four waves per SIMD hide each other's (370 us with two, 475 us with two
+// workgroups of eight waves that read every operand from LDS).
+//
+// Each layer's arithmetic is k_hexconv's: the same MFMA, the same K order, bias, ReLU and bf16
+// rounding, so the output equals the chain's bit for bit.  Positions outside the raster are
+// zero for the taps, as the chain stages them.  MASK: a tap t >= 1 is zero unless the cell and
+// the neighbour are both in the domain (flags staged with the input); without a mask only
+// positions outside the raster (after periodic wraps) are cut, by storing them as zeros.
+namespace r4 {
+constexpr int FW = 64;             // frame columns
+constexpr int OW = FW - 6;         // output columns
+constexpr int LW = FW + 2;         // staged columns (one pad or halo column on each side)
+constexpr int ICH = 4;             // input rows loaded at a time
+constexpr int IRING = 12;          // input rows staged
+constexpr int FRING = 32;          // flag rows staged (layer 3 is 6 rows behind layer 0)
+constexpr int NTH = 1024;
+constexpr int EXTRA = 9;           // steps of a strip beyond its output rows
+constexpr int DQ[7] = {0, 1, 0, -1, -1, 0, 1};
+constexpr int DR[7] = {0, 0, 1, 1, 0, -1, -1};
+}  // namespace r4
+
+// Element offset of 8-channel chunk `ch` of staged column c: a rotation of the chunks by column
+// keeps the 16 cells of an MFMA column on distinct LDS banks without padding (32 channels: four
+// chunks of 16 bytes, 16 channels: two).
+__device__ inline int act_at(int c, int ch) { return c * 32 + ((ch ^ ((c >> 2) & 3)) << 3); }
+__device__ inline int in_at(int c, int ch) { return c * 16 + ((ch ^ ((c >> 3) & 1)) << 3); }
+
+// One MFMA column's operands of the 3 rows around an output row, one set per dq (-1, 0, +1):
+// lane (g, l16) holds channels 8 g .. 8 g + 7 of its cell's neighbour.  Rows take turns: with
+// the newest (above the output row) in slot j, the middle one is in j + 2 and the oldest in
+// j + 1 (mod 3), so that no row is moved; with a domain mask, whose predicates take the registers
+// that three copies of a step need, slot 0 is the newest and rows are moved.
+struct Taps {
+    bf16x8 r[3][3];
+    int in[3];  // MASK: bit dq + 1, the cell is in the domain
+};
+
+// A new row into slot j; staged column c + 1 is frame column c.
+template <bool MASK>
+__device__ inline void taps_push(Taps &t, int j, const __bf16 *row, int c, int g,
+                                 const uint8_t *frow) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+        t.r[j][d] = *reinterpret_cast<const bf16x8 *>(row + act_at(c + d, g));
+    if constexpr (MASK) t.in[j] = frow[c] | frow[c + 1] << 1 | frow[c + 2] << 2;
+}
+// The newest row becomes the middle one, with slot 0 free.
+__device__ inline void taps_move(Taps &t) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        t.r[1][d] = t.r[2][d];
+        t.r[2][d] = t.r[0][d];
+    }
+    t.in[1] = t.in[2];
+    t.in[2] = t.in[0];
+}
+// MASK: the operand of a tap t >= 1 is zero unless both cells are in the domain.
+template <bool MASK>
+__device__ inline bf16x8 tap_of(const Taps &t, int j, int tap) {
+    using namespace r4;
+    const int mid = (j + 2) % 3, k = DR[tap] > 0 ? j : DR[tap] == 0 ? mid : (j + 1) % 3;
+    bf16x8 v = t.r[k][1 + DQ[tap]];
+    if constexpr (MASK)
+        if (tap > 0 && !((t.in[mid] >> 1) & (t.in[k] >> (1 + DQ[tap])) & 1)) v = bf16x8{};
+    return v;
 }
 
-// One layer over a WO x WO frame.  taps_all: every staged position of the tile is
-// a domain cell (an interior tile of an unmasked raster), so no tap is cut.
-// SSTR: 16-byte chunks between consecutive source cells; DSTR: bf16 values
-// between consecutive destination cells (hidden activations are padded from 64
-// to 80 bytes per cell, so that the 16 cells of an MFMA column fall on distinct
-// LDS banks when gathered and when written).
-template <int CIN, int COUT, int EPI, int WO, int SSTR, int DSTR>
-__device__ inline void net_layer(const uint4 *src, uint4 *dst, const uint8_t *fl,
-                                 const __bf16 *__restrict__ wm, const float *__restrict__ bias,
-                                 float *__restrict__ out, int nq, int nr, int64_t soff, int q0,
-                                 int r0, int cout_real, bool taps_all) {
-    using namespace f4;
-    constexpr int CH = CIN / 8;            // 16-byte chunks per source cell
-    constexpr int MB = COUT / 16;
-    constexpr int TPK = 32 / CIN;
-    constexpr int KSTEPS = (7 + TPK - 1) / TPK;
-    constexpr int WS = WO + 2;             // source frame edge
-    constexpr int OI = (WI - WO) / 2;      // this frame's origin in the staged frame
-    constexpr int NCELL = WO * WO;
-    constexpr int NGRP = (NCELL + 15) / 16;
-    constexpr int NCHUNK = (NGRP + NG - 1) / NG;
-    constexpr int OFF_S[7] = {0, 1, WS, WS - 1, -1, -WS, -WS + 1};
-    constexpr int OFF_I[7] = {0, 1, WI, WI - 1, -1, -WI, -WI + 1};
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int g = lane >> 4, l16 = lane & 15;
-    // this lane's weight fragments for every K step, loaded once per layer
-    bf16x8 av[KSTEPS][MB];
+// Four hidden activations of a cell (channels co..co+3) into its staged row; zeros unless keep.
+__device__ inline void put_act(__bf16 *row, int c, int co, const f32x4 &acc, const float *b,
+                               bool keep) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    uint2 w;
+    uint32_t *pw = &w.x;
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-        const int tap = ks * TPK + g / CH;
-        const int c0 = (g % CH) * 8;
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-            av[ks][m] = tap < 7 ? *reinterpret_cast<const bf16x8 *>(
-                                      wm + ((int64_t)(tap * COUT + m * 16 + l16)) * CIN + c0)
-                                : bf16x8{};
+    for (int j = 0; j < 4; j += 2) {
+        const float v0 = acc[j] + b[j], v1 = acc[j + 1] + b[j + 1];
+        const bf16x2 pk = {(__bf16)(v0 > 0.f ? v0 : 0.f), (__bf16)(v1 > 0.f ? v1 : 0.f)};
+        pw[j / 2] = keep ? __builtin_bit_cast(uint32_t, pk) : 0u;
     }
-    for (int chunk = w; chunk < NCHUNK; chunk += 4) {
-        f32x4 acc[MB][NG];
-        int sslot[NG], islot[NG], cell[NG];
-#pragma unroll
-        for (int n = 0; n < NG; ++n) {
-#pragma unroll
-            for (int m = 0; m < MB; ++m) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-            int c = (chunk * NG + n) * 16 + l16;
-            cell[n] = c;
-            c = c < NCELL ? c : NCELL - 1;  // lanes past the frame compute a copy, never stored
-            const int b = c / WO, a = c - b * WO;
-            sslot[n] = (b + 1) * WS + (a + 1);
-            islot[n] = (b + OI) * WI + (a + OI);
-        }
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int tap = ks * TPK + g / CH;
-            const int c0 = (g % CH) * 8;
-#pragma unroll
-            for (int n = 0; n < NG; ++n) {
-                if ((chunk * NG + n) >= NGRP) break;  // uniform over the wave
-                bf16x8 bv = bf16x8{};
-                if (tap < 7) {
-                    uint4 raw = src[(sslot[n] + OFF_S[tap]) * SSTR + c0 / 8];
-                    if (!taps_all && tap > 0 && !(fl[islot[n]] & fl[islot[n] + OFF_I[tap]]))
-                        raw = make_uint4(0u, 0u, 0u, 0u);
-                    bv = *reinterpret_cast<const bf16x8 *>(&raw);
-                }
-#pragma unroll
-                for (int m = 0; m < MB; ++m)
-                    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[ks][m], bv, acc[m][n], 0, 0, 0);
-            }
-        }
-        // epilogue: lane holds channels co = m*16 + 4g + j of cell[n]
-#pragma unroll
-        for (int n = 0; n < NG; ++n) {
-            const int c = cell[n];
-            if ((chunk * NG + n) >= NGRP || c >= NCELL) continue;
-            const int b = c / WO, a = c - b * WO;
-#pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                const int co = m * 16 + 4 * g;
-                float v[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = acc[m][n][j] + bias[co + j];
-                if constexpr (EPI == EPI_LIN) {
-                    const int q = q0 + a, r = r0 + b;
-                    if (q < nq && r < nr) {
-                        float *o = out + (soff + (int64_t)r * nq + q) * OUT_STRIDE;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (co + j < cout_real) o[co + j] = v[j];
-                    }
-                } else {
-                    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                    bf16x4 pk;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) pk[j] = (__bf16)(v[j] > 0.f ? v[j] : 0.f);
-                    *reinterpret_cast<bf16x4 *>(reinterpret_cast<__bf16 *>(dst) + c * DSTR + co) = pk;
-                }
-            }
-        }
-    }
+    *reinterpret_cast<uint2 *>(row + act_at(c + 1, co >> 3) + (co & 7)) = w;
 }
 
-__global__ __launch_bounds__(NT) void k_hexnet4(const __bf16 *__restrict__ x, Net4 nw,
-                                                float *__restrict__ out, int nq, int nr,
-                                                int ntiles_total, int cout_real,
-                                                const int32_t *live, ConvMask cm) {
-    using namespace f4;
-    constexpr int W0 = OT + 6, W1 = OT + 4;
-    constexpr int AS = 5;  // 16-byte chunks per cell of hidden activations (32 channels + pad)
-    __shared__ uint4 bufA[W0 * W0 * AS];  // layer 0 and layer 2 activations
-    __shared__ uint4 bufB[W1 * W1 * AS];  // the staged input (16 channels), then layer 1
-    __shared__ uint8_t fl[WI * WI];
-    static_assert(WI * WI * 2 <= W1 * W1 * AS, "staged input fits the layer-1 buffer");
-    const int ntq = (nq + OT - 1) / OT, ntr = (nr + OT - 1) / OT;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, 0);
-    if (tile < 0) return;
+// F32IN: x holds the FP32 features (FEATURES per cell), else the packed bf16 input.
+// w4: write the fourth float of each output too (zero).
+template <bool MASK, bool F32IN>
+__global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x, Net4 nw,
+                                                        float *__restrict__ out, int nq, int nr,
+                                                        int batch, int rh, int nseg, int w4,
+                                                        const int32_t *live, ConvMask cm) {
+    using namespace r4;
+    __shared__ __align__(16) __bf16 sin[IRING][LW * 16];
+    __shared__ __align__(16) __bf16 act[3][2][LW * 32];
+    __shared__ uint8_t fl[MASK ? FRING : 1][LW + 2];
     if (live && !*live) return;  // a surrogate window that does not run
-    const int per = ntq * ntr;
-    const int bs = tile / per, lt = tile - bs * per;
-    const int tr = lt / ntq;
-    const int q0 = (lt - tr * ntq) * OT, r0 = tr * OT;
-    const int64_t soff = (int64_t)bs * nq * nr;
-    // stage the 24 x 24 input frame: two 16-byte chunks per position, loads first
-    constexpr int NE = WI * WI * 2;
-    constexpr int ITERS = (NE + NT - 1) / NT;
-    uint4 v[ITERS];
-    uint8_t a[ITERS];
+    const int nstrip = (nq + OW - 1) / OW;
+    const int wgs = nstrip * nseg * batch;
+    const int id = xcd_tile(blockIdx.x, gridDim.x, wgs, 0);
+    if (id < 0) return;
+    const int b = id / (nstrip * nseg), rem = id - b * nstrip * nseg;
+    const int strip = rem / nseg, seg = rem - strip * nseg;
+    const int Q0 = strip * OW - 3;  // raster column of frame column 0
+    const int R0 = seg * rh, R1 = R0 + rh < nr ? R0 + rh : nr;
+    if (R0 >= nr) return;
+    const int64_t soff = (int64_t)b * nq * nr;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int g = lane >> 4, l16 = lane & 15;
+    // staged rows start as zeros: pad channels and columns are never written
+    for (int i = tid; i < IRING * LW * 16 / 8; i += NTH)
+        reinterpret_cast<uint4 *>(&sin[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = tid; i < 3 * 2 * LW * 32 / 8; i += NTH)
+        reinterpret_cast<uint4 *>(&act[0][0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+
+    // input rows: staged row v is raster row R0 - 4 + v, staged column c raster column Q0 - 1 + c;
+    // thread p of 256 owns the same elements of every row
+    constexpr int EL = F32IN ? (LW * FEATURES + 255) / 256 : 1;
+    const int p = tid & 255;
+    int eq[EL], eo[EL];  // raster column (-1: none) and offset in the staged row
+    int ec[EL];          // element of the source cell
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        const int e = threadIdx.x + it * NT;
-        const int p = e >> 1, ch = e & 1;
-        const int pb = p / WI, pa = p - pb * WI;
-        int q = q0 - 4 + pa, r = r0 - 4 + pb;
+    for (int i = 0; i < EL; ++i) {
+        const int e = p + 256 * i;
+        const int c = F32IN ? e / FEATURES : e / 2, ch = F32IN ? e - c * FEATURES : e - c * 2;
+        int q = Q0 - 1 + c;
         if (cm.perq) q = ((q % nq) + nq) % nq;
-        if (cm.perr) r = ((r % nr) + nr) % nr;
-        v[it] = make_uint4(0u, 0u, 0u, 0u);
-        a[it] = 0;
-        if (e < NE && q >= 0 && q < nq && r >= 0 && r < nr) {
-            const int64_t i = soff + (int64_t)r * nq + q;
-            v[it] = reinterpret_cast<const uint4 *>(x + i * FEATURES_PAD)[ch];
-            a[it] = cm.active ? (uint8_t)(cm.active[(int64_t)r * nq + q] != 0) : (uint8_t)1;
-        }
+        const bool ok = c < LW && q >= 0 && q < nq;
+        eq[i] = ok ? q : -1;
+        ec[i] = ch;
+        eo[i] = F32IN ? in_at(c, ch >> 3) + (ch & 7) : in_at(c, ch);
     }
+    const bool fthread = MASK && p < LW;  // stages the flag of column p
+    int fq = Q0 - 1 + p;
+    if (MASK && cm.perq) fq = ((fq % nq) + nq) % nq;
+    float vf[F32IN ? ICH : 1][EL];
+    uint4 vb[F32IN ? 1 : ICH];
+    uint8_t vfl[ICH];
+    auto load_rows = [&](int v0) {
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        const int e = threadIdx.x + it * NT;
-        if (e < NE) {
-            bufB[e] = v[it];
-            if ((e & 1) == 0) fl[e >> 1] = a[it];
+        for (int k = 0; k < ICH; ++k) {
+            int r = R0 - 4 + v0 + k;
+            if (cm.perr) r = ((r % nr) + nr) % nr;
+            const bool rok = r >= 0 && r < nr;
+            if constexpr (F32IN) {
+#pragma unroll
+                for (int i = 0; i < EL; ++i)
+                    vf[k][i] = rok && eq[i] >= 0
+                                   ? reinterpret_cast<const float *>(x)[(soff + (int64_t)r * nq + eq[i]) * FEATURES + ec[i]]
+                                   : 0.f;
+            } else {
+                vb[k] = rok && eq[0] >= 0
+                            ? reinterpret_cast<const uint4 *>(x)[(soff + (int64_t)r * nq + eq[0]) * 2 + ec[0]]
+                            : make_uint4(0u, 0u, 0u, 0u);
+            }
+            vfl[k] = MASK && fthread && rok && fq >= 0 && fq < nq
+                         ? (uint8_t)(cm.active[(int64_t)r * nq + fq] != 0)
+                         : (uint8_t)0;
         }
+    };
+    auto store_rows = [&](int v0) {
+#pragma unroll
+        for (int k = 0; k < ICH; ++k) {
+            __bf16 *row = sin[(v0 + k) % IRING];
+            if constexpr (F32IN) {
+#pragma unroll
+                for (int i = 0; i < EL; ++i)
+                    if (p + 256 * i < LW * FEATURES) row[eo[i]] = (__bf16)vf[k][i];
+            } else {
+                if (p < 2 * LW) *reinterpret_cast<uint4 *>(row + eo[0]) = vb[k];
+            }
+            if constexpr (MASK)
+                if (fthread) fl[(v0 + k) % FRING][p] = vfl[k];
+        }
+    };
+    // is frame column c a raster column? (rows are tested as they come)
+    auto inside_q = [&](int c) { return cm.perq || (Q0 + c >= 0 && Q0 + c < nq); };
+    auto inside_r = [&](int r) { return cm.perr || (r >= 0 && r < nr); };
+
+    // every wave: one MFMA column (frame columns 16 n .. 16 n + 15) of one layer
+    const int steps = (R1 - R0) + EXTRA;
+    constexpr int UN = MASK ? 1 : 3;  // steps per loop turn (see Taps)
+    const int n = wave & 3, c = n * 16 + l16;
+    const bool qok = inside_q(c);
+    if (wave >= 8) load_rows(wave >= 12 ? ICH : 0);  // the first rows, one latency for all
+    __syncthreads();
+    if (wave >= 12) {
+        // ---- layer 0, and the input
+        bf16x8 w[4][2];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const int tap = 2 * ks + g / 2;
+                w[ks][m] = tap < 7 ? *reinterpret_cast<const bf16x8 *>(
+                                         nw.wm[0] + (tap * 32 + m * 16 + l16) * 16 + (g % 2) * 8)
+                                   : bf16x8{};
+            }
+        float bb[2][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            bb[0][j] = nw.bias[0][4 * g + j];
+            bb[1][j] = nw.bias[0][16 + 4 * g + j];
+        }
+        store_rows(ICH);
+        // this lane's tap of K step ks is 2 ks or 2 ks + 1; its cell in a staged row
+        const bool second = g >= 2;
+        int slot[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            slot[ks] = in_at(c + 1 + (second ? DQ[ks < 3 ? 2 * ks + 1 : 6] : DQ[2 * ks]), g % 2);
+        // operands of step u, from staged input rows u, u + 1, u + 2
+        bf16x8 v[4];
+        auto operands = [&](int u) {
+            int ro[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ro[k] = (u + k) % IRING * (LW * 16);
+            bool in = true;
+            if constexpr (MASK) in = fl[(u + 1) % FRING][c + 1] != 0;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const int ta = 2 * ks, tb = ks < 3 ? 2 * ks + 1 : 6;
+                v[ks] = *reinterpret_cast<const bf16x8 *>(
+                    &sin[0][0] + (second ? ro[1 + DR[tb]] : ro[1 + DR[ta]]) + slot[ks]);
+                if constexpr (MASK) {
+                    const int dr = second ? DR[tb] : DR[ta], dq = second ? DQ[tb] : DQ[ta];
+                    const bool cut =
+                        (ks > 0 || second) && !(in && fl[(u + 1 + dr) % FRING][c + 1 + dq]);
+                    if (cut) v[ks] = bf16x8{};
+                }
+            }
+        };
+        __syncthreads();
+        operands(0);
+        for (int u = 0; u < steps; ++u) {
+            if (u % ICH == 0) load_rows(u + 2 * ICH);
+            // raster row R0 - 3 + u (the eighth tap does not exist: its weights are zero)
+            f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16x8 x8 = ks == 3 && second ? bf16x8{} : v[ks];
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][m], x8, acc[m], 0, 0, 0);
+            }
+            operands(u + 1);  // staged two rows ahead at least
+            const bool ok = MASK || (qok && inside_r(R0 - 3 + u));
+#pragma unroll
+            for (int m = 0; m < 2; ++m) put_act(act[0][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
+            if (u % ICH == ICH - 1) store_rows(u - (ICH - 1) + 2 * ICH);
+            __syncthreads();
+        }
+    } else if (wave >= 8) {
+        // ---- layer 3
+        bf16x8 w[7];
+#pragma unroll
+        for (int t = 0; t < 7; ++t)
+            w[t] = *reinterpret_cast<const bf16x8 *>(nw.wm[3] + (t * 16 + l16) * 32 + g * 8);
+        float bb[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bb[j] = nw.bias[3][4 * g + j];
+        store_rows(0);
+        Taps tp{};
+        const bool qout = g == 0 && c >= 3 && c < 3 + OW && Q0 + c < nq;
+        float *o = out + (soff + (int64_t)(R0 - 9) * nq + Q0 + c) * OUT_STRIDE;
+        const int64_t pitch = (int64_t)nq * OUT_STRIDE;
+        __syncthreads();
+        for (int u0 = 0; u0 < steps; u0 += UN)
+#pragma unroll
+            for (int j = 0; j < UN; ++j) {
+                const int u = u0 + j;
+                if (u >= steps) break;
+                if (MASK) taps_move(tp);
+                // raster row R0 - 9 + u; layer 2's row above it is the newest
+                taps_push<MASK>(tp, j, act[2][(u + 1) & 1], c, g,
+                                fl[MASK ? (u + FRING - 4) % FRING : 0]);
+                __builtin_amdgcn_sched_barrier(0);  // the reads first: they wait longest
+                f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int t = 0; t < 7; ++t)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t], tap_of<MASK>(tp, j, t), acc, 0, 0, 0);
+                if (qout && u >= 9) {
+                    if (w4) {
+                        *reinterpret_cast<float4 *>(o) =
+                            make_float4(acc[0] + bb[0], acc[1] + bb[1], acc[2] + bb[2], 0.f);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) o[k] = acc[k] + bb[k];
+                    }
+                }
+                o += pitch;
+                __syncthreads();
+            }
+    } else {
+        // ---- layer 1 (waves 0 to 3) or 2
+        const int l = 1 + (wave >> 2);
+        bf16x8 w[7][2];
+#pragma unroll
+        for (int t = 0; t < 7; ++t)
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                w[t][m] = *reinterpret_cast<const bf16x8 *>(nw.wm[l] + (t * 32 + m * 16 + l16) * 32 + g * 8);
+        float bb[2][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            bb[0][j] = nw.bias[l][4 * g + j];
+            bb[1][j] = nw.bias[l][16 + 4 * g + j];
+        }
+        Taps tp{};
+        __syncthreads();
+        for (int u0 = 0; u0 < steps; u0 += UN)
+#pragma unroll
+            for (int j = 0; j < UN; ++j) {
+                const int u = u0 + j;
+                if (u >= steps) break;
+                if (MASK) taps_move(tp);
+                // raster row R0 - 3 + u - 2 l; the row above it, of layer l - 1, is the newest
+                taps_push<MASK>(tp, j, act[l - 1][(u + 1) & 1], c, g,
+                                fl[MASK ? (u + FRING + 2 - 2 * l) % FRING : 0]);
+                __builtin_amdgcn_sched_barrier(0);
+                f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                for (int t = 0; t < 7; ++t) {
+                    const bf16x8 v = tap_of<MASK>(tp, j, t);
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][m], v, acc[m], 0, 0, 0);
+                }
+                const bool ok = MASK || (qok && inside_r(R0 - 3 + u - 2 * l));
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    put_act(act[l][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
+                __syncthreads();
+            }
     }
-    __syncthreads();
-    // the staged frame lies inside an unmasked raster: no tap is cut
-    const bool all = !cm.active && q0 >= 4 && q0 + OT + 4 <= nq && r0 >= 4 && r0 + OT + 4 <= nr;
-    net_layer<16, 32, EPI_RELU, OT + 6, 2, 8 * AS>(bufB, bufA, fl, nw.wm[0], nw.bias[0], nullptr,
-                                                   nq, nr, soff, q0, r0, 32, all);
-    __syncthreads();
-    net_layer<32, 32, EPI_RELU, OT + 4, AS, 8 * AS>(bufA, bufB, fl, nw.wm[1], nw.bias[1], nullptr,
-                                                    nq, nr, soff, q0, r0, 32, all);
-    __syncthreads();
-    net_layer<32, 32, EPI_RELU, OT + 2, AS, 8 * AS>(bufB, bufA, fl, nw.wm[2], nw.bias[2], nullptr,
-                                                    nq, nr, soff, q0, r0, 32, all);
-    __syncthreads();
-    net_layer<32, 16, EPI_LIN, OT, AS, 0>(bufA, nullptr, fl, nw.wm[3], nw.bias[3], out, nq, nr,
-                                          soff, q0, r0, cout_real, all);
 }
 
 // ------------------------------------------------------------ weight grad
@@ -620,15 +783,56 @@ hipError_t launch_conv(int cinp, int coutp, int epi, const __bf16 *x, const __bf
     return hipErrorInvalidValue;
 }
 
-int net4_tiles(int nq, int nr, int batch) {
-    return ((nq + f4::OT - 1) / f4::OT) * ((nr + f4::OT - 1) / f4::OT) * batch;
+// Segments of the rows: the split that costs the fewest rounds of steps, with one
+// workgroup per CU at a time and a strip's start (weights, first input rows) as six steps.
+static int net4_segments(int nq, int nr, int batch) {
+    const int64_t strips = (int64_t)((nq + r4::OW - 1) / r4::OW) * batch;
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    const int64_t least = (strips + 255) / 256;
+    for (int64_t rounds = least; rounds < least + 12; ++rounds) {
+        const int64_t most = rounds * 256 / strips;  // segments that these rounds hold
+        const int s = (int)(most < nr ? most : nr);
+        const int rh = (nr + s - 1) / s;
+        const int64_t c = rounds * (rh + r4::EXTRA + 6);
+        if (c < cost) {
+            cost = c;
+            best = (nr + rh - 1) / rh;
+        }
+    }
+    return best;
 }
 
-hipError_t launch_net4(const __bf16 *x, const Net4 &nw, float *out, int nq, int nr, int batch,
-                       int cout_real, const ConvMask &cm, hipStream_t st, const int32_t *live) {
-    const int nt = net4_tiles(nq, nr, batch);
-    hipLaunchKernelGGL(k_hexnet4, dim3(nt), dim3(NT), 0, st, x, nw, out, nq, nr, nt, cout_real,
-                       live, cm);
+hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bool w4, int nq,
+                       int nr, int batch, const ConvMask &cm, hipStream_t st,
+                       const int32_t *live) {
+    // a launch holds fewer than 2^32 threads: many small samples go in several
+    const int64_t strips = (nq + r4::OW - 1) / r4::OW;
+    const int64_t most = (int64_t(1) << 21) / strips;
+    if (most < 1) return hipErrorInvalidValue;
+    if (batch > most) {
+        const int64_t cells = (int64_t)nq * nr, step = cells * (f32in ? FEATURES * 4 : 32);
+        for (int64_t b = 0; b < batch; b += most) {
+            const int n = (int)(batch - b < most ? batch - b : most);
+            const hipError_t err = launch_net4((const char *)x + b * step, f32in, nw,
+                                               out + b * cells * OUT_STRIDE, w4, nq, nr, n, cm, st, live);
+            if (err != hipSuccess) return err;
+        }
+        return hipSuccess;
+    }
+    const int nseg = net4_segments(nq, nr, batch), rh = (nr + nseg - 1) / nseg;
+    const int64_t wgs = strips * nseg * batch;
+#define HEXSV_NET4(M, F)                                                                        \
+    hipLaunchKernelGGL((k_hexnet4<M, F>), dim3((unsigned)wgs), dim3(r4::NTH), 0, st, x, nw, out, \
+                       nq, nr, batch, rh, nseg, w4 ? 1 : 0, live, cm)
+    if (cm.active) {
+        if (f32in) HEXSV_NET4(true, true);
+        else HEXSV_NET4(true, false);
+    } else {
+        if (f32in) HEXSV_NET4(false, true);
+        else HEXSV_NET4(false, false);
+    }
+#undef HEXSV_NET4
     return hipGetLastError();
 }
 

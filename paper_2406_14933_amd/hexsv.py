@@ -554,8 +554,8 @@ class Surrogate:
         return n // (nq * nr)
 
     def set_fused(self, on=True):
-        """Forward of the 4-layer, 32-channel network as one fused kernel or one launch per
-        layer (the default); the outputs are the same bit for bit."""
+        """Forward of the 4-layer, 32-channel network as one fused kernel (how a surrogate
+        starts out) or one launch per layer; the outputs are the same bit for bit."""
         _check(lib().hexsv_surrogate_set_fused(self._h, 1 if on else 0))
 
     # grid (optional): the raster whose neighbour rule the taps follow (periodic sides, the
