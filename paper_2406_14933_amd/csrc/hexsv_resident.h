@@ -29,9 +29,10 @@
 // Bound by the chain of a step: rim words out, a poll that sees them (about 1.5 us across
 // XCDs), edges, wave speeds out and polled again, cells, two barriers; for 1024 x 1024 by the
 // arithmetic of four tiles per CU.  Per step of a whole run, setup and books included, single
-// launches -> resident: 64 x 64 FP64 8.2 -> 5.2 us, 1159 x 72 viscous 10.6 -> 6.9, 512 x 512
-// FP32 10.5 -> 6.2, 1024 x 1024 FP32 16.1 -> 12.9 and FP64 28.5 -> 27.4; 45 flumes in FP64, a
-// group of workgroups each, 24.9 -> 12.5.
+// launches -> resident: 64 x 64 FP64 8.2 -> 4.4 us, 1159 x 72 viscous 10.6 -> 6.0, 512 x 512
+// FP32 10.5 -> 5.7, 1024 x 1024 FP32 16.1 -> 12.8 and FP64 28.5 -> 25.8; 45 flumes in FP64, a
+// group of workgroups each, 24.9 -> 12.7.  Of that, edge codes kept in registers and the early
+// first read of the wave speeds gave 15 % on 64 x 64 and 7 % on 512 x 512 cells.
 #pragma once
 
 #include "hexsv_ensemble.h"
@@ -152,7 +153,11 @@ __device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const K
     __shared__ TileLDS<T, TQ, TR, VISC> L;
     __shared__ T wmax[NW], fmax[NW];
     __shared__ double red[3][4 * SUB], book[3];
-    __shared__ int sbad;
+    __shared__ int sbad, nghost;
+    // Workgroups of up to 8 KB a field have the registers to keep their cells' edge codes
+    // (edges_fixed); those of larger ones would spill.
+    constexpr bool FIXED = TQ * TR * sizeof(T) <= 8192;
+    __shared__ T ghosts[FIXED ? 3 * TQ * TR : 1];  // beds of outflow ghosts
     const int nwg = grp.count, ntq = grp.ntq;      // of the group
     const int wg = grp.wg, me_wg = grp.first + wg;  // in the group, in the launch
     const int tr = wg / ntq, tq = wg - tr * ntq;
@@ -164,7 +169,7 @@ __device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const K
     // this workgroup answers the roll call
     const size_t fstride = (size_t)W * rs.flag_cap;
     if (tid < W) send(rs.flags + (tag0 & 1) * fstride + tid * rs.flag_cap + me_wg, tag0, 0u);
-    if (tid == 0) sbad = 0;
+    if (tid == 0) sbad = nghost = 0;
     __syncthreads();
     tile_stage<T, TQ, TR, NT, EXT>(L, R, g, kc, tq, tr);
     // sub-tiles that see an inactive cell take the general path, as a tile of their own would
@@ -254,15 +259,33 @@ __device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const K
             if constexpr (VISC) L.c[s] = cell_wave(h, v1, v2, G);
         }
     };
-    // the largest of all workgroups' wave speeds of `tag` (infinite: give up); a barrier
+    // the largest of all workgroups' wave speeds of `tag` (infinite: give up); a barrier.  The
+    // first read of a word is issued early by ask_speeds, ahead of the edges: a read takes most
+    // of a microsecond whether or not it finds the word.
+    const int flag0 = NT - 1 - tid;  // from the other end than ring cells
+    unsigned long long asked[W];
+    auto ask_speeds = [&](uint32_t tag) {
+        if (flag0 < nwg) {
+            const unsigned long long *p = rs.flags + (tag & 1) * fstride + grp.first + flag0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) asked[w] = recv(p + w * rs.flag_cap);
+        }
+    };
     auto wait_speeds = [&](uint32_t tag, int limit) -> T {
         T c = T(0);
         polls = 0;
-        for (int f = NT - 1 - tid; f < nwg; f += NT) {  // from the other end than ring cells
+        for (int f = flag0; f < nwg; f += NT) {
             const unsigned long long *p = rs.flags + (tag & 1) * fstride + grp.first + f;
             uint32_t b[W];
-            bool got = false;
-            do {
+            bool got = f == flag0;  // asked for
+            if (got) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    got = got && (uint32_t)(asked[w] >> 32) == tag;
+                    b[w] = (uint32_t)asked[w];
+                }
+            }
+            while (!got && ok && again(limit)) {
                 got = true;
 #pragma unroll
                 for (int w = 0; w < W; ++w) {
@@ -270,7 +293,7 @@ __device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const K
                     got = got && (uint32_t)(v >> 32) == tag;
                     b[w] = (uint32_t)v;
                 }
-            } while (!got && ok && again(limit));
+            }
             const T u = value_of<T>(b);
             c = u > c ? u : c;
         }
@@ -290,15 +313,30 @@ __device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const K
     cells.G = uniform(cells.G);
     cells.l = uniform(cells.l);
     cells.half_l = uniform(cells.half_l);
+    // General sub-tiles: the rows (a wave's k-th cells) whose cells are all updated and have
+    // six neighbours in the domain take the short path all the same.
     bool general[PER];
+    int rows = 0;
+    uint32_t ec[FIXED ? CPT : 1];
     EdgeSums<T> es[CPT];
     auto edges = [&](int me) {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             if (general[p]) {
 #pragma unroll
-                for (int k = p * CPS; k < (p + 1) * CPS; ++k)
-                    if ((act >> k) & 1) es[k] = cells.template edges<true>(me, k);
+                for (int k = p * CPS; k < (p + 1) * CPS; ++k) {
+                    if constexpr (FIXED) {
+                        if ((rows >> k) & 1) {
+                            uint32_t codes = ec[k];  // opaque: its tests are not worth carrying
+                            asm volatile("" : "+v"(codes));
+                            es[k] = cells.edges_fixed(me, k, codes, ghosts);
+                        } else {
+                            es[k] = cells.template edges<false, sizeof(T) == 4>(me, k);
+                        }
+                    } else {
+                        if ((act >> k) & 1) es[k] = cells.template edges<true>(me, k);
+                    }
+                }
             } else {
 #pragma unroll
                 for (int k = p * CPS; k < (p + 1) * CPS; ++k)
@@ -314,7 +352,23 @@ __device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const K
         general[p] =
             uniform((int)(!tile_inner(g, q0, r0 + sub * TRS, TQ, TRS) || ((sbad >> sub) & 1))) != 0;
     }
+    if constexpr (FIXED) {
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            ec[k] = 0;
+            bool special = false;
+            if (general[k / CPS]) {
+                const bool mine = (act >> k) & 1;
+                if (mine) ec[k] = cells.edge_codes(tid, k, ghosts, &nghost);
+                special = !mine || ec[k] != 0;
+            }
+            if (__any(special)) rows |= 1 << k;
+        }
+        rows = uniform(rows);
+        __syncthreads();  // the ghosts' beds are there
+    }
     edges(tid);
+    ask_speeds(tag0);
     if (!__builtin_isfinite(wait_speeds(tag0, RES_ROLL_POLLS))) return;
 
     // time and CFL bound, the same in every workgroup; the rain book and the time steps'
@@ -404,6 +458,7 @@ __device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const K
         }
         wait_ring(tag);
         __syncthreads();  // the new state's records are staged
+        ask_speeds(tag);
         edges(me);
         const T cm = wait_speeds(tag, RES_STEP_POLLS);
         if (!__builtin_isfinite(cm)) return;

@@ -343,8 +343,9 @@ struct TileCells {
         : L(L_), R(R_), d(d_), g(g_), kc(kc_), q0(tq * TQ), r0(tr * TR), G((T)kc_.g),
           l((T)kc_.a), half_l((T)(0.5 * kc_.a)) {}
 
-    // GEN: edges may be walls, open, or lead to boundary cells (codes are staged)
-    template <bool GEN>
+    // GEN: edges may be walls, open, or lead to boundary cells (codes are staged).  LIKE_GEN:
+    // FP32 rounds as the general path does (see edge_vn), for interior cells beside those.
+    template <bool GEN, bool LIKE_GEN = false>
     __device__ inline EdgeSums<T> edges(int tid, int k) const {
         const T S3H = (T)0.86602540378443864676;
         const T NX[6] = {T(1), T(0.5), T(-0.5), T(-1), T(-0.5), T(0.5)};
@@ -431,33 +432,37 @@ struct TileCells {
             }
             if constexpr (F32) {
                 // mj holds l*theta_j*h_j
-                const T vn = (e == 0) ? vb1 : ((e == 3) ? -vb1 : vb1 * NX[e] + vb2 * NY[e]);
+                T vn;
+                if constexpr (LIKE_GEN) vn = edge_vn(e, vb1, vb2);
+                else vn = (e == 0) ? vb1 : ((e == 3) ? -vb1 : vb1 * NX[e] + vb2 * NY[e]);
                 const T dw = wj - wi;
                 // one selected mass serves both terms: the upwind mass of the flux
                 // (at vn = 0 the flux vanishes whatever it is) and the pressure mass,
                 // which at vn = 0 follows the free-surface tie rule
                 const T key = (vn != T(0)) ? vn : -dw;  // w_i > w_j decides at vn = 0
                 const T msel = key > T(0) ? Mi : mj;
-                const T F = msel * vn;
-                Ls -= F;
+                T F = msel * vn;
+                if constexpr (LIKE_GEN) edge_mass(Ls, F, msel, vn);
+                else Ls -= F;
                 A1 -= F * vb1;
                 A2 -= F * vb2;
                 const T Q = dw * msel;
                 A1 -= Q * NXh[e];
                 if (e != 0 && e != 3) A2 -= Q * NYh[e];
                 if (GEN && (EXT ? cd != CODE_INTERIOR : cd == CODE_OUTFLOW))
-                    Fout += F;  // outflow or Dirichlet edge
+                    Fout = __builtin_fmaf(msel, vn, Fout);  // outflow or Dirichlet edge
             } else {
-                const T vn = vb1 * NX[e] + vb2 * NY[e];
-                const T mup = vn > T(0) ? mi : (vn < T(0) ? mj : T(0));
-                const T mhat = vn != T(0) ? mup : (wi > wj ? mi : mj);
-                const T F = l * mup * vn;
+                const T vn = (e == 0) ? vb1 : ((e == 3) ? -vb1 : vb1 * NX[e] + vb2 * NY[e]);
+                // one selected mass, as above: at vn = 0 the flux vanishes whatever it is
+                const bool own = vn > T(0) || (vn == T(0) && wi > wj);
+                const T msel = own ? mi : mj;
+                const T F = l * msel * vn;
                 Ls -= F;
                 A1 -= F * vb1;
                 A2 -= F * vb2;
-                const T P = half_l * (wj - wi) * mhat;
+                const T P = half_l * (wj - wi) * msel;
                 S1 -= P * NX[e];
-                S2 -= P * NY[e];
+                if (e != 0 && e != 3) S2 -= P * NY[e];
                 if (GEN && (EXT ? cd != CODE_INTERIOR : cd == CODE_OUTFLOW))
                     Fout += F;  // outflow or Dirichlet edge
             }
@@ -481,6 +486,161 @@ struct TileCells {
             A2 = A2 + V2;
         }
         if constexpr (!F32) {  // FP32 sums the pressure part with J
+            A1 = A1 + S1;
+            A2 = A2 + S2;
+        }
+        return EdgeSums<T>{Ls, A1, A2, Fout, vh1i, vh2i};
+    }
+
+    // A cell's edge codes as a word, three bits each, for kernels that keep it over many
+    // steps; the beds of its outflow ghosts go to consecutive entries of a table in LDS (at
+    // most three per cell), the first one's number to the word's upper bits.
+    static constexpr uint32_t CODE_FLAT = 6;  // outflow without extrapolation
+    __device__ inline uint32_t edge_codes(int tid, int k, T *ghosts, int *count) const {
+        constexpr int OFF[6] = {1, W, W - 1, -1, -W, -W + 1};
+        int lq, lr;
+        Regs::cell(tid, k, lq, lr);
+        const int s = (lr + 1) * W + (lq + 1);
+        const int q = q0 + lq, r = r0 + lr;
+        uint32_t ec = 0;
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            const uint32_t cd = L.code[s + OFF[e]], op = L.code[s - OFF[e]];
+            const bool bed = cd == CODE_OUTFLOW && op == CODE_INTERIOR;
+            n += bed ? 1 : 0;
+            ec |= (cd == CODE_OUTFLOW && !bed ? CODE_FLAT : cd) << (3 * e);
+        }
+        if (n > 0) {
+            uint32_t at = (uint32_t)atomicAdd(count, n);
+            ec |= at << 18;
+#pragma unroll 1
+            for (int e = 0; e < 6; ++e)
+                if (((ec >> (3 * e)) & 7) == CODE_OUTFLOW) {
+                    int qo = q - dq_of(e), ro = r - dr_of(e);
+                    wrap_pos(g, qo, ro);
+                    const T zi = ld(d.z, (uint32_t)(r * g.pitch + q));
+                    ghosts[at++] = T(2) * zi - d.z[(int64_t)ro * g.pitch + qo];
+                }
+        }
+        return ec;
+    }
+
+    // The normal velocity of edge e and the flux's part in the mass sum, with FP32's fused
+    // multiply-adds where the compiler places them in edges<true>.
+    __device__ static inline T edge_vn(int e, T vb1, T vb2) {
+        const T S3H = (T)0.86602540378443864676;
+        const T NX[6] = {T(1), T(0.5), T(-0.5), T(-1), T(-0.5), T(0.5)};
+        const T NY[6] = {T(0), S3H, S3H, T(0), -S3H, -S3H};
+        if (e == 0) return vb1;
+        if (e == 3) return -vb1;
+        if constexpr (F32)
+            return e == 5 ? __builtin_fmaf(vb1, NX[e], vb2 * NY[e])
+                          : __builtin_fmaf(vb2, NY[e], vb1 * NX[e]);
+        else return vb1 * NX[e] + vb2 * NY[e];
+    }
+    __device__ static inline void edge_mass(T &Ls, T &F, T m, T vn) {
+        if constexpr (EXT) {  // F = m vn, rounded
+            asm("" : "+v"(F));
+            Ls -= F;
+        } else {
+            Ls = __builtin_fmaf(-m, vn, Ls);
+        }
+    }
+
+    // edges<true> with the codes of edge_codes: the same sums bit for bit.  Every kind of edge
+    // is a choice of values here, not of paths: the staged codes' way costs a chain of LDS
+    // reads per edge (the code, then the record) and two reads of memory per open edge, which
+    // the many-step kernels would wait for in every step.
+    __device__ inline EdgeSums<T> edges_fixed(int tid, int k, uint32_t ec, const T *ghosts) const {
+        const T S3H = (T)0.86602540378443864676;
+        const T NX[6] = {T(1), T(0.5), T(-0.5), T(-1), T(-0.5), T(0.5)};
+        const T NY[6] = {T(0), S3H, S3H, T(0), -S3H, -S3H};
+        const T NXh[6] = {T(0.5), T(0.25), T(-0.25), T(-0.5), T(-0.25), T(0.25)};
+        const T NYh[6] = {T(0), T(0.5) * S3H, T(0.5) * S3H, T(0), -T(0.5) * S3H, -T(0.5) * S3H};
+        constexpr int OFF[6] = {1, W, W - 1, -1, -W, -W + 1};
+        int lq, lr;
+        Regs::cell(tid, k, lq, lr);
+        const int s = (lr + 1) * W + (lq + 1);
+        const T hi = R.h[k];
+        const T mi = R.th[k] * hi;
+        const typename Rec<T>::type me = L.rec[s];
+        const T Mi = me.x, wi = me.y, vh1i = me.z, vh2i = me.w;
+        typename Rec<T>::type nbs[6];
+#pragma unroll
+        for (int e = 0; e < 6; ++e) nbs[e] = L.rec[s + OFF[e]];
+        uint32_t ghost = ec >> 18;
+        T Ls = T(0), A1 = T(0), A2 = T(0), S1 = T(0), S2 = T(0), Fout = T(0);
+        T V1 = T(0), V2 = T(0);
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            const uint32_t cd = (ec >> (3 * e)) & 7;
+            const bool in = cd == CODE_INTERIOR, wall = cd == CODE_WALL, bed = cd == CODE_OUTFLOW;
+            const bool held = EXT && (cd == CODE_DIRICHLET || cd == CODE_FLUX);
+            const bool flux = EXT && cd == CODE_FLUX;
+            const bool cell = in || held;
+            const T mj = cell ? nbs[e].x : Mi;
+            const T vh1j = cell ? nbs[e].z : vh1i, vh2j = cell ? nbs[e].w : vh2i;
+            T wj = cell ? nbs[e].y : wi;
+            if (__any(bed)) {
+                const T wg = G * (ghosts[bed ? ghost : 0] + hi);
+                wj = bed ? wg : wj;
+                ghost += bed ? 1 : 0;
+            }
+            const T vb1 = (held ? vh1j : vh1i) + vh1j;
+            const T vb2 = (held ? vh2j : vh2i) + vh2j;
+            T vn = edge_vn(e, vb1, vb2);
+            T dw = wj - wi;
+            if constexpr (EXT) {
+                T wf;
+                if constexpr (F32) wf = __builtin_fmaf(G, wj + hi, -wi);
+                else wf = G * (wj + hi) - wi;
+                dw = flux ? wf : dw;
+            }
+            vn = wall ? T(0) : vn;  // no flux and no pressure difference
+            dw = wall ? T(0) : dw;
+            if constexpr (F32) {
+                const T key = (vn != T(0)) ? vn : -dw;
+                const T msel = key > T(0) ? Mi : mj;
+                const T mf = flux ? mj : msel, mp = flux ? Mi : msel;
+                T F = mf * vn;
+                edge_mass(Ls, F, mf, vn);
+                A1 = __builtin_fmaf(-F, vb1, A1);
+                A2 = __builtin_fmaf(-F, vb2, A2);
+                const T Q = dw * mp;
+                A1 = __builtin_fmaf(-Q, NXh[e], A1);
+                if (e != 0 && e != 3) A2 = __builtin_fmaf(-Q, NYh[e], A2);
+                const T Fo = __builtin_fmaf(mf, vn, Fout);
+                Fout = in || wall ? Fout : Fo;
+            } else {
+                const bool own = vn > T(0) || (vn == T(0) && wi > wj);
+                const T msel = own ? mi : mj;
+                const T mf = flux ? mj : msel, mp = flux ? mi : msel;
+                const T F = l * mf * vn;
+                Ls -= F;
+                A1 -= F * vb1;
+                A2 -= F * vb2;
+                const T P = half_l * dw * mp;
+                S1 -= P * NX[e];
+                if (e != 0 && e != 3) S2 -= P * NY[e];
+                Fout = in || wall ? Fout : Fout + F;
+            }
+            if constexpr (V) {
+                const T ci = L.c[s], cj = L.c[s + OFF[e]];
+                const T cij = ci > cj ? ci : cj;
+                const T ms = Mi + mj;
+                T mu = ms > T(0) ? p_div(T(2) * Mi * mj, ms) : T(0);
+                mu = in ? mu : T(0);
+                const T lc = F32 ? cij : l * cij;
+                V1 += lc * mu * (T(2) * (vh1j - vh1i));
+                V2 += lc * mu * (T(2) * (vh2j - vh2i));
+            }
+        }
+        if constexpr (V) {
+            A1 = A1 + V1;
+            A2 = A2 + V2;
+        }
+        if constexpr (!F32) {
             A1 = A1 + S1;
             A2 = A2 + S2;
         }
