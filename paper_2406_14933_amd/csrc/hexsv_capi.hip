@@ -549,19 +549,6 @@ extern "C" int hexsv_sim_set_state(hexsv_sim *s, double t0, const double *d_h, c
     }
     const int64_t n = s->grid->n;
     const uint8_t *act = s->grid->d_active;
-    for (int p = 0; p < 2; ++p) {
-        if (s->prec == HEXSV_FP64) {
-            KDom<double> d = dom_of<double>(s);
-            HIP_TRY(launch_import<double>(d_h, d.st[p][0], act, 1, n, stream));
-            HIP_TRY(launch_import<double>(d_v1, d.st[p][1], act, 1, n, stream));
-            HIP_TRY(launch_import<double>(d_v2, d.st[p][2], act, 1, n, stream));
-        } else {
-            KDom<float> d = dom_of<float>(s);
-            HIP_TRY(launch_import<float>(d_h, d.st[p][0], act, 1, n, stream));
-            HIP_TRY(launch_import<float>(d_v1, d.st[p][1], act, 1, n, stream));
-            HIP_TRY(launch_import<float>(d_v2, d.st[p][2], act, 1, n, stream));
-        }
-    }
     Ctl &c = *s->h_ctl;
     memset(&c, 0, sizeof c);
     c.t = t0;
@@ -573,7 +560,11 @@ extern "C" int hexsv_sim_set_state(hexsv_sim *s, double t0, const double *d_h, c
     c.err_cell = -1;
     HIP_TRY(hipMemcpyAsync(s->d_ctl, s->h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, stream));
     HIP_TRY(hipMemsetAsync(s->d_acc, 0, ACC_BYTES, stream));
-    HIP_TRY(s->prec == HEXSV_FP64 ? prime<double>(s, 1, stream) : prime<float>(s, 1, stream));
+    HIP_TRY(s->prec == HEXSV_FP64
+                ? launch_set_state<double>(dom_of<double>(s), d_h, d_v1, d_v2, act, n, s->kc, s->d_ctl,
+                                           s->d_part, PRIME_BLOCKS, stream)
+                : launch_set_state<float>(dom_of<float>(s), d_h, d_v1, d_v2, act, n, s->kc, s->d_ctl,
+                                          s->d_part, PRIME_BLOCKS, stream));
     HIP_TRY(hipMemcpyAsync(s->h_ctl, s->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
     s->state_set = true;

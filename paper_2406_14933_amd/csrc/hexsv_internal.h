@@ -159,6 +159,11 @@ constexpr int PRIME_BLOCKS = 1024;
 template <typename T>
 hipError_t launch_prime(const KDom<T> &d, int64_t n, const KConst &kc, Ctl *ctl, Part *part,
                         int nblocks, int reset_books, hipStream_t stream);
+// The caller's FP64 state into both buffers (zero outside the domain), primed (with the books).
+template <typename T>
+hipError_t launch_set_state(const KDom<T> &d, const double *h, const double *v1, const double *v2,
+                            const uint8_t *active, int64_t n, const KConst &kc, Ctl *ctl,
+                            Part *part, int nblocks, hipStream_t stream);
 
 // FP64 caller arrays -> internal precision (theta forced to 0 outside the mask).
 // nq, pitch: the internal rows are `pitch` cells apart (0: the caller's layout).

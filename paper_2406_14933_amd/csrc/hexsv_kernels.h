@@ -145,6 +145,47 @@ hipError_t launch_prime(const KDom<T> &d, int64_t n, const KConst &kc, Ctl *ctl,
     return launch_prime_finalize(ctl, part, nblocks, kc, reset_books, stream);
 }
 
+// A new state into both buffers, with k_prime's reductions on the way (the same cells per
+// thread and roundings): 48 bytes a cell in FP32, where six imports and a priming pass moved
+// 84, and one launch for seven, which is what small rasters notice.  4096 x 4096 cells: 354 us
+// in seven launches before.
+template <typename T>
+__global__ __launch_bounds__(256) void k_set_state(KDom<T> d, const double *__restrict__ h,
+                                                   const double *__restrict__ v1,
+                                                   const double *__restrict__ v2,
+                                                   const uint8_t *__restrict__ active, int64_t n,
+                                                   KConst kc, Part *part) {
+    double c = 0.0, s = 0.0;
+    const T G = (T)kc.g;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const bool in = !active || active[i] != 0;
+        const T hh = in ? (T)h[i] : T(0), a = in ? (T)v1[i] : T(0), b = in ? (T)v2[i] : T(0);
+        for (int p = 0; p < 2; ++p) {
+            d.st[p][0][i] = hh;
+            d.st[p][1][i] = a;
+            d.st[p][2][i] = b;
+        }
+        const T th = d.th[i];
+        if (!(th > T(0))) continue;
+        const T cc = cell_wave(hh, a, b, G);
+        c = (double)cc > c ? (double)cc : c;
+        s += kc.sigma * ((double)th * (double)hh);
+    }
+    const Part p = block_reduce<256>(c, s, 0.0, 0.0);
+    if (threadIdx.x == 0) part[blockIdx.x] = p;
+}
+
+template <typename T>
+hipError_t launch_set_state(const KDom<T> &d, const double *h, const double *v1, const double *v2,
+                            const uint8_t *active, int64_t n, const KConst &kc, Ctl *ctl,
+                            Part *part, int nblocks, hipStream_t stream) {
+    hipLaunchKernelGGL((k_set_state<T>), dim3(nblocks), dim3(256), 0, stream, d, h, v1, v2, active,
+                       n, kc, part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_prime_finalize(ctl, part, nblocks, kc, 1, stream);
+}
+
 // Cell i of a row-major raster of nq columns sits at element (i / nq) pitch + i % nq
 // of an array whose rows are `pitch` apart (pitch == nq: the same index).
 __device__ inline int64_t pitched(int64_t i, int64_t nq, int64_t pitch) {
@@ -684,6 +725,9 @@ hipError_t launch_win_scale(const KDom<T> &d, int64_t n, const Ctl *ctl, const S
                                        int, int, int, hipStream_t);                           \
     template hipError_t launch_prime<T>(const KDom<T> &, int64_t, const KConst &, Ctl *, Part *, \
                                         int, int, hipStream_t);                               \
+    template hipError_t launch_set_state<T>(const KDom<T> &, const double *, const double *, \
+                                            const double *, const uint8_t *, int64_t,         \
+                                            const KConst &, Ctl *, Part *, int, hipStream_t); \
     template hipError_t launch_win_probe<T>(const KDom<T> &, const KGrid &, const KConst &,   \
                                             const KRain &, const Ctl *, SurWin *, T *, double, \
                                             const float2 *, FeatScale, int, void *, Part *,   \
