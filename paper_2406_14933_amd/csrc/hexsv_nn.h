@@ -39,15 +39,20 @@ hipError_t launch_conv(int cinp, int coutp, int epi, const __bf16 *x, const __bf
 // The 4-layer network with 32 hidden channels in one launch (k_hexnet4): weights
 // and biases of each layer as for launch_conv (layer 0: 16 -> 32, layers 1-2:
 // 32 -> 32, layer 3: 32 -> 16 with 3 outputs written, FP32, OUT_STRIDE per cell;
-// w4: and a zero); x: the FP32 features (f32in) or the packed bf16 input.  The
-// output equals the layer-by-layer launch_conv chain bit for bit.
+// w4: and a zero); x: the FP32 features (f32in) or the packed bf16 input; keep
+// (with f32in): also what the gradient reads.  All equal the layer-by-layer
+// launch_conv chain's bit for bit.
 struct Net4 {
     const __bf16 *wm[4];
     const float *bias[4];
 };
+// What the gradient reads of a forward: the packed input and the hidden activations.
+struct Net4Keep {
+    __bf16 *x0, *act[3];
+};
 hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bool w4, int nq,
                        int nr, int batch, const ConvMask &cm, hipStream_t st,
-                       const int32_t *live = nullptr);
+                       const int32_t *live = nullptr, const Net4Keep *keep = nullptr);
 // Weight-gradient partials: one record (7*coutp*cinp + coutp floats) per workgroup of
 // the launch, which sweeps the tiles with its sums in registers.  WGRAD_WGS workgroups
 // are two per CU, all resident: more would only add records to reduce.

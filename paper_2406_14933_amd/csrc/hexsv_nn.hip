@@ -172,8 +172,8 @@ __device__ inline bf16x8 tap_of(const Taps &t, int j, int tap) {
 }
 
 // Four hidden activations of a cell (channels co..co+3) into its staged row; zeros unless keep.
-__device__ inline void put_act(__bf16 *row, int c, int co, const f32x4 &acc, const float *b,
-                               bool keep) {
+__device__ inline uint2 put_act(__bf16 *row, int c, int co, const f32x4 &acc, const float *b,
+                                bool keep) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     uint2 w;
     uint32_t *pw = &w.x;
@@ -184,15 +184,18 @@ __device__ inline void put_act(__bf16 *row, int c, int co, const f32x4 &acc, con
         pw[j / 2] = keep ? __builtin_bit_cast(uint32_t, pk) : 0u;
     }
     *reinterpret_cast<uint2 *>(row + act_at(c + 1, co >> 3) + (co & 7)) = w;
+    return w;
 }
 
 // F32IN: x holds the FP32 features (FEATURES per cell), else the packed bf16 input.
-// w4: write the fourth float of each output too (zero).
-template <bool MASK, bool F32IN>
+// w4: write the fourth float of each output too (zero).  KEEP: the packed input and the hidden
+// activations go to memory too, as the chain leaves them for the gradient.
+template <bool MASK, bool F32IN, bool KEEP>
 __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x, Net4 nw,
                                                         float *__restrict__ out, int nq, int nr,
                                                         int batch, int rh, int nseg, int w4,
-                                                        const int32_t *live, ConvMask cm) {
+                                                        const int32_t *live, ConvMask cm,
+                                                        Net4Keep keep) {
     using namespace r4;
     __shared__ __align__(16) __bf16 sin[IRING][LW * 16];
     __shared__ __align__(16) __bf16 act[3][2][LW * 32];
@@ -285,6 +288,10 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
     constexpr int UN = MASK ? 1 : 3;  // steps per loop turn (see Taps)
     const int n = wave & 3, c = n * 16 + l16;
     const bool qok = inside_q(c);
+    // this workgroup's output columns; its output rows are R0 to R1 - 1 (KEEP: of every layer)
+    const bool own_q = c >= 3 && c < 3 + OW && Q0 + c < nq;
+    const auto own_r = [&](int r) { return r >= R0 && r < R1; };
+    const auto cell_at = [&](int r) { return soff + (int64_t)r * nq + Q0 + c; };
     if (wave >= 8) load_rows(wave >= 12 ? ICH : 0);  // the first rows, one latency for all
     __syncthreads();
     if (wave >= 12) {
@@ -339,6 +346,10 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
             if (u % ICH == 0) load_rows(u + 2 * ICH);
             // raster row R0 - 3 + u (the eighth tap does not exist: its weights are zero)
             f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+            const int r = R0 - 3 + u;
+            const bool mine = KEEP && own_q && own_r(r);
+            if (mine && !second)  // the cell itself: tap 0 of the first K step
+                *reinterpret_cast<bf16x8 *>(keep.x0 + cell_at(r) * FEATURES_PAD + g * 8) = v[0];
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 const bf16x8 x8 = ks == 3 && second ? bf16x8{} : v[ks];
@@ -347,9 +358,13 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
                     acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][m], x8, acc[m], 0, 0, 0);
             }
             operands(u + 1);  // staged two rows ahead at least
-            const bool ok = MASK || (qok && inside_r(R0 - 3 + u));
+            const bool ok = MASK || (qok && inside_r(r));
 #pragma unroll
-            for (int m = 0; m < 2; ++m) put_act(act[0][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
+            for (int m = 0; m < 2; ++m) {
+                const uint2 a = put_act(act[0][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
+                if (mine)
+                    *reinterpret_cast<uint2 *>(keep.act[0] + cell_at(r) * 32 + m * 16 + 4 * g) = a;
+            }
             if (u % ICH == ICH - 1) store_rows(u - (ICH - 1) + 2 * ICH);
             __syncthreads();
         }
@@ -364,7 +379,7 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
         for (int j = 0; j < 4; ++j) bb[j] = nw.bias[3][4 * g + j];
         store_rows(0);
         Taps tp{};
-        const bool qout = g == 0 && c >= 3 && c < 3 + OW && Q0 + c < nq;
+        const bool qout = g == 0 && own_q;
         float *o = out + (soff + (int64_t)(R0 - 9) * nq + Q0 + c) * OUT_STRIDE;
         const int64_t pitch = (int64_t)nq * OUT_STRIDE;
         __syncthreads();
@@ -397,6 +412,7 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
     } else {
         // ---- layer 1 (waves 0 to 3) or 2
         const int l = 1 + (wave >> 2);
+        __bf16 *const kept = KEEP ? (l == 1 ? keep.act[1] : keep.act[2]) : nullptr;
         bf16x8 w[7][2];
 #pragma unroll
         for (int t = 0; t < 7; ++t)
@@ -429,10 +445,14 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
                     for (int m = 0; m < 2; ++m)
                         acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][m], v, acc[m], 0, 0, 0);
                 }
-                const bool ok = MASK || (qok && inside_r(R0 - 3 + u - 2 * l));
+                const int r = R0 - 3 + u - 2 * l;
+                const bool ok = MASK || (qok && inside_r(r));
 #pragma unroll
-                for (int m = 0; m < 2; ++m)
-                    put_act(act[l][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
+                for (int m = 0; m < 2; ++m) {
+                    const uint2 a = put_act(act[l][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
+                    if (KEEP && own_q && own_r(r))
+                        *reinterpret_cast<uint2 *>(kept + cell_at(r) * 32 + m * 16 + 4 * g) = a;
+                }
                 __syncthreads();
             }
     }
@@ -737,7 +757,7 @@ __global__ __launch_bounds__(256) void k_l1_loss(const float *__restrict__ pred,
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// FP32 features (6 per cell) -> bf16 activations (8 channels, 2 zero).
+// FP32 features -> the packed bf16 input (FEATURES_PAD channels, the last ones zero).
 __global__ void k_pack_features(const float *__restrict__ f, int64_t ncell,
                                 __bf16 *__restrict__ x) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncell;
@@ -805,7 +825,7 @@ static int net4_segments(int nq, int nr, int batch) {
 
 hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bool w4, int nq,
                        int nr, int batch, const ConvMask &cm, hipStream_t st,
-                       const int32_t *live) {
+                       const int32_t *live, const Net4Keep *keep) {
     // a launch holds fewer than 2^32 threads: many small samples go in several
     const int64_t strips = (nq + r4::OW - 1) / r4::OW;
     const int64_t most = (int64_t(1) << 21) / strips;
@@ -814,23 +834,33 @@ hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bo
         const int64_t cells = (int64_t)nq * nr, step = cells * (f32in ? FEATURES * 4 : 32);
         for (int64_t b = 0; b < batch; b += most) {
             const int n = (int)(batch - b < most ? batch - b : most);
+            Net4Keep k = keep ? *keep : Net4Keep{};
+            if (keep) {
+                k.x0 += b * cells * FEATURES_PAD;
+                for (int l = 0; l < 3; ++l) k.act[l] += b * cells * 32;
+            }
             const hipError_t err = launch_net4((const char *)x + b * step, f32in, nw,
-                                               out + b * cells * OUT_STRIDE, w4, nq, nr, n, cm, st, live);
+                                               out + b * cells * OUT_STRIDE, w4, nq, nr, n, cm, st,
+                                               live, keep ? &k : nullptr);
             if (err != hipSuccess) return err;
         }
         return hipSuccess;
     }
     const int nseg = net4_segments(nq, nr, batch), rh = (nr + nseg - 1) / nseg;
     const int64_t wgs = strips * nseg * batch;
-#define HEXSV_NET4(M, F)                                                                        \
-    hipLaunchKernelGGL((k_hexnet4<M, F>), dim3((unsigned)wgs), dim3(r4::NTH), 0, st, x, nw, out, \
-                       nq, nr, batch, rh, nseg, w4 ? 1 : 0, live, cm)
+    if (keep && !f32in) return hipErrorInvalidValue;
+#define HEXSV_NET4(M, F, K)                                                                    \
+    hipLaunchKernelGGL((k_hexnet4<M, F, K>), dim3((unsigned)wgs), dim3(r4::NTH), 0, st, x, nw,  \
+                       out, nq, nr, batch, rh, nseg, w4 ? 1 : 0, live, cm,                      \
+                       keep ? *keep : Net4Keep{})
     if (cm.active) {
-        if (f32in) HEXSV_NET4(true, true);
-        else HEXSV_NET4(true, false);
+        if (keep) HEXSV_NET4(true, true, true);
+        else if (f32in) HEXSV_NET4(true, true, false);
+        else HEXSV_NET4(true, false, false);
     } else {
-        if (f32in) HEXSV_NET4(false, true);
-        else HEXSV_NET4(false, false);
+        if (keep) HEXSV_NET4(false, true, true);
+        else if (f32in) HEXSV_NET4(false, true, false);
+        else HEXSV_NET4(false, false, false);
     }
 #undef HEXSV_NET4
     return hipGetLastError();

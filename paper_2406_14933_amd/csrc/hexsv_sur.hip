@@ -356,9 +356,15 @@ static int gradient(hexsv_surrogate *s, const hexsv_grid *grid, int batch, int n
     int64_t cells;
     rc = check_shape(s, batch, nq, nr, &cells);
     if (rc) return rc;
-    HIP_TRY(nn::launch_pack_features(feat, cells, s->x0, st));
-    rc = forward_packed(s, nq, nr, batch, cm, st, nullptr, true);
-    if (rc) return rc;
+    if (runs_fused(s, nq)) {
+        const nn::Net4Keep keep{s->x0, {s->act[0], s->act[1], s->act[2]}};
+        HIP_TRY(nn::launch_net4(feat, true, net4_of(s), s->out, false, nq, nr, batch, cm, st, nullptr,
+                                &keep));
+    } else {
+        HIP_TRY(nn::launch_pack_features(feat, cells, s->x0, st));
+        rc = forward_packed(s, nq, nr, batch, cm, st, nullptr, true);
+        if (rc) return rc;
+    }
     const double inv_count = 1.0 / (3.0 * (double)cells);
     HIP_TRY(nn::launch_l1_loss(s->out, target, cells, inv_count, s->dy_last, s->lpart, LOSS_PARTS, st));
     const int nrec = nn::wgrad_records(nq, nr, batch);

@@ -39,3 +39,26 @@ def test_fused_forward_equals_the_layer_chain(hx, nq, nr, batch, kind):
         sur.forward_noalloc(f, nq, nr, out, grid=grid)
         assert torch.equal(out[:, :3], chain[:, :3])
         assert bool((out[:, 3] == 7.0).all())
+
+
+@pytest.mark.parametrize("nq,nr,batch", [(1, 1, 1), (59, 9, 3), (117, 130, 2)])
+@pytest.mark.parametrize("kind", ["plain", "masked"])
+def test_gradient_from_the_fused_forward(hx, nq, nr, batch, kind):
+    """The fused forward leaves the gradient the chain's activations: equal bit for bit."""
+    rng = np.random.default_rng(nq + nr)
+    p = (so.init_params(6, 4, 32, out_scale=1.0)
+         + rng.normal(scale=0.05, size=so.num_params(4, 32))).astype(np.float32)
+    grid = None
+    if kind == "masked":
+        active = (rng.random((nr, nq)) < 0.8).astype(np.uint8)
+        active[0, 0] = 1
+        grid = hx.Grid(nq, nr, 1.0, side=(hx.WALL,) * 4, active=active)
+    n = batch * nq * nr
+    f = torch.from_numpy(rng.normal(size=(n, so.FEATURES)).astype(np.float32)).cuda()
+    t = torch.from_numpy(rng.normal(size=(n, 3)).astype(np.float32)).cuda()
+    sur = hx.Surrogate(4, 32)
+    sur.set_params(p)
+    loss, g = sur.gradient(f, t, nq, nr, grid)
+    sur.set_fused(False)
+    loss0, g0 = sur.gradient(f, t, nq, nr, grid)
+    assert torch.equal(g, g0) and loss == loss0
