@@ -854,13 +854,10 @@ extern "C" int hexsv_sim_get_state(const hexsv_sim *sc, double *d_h, double *d_v
     hexsv_sim *s = const_cast<hexsv_sim *>(sc);
     if (!s) return fail(HEXSV_EINVAL, "get_state: null sim");
     if (!s->state_set) return fail(HEXSV_ESTATE, "get_state: no state set");
-    HIP_TRY(hipMemcpyAsync(s->h_ctl, s->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    const int par = s->h_ctl->parity;
     if (s->prec == HEXSV_FP64)
-        HIP_TRY(launch_export<double>(dom_of<double>(s), par, s->grid->n, d_h, d_v1, d_v2, d_q1, d_q2, stream));
+        HIP_TRY(launch_export<double>(dom_of<double>(s), s->d_ctl, s->grid->n, d_h, d_v1, d_v2, d_q1, d_q2, stream));
     else
-        HIP_TRY(launch_export<float>(dom_of<float>(s), par, s->grid->n, d_h, d_v1, d_v2, d_q1, d_q2, stream));
+        HIP_TRY(launch_export<float>(dom_of<float>(s), s->d_ctl, s->grid->n, d_h, d_v1, d_v2, d_q1, d_q2, stream));
     return HEXSV_OK;
 }
 

@@ -636,16 +636,13 @@ extern "C" int hexsv_ensemble_get_state(const hexsv_ensemble *ec, int32_t s, dou
     hexsv_ensemble *e = const_cast<hexsv_ensemble *>(ec);
     if (!e || s < 0 || s >= e->n) return fail(HEXSV_EINVAL, "ensemble_get_state: bad argument");
     if (!e->ready[s]) return fail(HEXSV_ESTATE, "ensemble_get_state: scenario %d has no state", s);
-    HIP_TRY(hipMemcpyAsync(e->h_ctl + s, e->d_ctl + s, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    const int par = e->h_ctl[s].parity;
     const int64_t n = e->grids[s]->n;
     const int nq = e->grids[s]->kg.nq, pitch = e->scen[s].g.pitch;
     if (e->prec == HEXSV_FP64)
-        HIP_TRY(launch_export<double>(ens_dom<double>(e, s), par, n, d_h, d_v1, d_v2, d_q1, d_q2, stream,
+        HIP_TRY(launch_export<double>(ens_dom<double>(e, s), e->d_ctl + s, n, d_h, d_v1, d_v2, d_q1, d_q2, stream,
                                       nq, pitch));
     else
-        HIP_TRY(launch_export<float>(ens_dom<float>(e, s), par, n, d_h, d_v1, d_v2, d_q1, d_q2, stream,
+        HIP_TRY(launch_export<float>(ens_dom<float>(e, s), e->d_ctl + s, n, d_h, d_v1, d_v2, d_q1, d_q2, stream,
                                      nq, pitch));
     return HEXSV_OK;
 }

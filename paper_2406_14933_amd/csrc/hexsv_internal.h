@@ -172,7 +172,7 @@ hipError_t launch_import(const double *src, T *dst, const uint8_t *active, int z
                          int64_t n, hipStream_t stream, int64_t nq = 0, int64_t pitch = 0);
 // internal state -> FP64 caller arrays (each output nullable); nq, pitch as above.
 template <typename T>
-hipError_t launch_export(const KDom<T> &d, int par, int64_t n, double *h, double *v1,
+hipError_t launch_export(const KDom<T> &d, const Ctl *ctl, int64_t n, double *h, double *v1,
                          double *v2, double *q1, double *q2, hipStream_t stream,
                          int64_t nq = 0, int64_t pitch = 0);
 

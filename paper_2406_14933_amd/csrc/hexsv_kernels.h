@@ -218,9 +218,12 @@ hipError_t launch_import(const double *src, T *dst, const uint8_t *active, int z
     return hipGetLastError();
 }
 
+// The buffer that holds the state is read from the control block, which spares the caller a
+// round trip to the host before the launch.
 template <typename T>
-__global__ void k_export(KDom<T> d, int par, int64_t n, double *h, double *v1, double *v2,
+__global__ void k_export(KDom<T> d, const Ctl *ctl, int64_t n, double *h, double *v1, double *v2,
                          double *q1, double *q2, int64_t nq, int64_t pitch) {
+    const int par = ctl->parity;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t j = pitched(i, nq, pitch);
@@ -239,12 +242,12 @@ __global__ void k_export(KDom<T> d, int par, int64_t n, double *h, double *v1, d
 }
 
 template <typename T>
-hipError_t launch_export(const KDom<T> &d, int par, int64_t n, double *h, double *v1,
+hipError_t launch_export(const KDom<T> &d, const Ctl *ctl, int64_t n, double *h, double *v1,
                          double *v2, double *q1, double *q2, hipStream_t stream, int64_t nq,
                          int64_t pitch) {
     const int nb = (int)((n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536);
     if (nq <= 0 || pitch < nq) nq = pitch = 1;
-    hipLaunchKernelGGL((k_export<T>), dim3(nb > 0 ? nb : 1), dim3(256), 0, stream, d, par, n,
+    hipLaunchKernelGGL((k_export<T>), dim3(nb > 0 ? nb : 1), dim3(256), 0, stream, d, ctl, n,
                        h, v1, v2, q1, q2, nq, pitch);
     return hipGetLastError();
 }
@@ -747,7 +750,7 @@ hipError_t launch_win_scale(const KDom<T> &d, int64_t n, const Ctl *ctl, const S
                                             const SurWin *, hipStream_t);                     \
     template hipError_t launch_import<T>(const double *, T *, const uint8_t *, int, int64_t,  \
                                          hipStream_t, int64_t, int64_t);                      \
-    template hipError_t launch_export<T>(const KDom<T> &, int, int64_t, double *, double *,   \
+    template hipError_t launch_export<T>(const KDom<T> &, const Ctl *, int64_t, double *, double *,   \
                                          double *, double *, double *, hipStream_t, int64_t,  \
                                          int64_t);
 
