@@ -29,9 +29,9 @@
 // Bound by the chain of a step: rim words out, a poll that sees them (about 1.5 us across
 // XCDs), edges, wave speeds out and polled again, cells, two barriers; for 1024 x 1024 by the
 // arithmetic of four tiles per CU.  Per step of a whole run, setup and books included, single
-// launches -> resident: 64 x 64 FP64 8.2 -> 4.4 us, 1159 x 72 viscous 10.6 -> 6.0, 512 x 512
-// FP32 10.5 -> 5.7, 1024 x 1024 FP32 16.1 -> 12.8 and FP64 28.5 -> 25.8; 45 flumes in FP64, a
-// group of workgroups each, 24.9 -> 12.7.  Of that, edge codes kept in registers and the early
+// launches -> resident: 64 x 64 FP64 8.3 -> 4.2 us, 1159 x 72 viscous 10.6 -> 5.4, 512 x 512
+// FP32 10.7 -> 5.6, 1024 x 1024 FP32 16.2 -> 12.3 and FP64 28.1 -> 25.5; 45 flumes in FP64, a
+// group of workgroups each, 25.1 -> 11.7.  Of that, edge codes kept in registers and the early
 // first read of the wave speeds gave 15 % on 64 x 64 and 7 % on 512 x 512 cells.
 #pragma once
 
