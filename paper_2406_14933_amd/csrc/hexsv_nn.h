@@ -7,7 +7,7 @@
 namespace hexsv {
 namespace nn {
 
-enum { EPI_RELU = 0, EPI_LIN = 1, EPI_MASK = 2 };
+enum { EPI_RELU = 0, EPI_LIN = 1 };
 constexpr int OUT_STRIDE = 4;  // floats per cell of the network output (3 used)
 constexpr int FEATURES = 11;     // network input channels
 constexpr int FEATURES_PAD = 16; // stored input channels per cell (bf16, zero padded)
@@ -29,13 +29,11 @@ int conv_tiles(int nq, int nr, int batch);
 
 // Hex convolution of channels-last bf16 x (cinp channels) with the MFMA
 // weight layout wm[t][coutp][cinp]; epilogue per EPI_* (see hexsv_nn.hip).
-// Built for (cinp, coutp, epi) in {(16,32,RELU), (32,32,RELU), (32,16,LIN),
-// (16,32,MASK), (32,32,MASK)}.
+// Built for (cinp, coutp, epi) in {(16,32,RELU), (32,32,RELU), (32,16,LIN)}.
 // live (nullable, device): the launch does nothing unless *live != 0.
 hipError_t launch_conv(int cinp, int coutp, int epi, const __bf16 *x, const __bf16 *wm,
-                       const float *bias, void *out, const __bf16 *mask, int nq, int nr,
-                       int batch, int cout_real, const ConvMask &cm, hipStream_t st,
-                       const int32_t *live = nullptr);
+                       const float *bias, void *out, int nq, int nr, int batch, int cout_real,
+                       const ConvMask &cm, hipStream_t st, const int32_t *live = nullptr);
 // The 4-layer network with 32 hidden channels in one launch (k_hexnet4): weights
 // and biases of each layer as for launch_conv (layer 0: 16 -> 32, layers 1-2:
 // 32 -> 32, layer 3: 32 -> 16 with 3 outputs written, FP32, OUT_STRIDE per cell;
@@ -55,23 +53,27 @@ hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bo
                        const int32_t *live = nullptr, const Net4Keep *keep = nullptr);
 // Weight-gradient partials: one record (7*coutp*cinp + coutp floats) per workgroup of
 // the launch, which sweeps the tiles with its sums in registers.  WGRAD_WGS workgroups
-// are two per CU, all resident: more would only add records to reduce.
+// are two per CU, all resident: more would only add records to reduce (half as many with the
+// data gradient, whose workgroups fill a CU).  Layers with 32
+// input channels (not the first): the data gradient dx through x's ReLU as well, with the
+// transposed stencil's weights wt[t][cinp][coutp].
 constexpr int WGRAD_WGS = 512;
-int wgrad_records(int nq, int nr, int batch);
+int wgrad_records(int nq, int nr, int batch, bool dx);
 hipError_t launch_wgrad(int cinp, int coutp, const __bf16 *x, const __bf16 *dy, float *part,
-                        int nq, int nr, int batch, const ConvMask &cm, hipStream_t st);
-// All layers' records (nrec of each) into the flat gradient; block0 is set by the launcher.
+                        const __bf16 *wt, __bf16 *dx, int nq, int nr, int batch,
+                        const ConvMask &cm, hipStream_t st);
+// All layers' records into the flat gradient; block0 is set by the launcher.
 constexpr int MAX_LAYERS = 16;
 struct WgradLayer {
     const float *part;
     int64_t off;  // of the layer's W in the flat parameters
-    int cinp, coutp, cin, cout, block0;
+    int cinp, coutp, cin, cout, nrec, block0;
 };
 struct WgradTable {
     int layers;
     WgradLayer y[MAX_LAYERS];
 };
-hipError_t launch_wgrad_reduce(WgradTable tab, int nrec, float *grad, hipStream_t st);
+hipError_t launch_wgrad_reduce(WgradTable tab, float *grad, hipStream_t st);
 hipError_t launch_prepare_weights(const float *p, int cin, int cout, int cinp, int coutp,
                                   __bf16 *wm, __bf16 *wt, float *bias, hipStream_t st);
 hipError_t launch_adam(float *p, float *m, float *v, const float *g, int64_t n, float lr,

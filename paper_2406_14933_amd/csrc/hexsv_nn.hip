@@ -1,7 +1,7 @@
 // hexsv_nn.hip — kernels of the learned hex-convolution surrogate: BF16 MFMA
-// forward / data-gradient / weight-gradient hex convolutions with FP32
-// accumulation (the tile's staging and MFMA mapping are in hexsv_conv.h), the
-// fused 4-layer forward, the L1 loss, Adam, and the weight-layout preparation.
+// forward and gradient hex convolutions with FP32 accumulation (the tile's
+// staging and MFMA mapping are in hexsv_conv.h), the one-launch 4-layer forward,
+// the L1 loss, Adam, and the weight-layout preparation.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -17,13 +17,11 @@ namespace nn {
 // out[i][co] for the tile; EPI selects the epilogue:
 //   EPI_RELU:  bf16 out = max(acc + b, 0)           (hidden layers, forward)
 //   EPI_LIN:   f32 out[i][co < cout_real] = acc + b  (last layer, forward)
-//   EPI_MASK:  bf16 out = acc * (mask[i][co] > 0)    (data gradient through ReLU)
 template <int CIN, int COUT, int EPI>
 __global__ __launch_bounds__(NT) void k_hexconv(const __bf16 *__restrict__ x,
                                                 const __bf16 *__restrict__ wm,
-                                                const float *__restrict__ bias, void *out,
-                                                const __bf16 *__restrict__ mask, int nq, int nr,
-                                                int ntiles_total, int cout_real,
+                                                const float *__restrict__ bias, void *out, int nq,
+                                                int nr, int ntiles_total, int cout_real,
                                                 const int32_t *live, ConvMask cm) {
     constexpr int CH = CIN / 8;
     constexpr int MB = COUT / 16;                 // output-channel blocks
@@ -58,26 +56,15 @@ __global__ __launch_bounds__(NT) void k_hexconv(const __bf16 *__restrict__ x,
             const int co = m * 16 + 4 * g;
             float v[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = acc[m][n][j];
-            if constexpr (EPI == EPI_RELU || EPI == EPI_LIN) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] += bias[co + j];
-            }
+            for (int j = 0; j < 4; ++j) v[j] = acc[m][n][j] + bias[co + j];
             if constexpr (EPI == EPI_LIN) {
                 float *o = reinterpret_cast<float *>(out) + i * OUT_STRIDE;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     if (co + j < cout_real) o[co + j] = v[j];
             } else {
-                if constexpr (EPI == EPI_RELU) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] = v[j] > 0.f ? v[j] : 0.f;
-                }
-                if constexpr (EPI == EPI_MASK) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (!((float)mask[i * COUT + co + j] > 0.f)) v[j] = 0.f;
-                }
+                for (int j = 0; j < 4; ++j) v[j] = v[j] > 0.f ? v[j] : 0.f;
                 __bf16 *o = reinterpret_cast<__bf16 *>(out) + i * COUT + co;
                 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
                 bf16x4 pk;
@@ -488,16 +475,30 @@ __device__ inline bf16x8 read_cells8(const __bf16 *p, int cell_stride) {
 // transposing reads (8 two-byte gathers per operand before); rows are padded by 16
 // bytes per cell against bank conflicts.  The next tile's loads are in flight during
 // the arithmetic.  2 x 512 x 512 samples, 32 -> 32 channels: 27 us against 48 us.
-template <int CIN, int COUT>
-__global__ __launch_bounds__(NT, 2) void k_hexconv_wgrad(const __bf16 *__restrict__ x,
+//
+// DX (every layer but the first): the data gradient too, dx = (W^T stencil of dy) where
+// x > 0, from the same staged tiles: dy is staged with its halo, x's own cells are the ReLU's
+// mask.  Four more waves do it, one row each, with conv_acc's MFMAs in its order, so a SIMD
+// holds one wave of each gradient and one workgroup fills a CU (half the records).  As a
+// launch of its own it read dy and x again: 39 us against 50 for 32 -> 32 channels, 33
+// against 39 for the last layer, and the reduction 9.5 against 14.7.  One set of four waves
+// that did both spilled 184 registers (128 us).
+template <bool DX>
+constexpr int WG_NT = DX ? 512 : 256;
+template <int CIN, int COUT, bool DX>
+__global__ __launch_bounds__(WG_NT<DX>, 2) void k_hexconv_wgrad(const __bf16 *__restrict__ x,
                                                          const __bf16 *__restrict__ dy,
-                                                         float *__restrict__ part, int nq, int nr,
+                                                         float *__restrict__ part,
+                                                         const __bf16 *__restrict__ wt,
+                                                         __bf16 *__restrict__ dx, int nq, int nr,
                                                          int ntiles_total, ConvMask cm) {
+    constexpr int NTH = WG_NT<DX>;
     constexpr int CH = CIN / 8, DCH = COUT / 8;
     constexpr int MB = COUT / 16, NB = CIN / 16;
     constexpr int PSZ = 7 * COUT * CIN + COUT;
     constexpr int XS = CIN + 8, DS = COUT + 8;  // padded bf16 per staged cell
-    constexpr int XB = NSLOT * XS * 2, DB = TQ * TR * DS * 2;
+    constexpr int DN = DX ? NSLOT : TQ * TR;    // staged cells of dy
+    constexpr int XB = NSLOT * XS * 2, DB = DN * DS * 2;
     constexpr int BYTES = XB + DB > PSZ * 4 ? XB + DB : PSZ * 4;
     __shared__ __align__(16) unsigned char smem[BYTES];
     __shared__ uint8_t fl[NSLOT];
@@ -506,10 +507,11 @@ __global__ __launch_bounds__(NT, 2) void k_hexconv_wgrad(const __bf16 *__restric
     float *red = reinterpret_cast<float *>(smem);  // the waves' sums, after the last tile
     const int ntq = (nq + TQ - 1) / TQ, ntr = (nr + TR - 1) / TR;
     const bool masked = cm.active != nullptr;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, l16 = lane & 15;
+    const int w = wave & 3;  // row of the tile
 
-    constexpr int XIT = (NSLOT * CH + NT - 1) / NT, DIT = (TQ * TR * DCH + NT - 1) / NT;
+    constexpr int XIT = (NSLOT * CH + NTH - 1) / NTH, DIT = (DN * DCH + NTH - 1) / NTH;
     uint4 xv[XIT], dv[DIT];
     uint8_t av[XIT];
     auto load = [&](int tile) {
@@ -518,7 +520,7 @@ __global__ __launch_bounds__(NT, 2) void k_hexconv_wgrad(const __bf16 *__restric
         const int64_t soff = (int64_t)b * nq * nr;
 #pragma unroll
         for (int it = 0; it < XIT; ++it) {
-            const int e = threadIdx.x + it * NT;
+            const int e = threadIdx.x + it * NTH;
             const int s = e / CH, ch = e - s * CH;
             const int lr = s / SW, lq = s - lr * SW;
             int q = q0 + lq - 1, r = r0 + lr - 1;
@@ -533,35 +535,28 @@ __global__ __launch_bounds__(NT, 2) void k_hexconv_wgrad(const __bf16 *__restric
         }
 #pragma unroll
         for (int it = 0; it < DIT; ++it) {  // dy of the tile's cells, zero outside the raster
-            const int e = threadIdx.x + it * NT;
+            const int e = threadIdx.x + it * NTH;
             const int c = e / DCH, ch = e - c * DCH;
-            const int q = q0 + c % TQ, r = r0 + c / TQ;
+            int q, r;
+            if constexpr (DX) {
+                q = q0 + c % SW - 1;
+                r = r0 + c / SW - 1;
+                if (cm.perq) q = q < 0 ? q + nq : (q >= nq ? q - nq : q);
+                if (cm.perr) r = r < 0 ? r + nr : (r >= nr ? r - nr : r);
+            } else {
+                q = q0 + c % TQ;
+                r = r0 + c / TQ;
+            }
             dv[it] = make_uint4(0u, 0u, 0u, 0u);
-            if (e < TQ * TR * DCH && q < nq && r < nr)
+            if (e < DN * DCH && q >= 0 && q < nq && r >= 0 && r < nr)
                 dv[it] = reinterpret_cast<const uint4 *>(dy + (soff + (int64_t)r * nq + q) * COUT)[ch];
         }
     };
 
-    f32x4 acc[7][MB][NB], accb[MB];
-#pragma unroll
-    for (int m = 0; m < MB; ++m) {
-        accb[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < 7; ++t)
-#pragma unroll
-            for (int n = 0; n < NB; ++n) acc[t][m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    bf16x8 ones;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.f;
-
-    int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, 0);
-    if (tile >= 0) load(tile);
-    for (int k = 0; tile >= 0; ++k) {
-        __syncthreads();  // the previous tile's operands have been read
+    auto stage = [&]() {
 #pragma unroll
         for (int it = 0; it < XIT; ++it) {
-            const int e = threadIdx.x + it * NT;
+            const int e = threadIdx.x + it * NTH;
             if (e < NSLOT * CH) {
                 const int s = e / CH, ch = e - s * CH;
                 *reinterpret_cast<uint4 *>(sx + s * XS + ch * 8) = xv[it];
@@ -570,85 +565,178 @@ __global__ __launch_bounds__(NT, 2) void k_hexconv_wgrad(const __bf16 *__restric
         }
 #pragma unroll
         for (int it = 0; it < DIT; ++it) {
-            const int e = threadIdx.x + it * NT;
-            if (e < TQ * TR * DCH) {
+            const int e = threadIdx.x + it * NTH;
+            if (e < DN * DCH) {
                 const int c = e / DCH, ch = e - c * DCH;
                 *reinterpret_cast<uint4 *>(sdy + c * DS + ch * 8) = dv[it];
             }
         }
-        tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, k + 1);
+    };
+    // the tiles in turn, the next one's loads in flight: wait until the last one's operands
+    // have been read, stage, then do(tile's place)
+    auto sweep = [&](auto &&work) {
+        int tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, 0);
         if (tile >= 0) load(tile);
-        __syncthreads();
+        for (int k = 0; tile >= 0; ++k) {
+            __syncthreads();
+            stage();
+            int b, q0, r0;
+            tile_of(tile, ntq, ntr, b, q0, r0);
+            tile = xcd_tile(blockIdx.x, gridDim.x, ntiles_total, k + 1);
+            if (tile >= 0) load(tile);
+            __syncthreads();
+            work(b, q0, r0);
+        }
+    };
+
+    if (DX && wave >= 4) {
+        // ---- data gradient, as conv_acc does it, over dy with the transposed stencil
+        sweep([&](int b, int q0, int r0) {
+            constexpr int TPK = 32 / COUT, KSTEPS = (7 + TPK - 1) / TPK;
+            const int64_t soff = (int64_t)b * nq * nr;
+            f32x4 da[NB][4];
 #pragma unroll
-        for (int ks = 0; ks < TQ / 32; ++ks) {
-            const int c0 = ks * 32 + 8 * g;                 // first of this lane's 8 cells
-            const int sc = (w + 1) * SW + (c0 + 1);         // its staged slot
-            const int row = l16 >> 2, col = (l16 & 3) * 4;  // what this lane addresses
-            bf16x8 a[MB];
+            for (int m = 0; m < NB; ++m)
 #pragma unroll
-            for (int m = 0; m < MB; ++m)
-                a[m] = read_cells8(sdy + (w * TQ + c0 + row) * DS + m * 16 + col, DS);
+                for (int n = 0; n < 4; ++n) da[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int m = 0; m < MB; ++m)
-                accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], ones, accb[m], 0, 0, 0);
+            for (int ks = 0; ks < KSTEPS; ++ks) {
+                const int tap = ks * TPK + g / DCH, c0 = (g % DCH) * 8;
+                bf16x8 a[NB];
 #pragma unroll
-            for (int t = 0; t < 7; ++t) {
+                for (int m = 0; m < NB; ++m)
+                    a[m] = tap < 7 ? *reinterpret_cast<const bf16x8 *>(
+                                         wt + (tap * CIN + m * 16 + l16) * COUT + c0)
+                                   : bf16x8{};
 #pragma unroll
-                for (int n = 0; n < NB; ++n) {
-                    bf16x8 bv = read_cells8(sx + (sc + OFFS[t] + row) * XS + n * 16 + col, XS);
-                    if (masked && t > 0) {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            if (!(fl[sc + j] & fl[sc + OFFS[t] + j])) bv[j] = (__bf16)0.f;
+                for (int n = 0; n < 4; ++n) {
+                    const int s = (w + 1) * SW + n * 16 + l16 + 1;
+                    bf16x8 bv = bf16x8{};
+                    if (tap < 7) {
+                        bv = *reinterpret_cast<const bf16x8 *>(sdy + (s + OFFS[tap]) * DS + c0);
+                        if (masked && tap > 0 && !(fl[s] & fl[s + OFFS[tap]])) bv = bf16x8{};
                     }
+#pragma unroll
+                    for (int m = 0; m < NB; ++m)
+                        da[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], bv, da[m][n], 0, 0, 0);
+                }
+            }
+            const int r = r0 + w;
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                const int q = q0 + n * 16 + l16, s = (w + 1) * SW + n * 16 + l16 + 1;
+                if (q >= nq || r >= nr) continue;
+#pragma unroll
+                for (int m = 0; m < NB; ++m) {
+                    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                    const int co = m * 16 + 4 * g;
+                    const bf16x4 own = *reinterpret_cast<const bf16x4 *>(sx + s * XS + co);
+                    bf16x4 pk;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        pk[j] = (float)own[j] > 0.f ? (__bf16)da[m][n][j] : (__bf16)0.f;
+                    *reinterpret_cast<bf16x4 *>(dx + (soff + (int64_t)r * nq + q) * CIN + co) = pk;
+                }
+            }
+        });
+        for (int v = 0; v < 4; ++v) __syncthreads();  // the other waves' reduction
+    } else {
+        // ---- weight gradient
+        f32x4 acc[7][MB][NB], accb[MB];
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            accb[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < 7; ++t)
+#pragma unroll
+                for (int n = 0; n < NB; ++n) acc[t][m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        bf16x8 ones;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.f;
+
+        sweep([&](int, int q0, int r0) {
+            // dy staged with periodic wraps: positions of the tile past the raster's end hold
+            // other cells', which the weights must not see
+            const bool cut = DX && (cm.perq || cm.perr) && (q0 + TQ > nq || r0 + TR > nr);
+#pragma unroll
+            for (int ks = 0; ks < TQ / 32; ++ks) {
+                const int c0 = ks * 32 + 8 * g;                 // first of this lane's 8 cells
+                const int sc = (w + 1) * SW + (c0 + 1);         // its staged slot
+                const int row = l16 >> 2, col = (l16 & 3) * 4;  // what this lane addresses
+                bf16x8 a[MB];
+#pragma unroll
+                for (int m = 0; m < MB; ++m)
+                    a[m] = read_cells8(sdy + ((DX ? sc : w * TQ + c0) + row) * DS + m * 16 + col, DS);
+                if (cut) {
 #pragma unroll
                     for (int m = 0; m < MB; ++m)
-                        acc[t][m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], bv, acc[t][m][n], 0, 0, 0);
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if (q0 + c0 + j >= nq || r0 + w >= nr) a[m][j] = (__bf16)0.f;
                 }
-            }
-        }
-    }
-    // the four waves' sums in wave order: a lane holds dW rows co = m*16 + 4g + j,
-    // column ci = n*16 + l16
-    for (int v = 0; v < NT / 64; ++v) {
-        __syncthreads();
-        if (w != v) continue;
 #pragma unroll
-        for (int m = 0; m < MB; ++m)
+                for (int m = 0; m < MB; ++m)
+                    accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], ones, accb[m], 0, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int co = m * 16 + 4 * g + j;
-#pragma unroll
-                for (int t = 0; t < 7; ++t)
+                for (int t = 0; t < 7; ++t) {
 #pragma unroll
                     for (int n = 0; n < NB; ++n) {
-                        float *o = red + (t * COUT + co) * CIN + n * 16 + l16;
-                        *o = v == 0 ? acc[t][m][n][j] : *o + acc[t][m][n][j];
+                        bf16x8 bv = read_cells8(sx + (sc + OFFS[t] + row) * XS + n * 16 + col, XS);
+                        if (masked && t > 0) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j)
+                                if (!(fl[sc + j] & fl[sc + OFFS[t] + j])) bv[j] = (__bf16)0.f;
+                        }
+#pragma unroll
+                        for (int m = 0; m < MB; ++m)
+                            acc[t][m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], bv, acc[t][m][n], 0, 0, 0);
                     }
-                if (l16 == 0) {
-                    float *o = red + 7 * COUT * CIN + co;
-                    *o = v == 0 ? accb[m][j] : *o + accb[m][j];
                 }
             }
+        });
+        // the four waves' sums in wave order: a lane holds dW rows co = m*16 + 4g + j,
+        // column ci = n*16 + l16
+        for (int v = 0; v < 4; ++v) {
+            __syncthreads();
+            if (w != v) continue;
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int co = m * 16 + 4 * g + j;
+#pragma unroll
+                    for (int t = 0; t < 7; ++t)
+#pragma unroll
+                        for (int n = 0; n < NB; ++n) {
+                            float *o = red + (t * COUT + co) * CIN + n * 16 + l16;
+                            *o = v == 0 ? acc[t][m][n][j] : *o + acc[t][m][n][j];
+                        }
+                    if (l16 == 0) {
+                        float *o = red + 7 * COUT * CIN + co;
+                        *o = v == 0 ? accb[m][j] : *o + accb[m][j];
+                    }
+                }
+        }
     }
     __syncthreads();
     float *P = part + (int64_t)blockIdx.x * PSZ;
-    for (int e = threadIdx.x; e < PSZ; e += NT) P[e] = red[e];
+    for (int e = threadIdx.x; e < PSZ; e += NTH) P[e] = red[e];
 }
 
 // Sum the workgroups' partials of every layer in a fixed order (deterministic) and
 // scatter them into the flat parameter-gradient layout W[o][c][t] (o < cout, c < cin),
 // b[o].  16 threads share an element, each adding every 16th record with eight loads
 // in flight, then a tree over the 16: one launch for all layers, 15 us at 512
-// records of 4 layers, where one thread per element over 2048 records took 635 us a
+// records of 4 layers (10 with half the records of three), where one thread per element over 2048 records took 635 us a
 // layer (its loads one behind the other).
 constexpr int RED_GRP = 16, RED_EL = 256 / RED_GRP;
-__global__ __launch_bounds__(256) void k_wgrad_reduce(WgradTable tab, int nrec,
+__global__ __launch_bounds__(256) void k_wgrad_reduce(WgradTable tab,
                                                       float *__restrict__ grad) {
     int l = 0;
     while (l + 1 < tab.layers && (int)blockIdx.x >= tab.y[l + 1].block0) ++l;
     const WgradLayer y = tab.y[l];
-    const int psz = 7 * y.coutp * y.cinp + y.coutp;
+    const int psz = 7 * y.coutp * y.cinp + y.coutp, nrec = y.nrec;
     const int el = threadIdx.x % RED_EL, grp = threadIdx.x / RED_EL;
     const int src = ((int)blockIdx.x - y.block0) * RED_EL + el;
     float s = 0.f;
@@ -784,21 +872,18 @@ int conv_tiles(int nq, int nr, int batch) {
 }
 
 hipError_t launch_conv(int cinp, int coutp, int epi, const __bf16 *x, const __bf16 *wm,
-                       const float *bias, void *out, const __bf16 *mask, int nq, int nr,
-                       int batch, int cout_real, const ConvMask &cm, hipStream_t st,
-                       const int32_t *live) {
+                       const float *bias, void *out, int nq, int nr, int batch, int cout_real,
+                       const ConvMask &cm, hipStream_t st, const int32_t *live) {
     const int nt = conv_tiles(nq, nr, batch);
 #define HEXSV_CONV(CI, CO, E)                                                                   \
     if (cinp == CI && coutp == CO && epi == E) {                                                \
         hipLaunchKernelGGL((k_hexconv<CI, CO, E>), dim3(nt), dim3(NT), 0, st, x, wm, bias, out, \
-                           mask, nq, nr, nt, cout_real, live, cm);                              \
+                           nq, nr, nt, cout_real, live, cm);                                    \
         return hipGetLastError();                                                               \
     }
     HEXSV_CONV(16, 32, EPI_RELU)
     HEXSV_CONV(32, 32, EPI_RELU)
     HEXSV_CONV(32, 16, EPI_LIN)
-    HEXSV_CONV(16, 32, EPI_MASK)
-    HEXSV_CONV(32, 32, EPI_MASK)
 #undef HEXSV_CONV
     return hipErrorInvalidValue;
 }
@@ -866,18 +951,20 @@ hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bo
     return hipGetLastError();
 }
 
-int wgrad_records(int nq, int nr, int batch) {
-    const int nt = conv_tiles(nq, nr, batch);
-    return nt < WGRAD_WGS ? nt : WGRAD_WGS;
+int wgrad_records(int nq, int nr, int batch, bool dx) {
+    const int nt = conv_tiles(nq, nr, batch), most = dx ? WGRAD_WGS / 2 : WGRAD_WGS;
+    return nt < most ? nt : most;
 }
 
 hipError_t launch_wgrad(int cinp, int coutp, const __bf16 *x, const __bf16 *dy, float *part,
-                        int nq, int nr, int batch, const ConvMask &cm, hipStream_t st) {
-    const int nt = conv_tiles(nq, nr, batch), nwg = wgrad_records(nq, nr, batch);
+                        const __bf16 *wt, __bf16 *dx, int nq, int nr, int batch,
+                        const ConvMask &cm, hipStream_t st) {
+    if ((cinp == 32) != (dx != nullptr)) return hipErrorInvalidValue;
+    const int nt = conv_tiles(nq, nr, batch), nwg = wgrad_records(nq, nr, batch, dx != nullptr);
 #define HEXSV_WG(CI, CO)                                                                       \
     if (cinp == CI && coutp == CO) {                                                           \
-        hipLaunchKernelGGL((k_hexconv_wgrad<CI, CO>), dim3(nwg), dim3(NT), 0, st, x, dy, part,  \
-                           nq, nr, nt, cm);                                                    \
+        hipLaunchKernelGGL((k_hexconv_wgrad<CI, CO, CI == 32>), dim3(nwg), dim3(WG_NT<CI == 32>), 0, \
+                           st, x, dy, part, wt, dx, nq, nr, nt, cm);                                   \
         return hipGetLastError();                                                              \
     }
     HEXSV_WG(16, 32)
@@ -887,13 +974,13 @@ hipError_t launch_wgrad(int cinp, int coutp, const __bf16 *x, const __bf16 *dy, 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_wgrad_reduce(WgradTable tab, int nrec, float *grad, hipStream_t st) {
+hipError_t launch_wgrad_reduce(WgradTable tab, float *grad, hipStream_t st) {
     int blocks = 0;
     for (int l = 0; l < tab.layers; ++l) {
         tab.y[l].block0 = blocks;
         blocks += (7 * tab.y[l].coutp * tab.y[l].cinp + tab.y[l].coutp + RED_EL - 1) / RED_EL;
     }
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks), dim3(256), 0, st, tab, nrec, grad);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks), dim3(256), 0, st, tab, grad);
     return hipGetLastError();
 }
 

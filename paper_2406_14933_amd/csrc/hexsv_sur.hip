@@ -264,7 +264,7 @@ static int forward_packed(hexsv_surrogate *s, int nq, int nr, int batch, const n
         const bool last = l == s->layers - 1;
         void *o = last ? (void *)s->out : (void *)s->act[l];
         HIP_TRY(nn::launch_conv(y.cinp, y.coutp, last ? nn::EPI_LIN : nn::EPI_RELU, x, y.wm, y.bias,
-                                o, nullptr, nq, nr, batch, y.cout, cm, st, live));
+                                o, nq, nr, batch, y.cout, cm, st, live));
         if (!last) x = s->act[l];
     }
     return HEXSV_OK;
@@ -339,7 +339,7 @@ int sur_forward_hidden(hexsv_surrogate *s, const hexsv_grid *grid, hipStream_t s
     for (int l = 0; l + 1 < s->layers; ++l) {
         const SurLayer &y = s->L[l];
         HIP_TRY(nn::launch_conv(y.cinp, y.coutp, nn::EPI_RELU, x, y.wm, y.bias, s->act[l],
-                                nullptr, nq, nr, 1, y.cout, cm, st, live));
+                                nq, nr, 1, y.cout, cm, st, live));
         x = s->act[l];
     }
     const SurLayer &y = s->L[s->layers - 1];
@@ -367,7 +367,6 @@ static int gradient(hexsv_surrogate *s, const hexsv_grid *grid, int batch, int n
     }
     const double inv_count = 1.0 / (3.0 * (double)cells);
     HIP_TRY(nn::launch_l1_loss(s->out, target, cells, inv_count, s->dy_last, s->lpart, LOSS_PARTS, st));
-    const int nrec = nn::wgrad_records(nq, nr, batch);
     nn::WgradTable tab;
     tab.layers = s->layers;
     float *part = s->wpart;
@@ -376,18 +375,14 @@ static int gradient(hexsv_surrogate *s, const hexsv_grid *grid, int batch, int n
     for (int l = s->layers - 1; l >= 0; --l) {
         const SurLayer &y = s->L[l];
         const __bf16 *xin = l == 0 ? s->x0 : s->act[l - 1];
-        HIP_TRY(nn::launch_wgrad(y.cinp, y.coutp, xin, dy, part, nq, nr, batch, cm, st));
-        tab.y[l] = nn::WgradLayer{part, y.off, y.cinp, y.coutp, y.cin, y.cout, 0};
+        __bf16 *dx = l > 0 ? buf[l & 1] : nullptr;
+        const int nrec = nn::wgrad_records(nq, nr, batch, dx != nullptr);
+        HIP_TRY(nn::launch_wgrad(y.cinp, y.coutp, xin, dy, part, y.wt, dx, nq, nr, batch, cm, st));
+        tab.y[l] = nn::WgradLayer{part, y.off, y.cinp, y.coutp, y.cin, y.cout, nrec, 0};
         part += (size_t)nrec * (7 * y.coutp * y.cinp + y.coutp);
-        if (l > 0) {
-            __bf16 *dx = buf[l & 1];
-            // data gradient: input channels of the transposed stencil = coutp, output = cinp
-            HIP_TRY(nn::launch_conv(y.coutp, y.cinp, nn::EPI_MASK, dy, y.wt, nullptr, dx, s->act[l - 1],
-                                    nq, nr, batch, y.cin, cm, st));
-            dy = dx;
-        }
+        dy = dx;
     }
-    HIP_TRY(nn::launch_wgrad_reduce(tab, nrec, s->d_g, st));
+    HIP_TRY(nn::launch_wgrad_reduce(tab, s->d_g, st));
     HIP_TRY(hipMemcpyAsync(s->h_lpart, s->lpart, sizeof(double) * LOSS_PARTS, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     double tot = 0.0;
@@ -493,7 +488,7 @@ extern "C" int hexsv_surrogate_forward_noalloc(hexsv_surrogate *s, const hexsv_g
         const bool last = l == s->layers - 1;
         void *o = last ? (void *)d_out : (void *)act[l & 1];
         HIP_TRY(nn::launch_conv(y.cinp, y.coutp, last ? nn::EPI_LIN : nn::EPI_RELU, x, y.wm, y.bias,
-                                o, nullptr, nq, nr, batch, y.cout, cm, st));
+                                o, nq, nr, batch, y.cout, cm, st));
         if (!last) x = act[l & 1];
     }
     return HEXSV_OK;
