@@ -158,20 +158,24 @@ __device__ inline bf16x8 tap_of(const Taps &t, int j, int tap) {
     return v;
 }
 
-// Four hidden activations of a cell (channels co..co+3) into its staged row; zeros unless keep.
-__device__ inline uint2 put_act(__bf16 *row, int c, int co, const f32x4 &acc, const float *b,
-                                bool keep) {
+// Output channel of row i of MFMA block m (of two): a lane's eight accumulators, rows 4 g .. 4 g
+// + 3 of both blocks, are channels 8 g .. 8 g + 7, one 16-byte chunk of its cell.
+__device__ inline int row_channel(int m, int i) { return 8 * (i >> 2) + 4 * m + (i & 3); }
+
+// The eight hidden activations of lane group g's cell into its staged row; zeros unless keep.
+__device__ inline uint4 put_act(__bf16 *row, int c, int g, const f32x4 (&acc)[2],
+                                const float (&b)[8], bool keep) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    uint2 w;
-    uint32_t *pw = &w.x;
+    uint32_t w[4];
 #pragma unroll
-    for (int j = 0; j < 4; j += 2) {
-        const float v0 = acc[j] + b[j], v1 = acc[j + 1] + b[j + 1];
+    for (int j = 0; j < 8; j += 2) {
+        const float v0 = acc[j / 4][j % 4] + b[j], v1 = acc[j / 4][j % 4 + 1] + b[j + 1];
         const bf16x2 pk = {(__bf16)(v0 > 0.f ? v0 : 0.f), (__bf16)(v1 > 0.f ? v1 : 0.f)};
-        pw[j / 2] = keep ? __builtin_bit_cast(uint32_t, pk) : 0u;
+        w[j / 2] = keep ? __builtin_bit_cast(uint32_t, pk) : 0u;
     }
-    *reinterpret_cast<uint2 *>(row + act_at(c + 1, co >> 3) + (co & 7)) = w;
-    return w;
+    const uint4 v = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4 *>(row + act_at(c + 1, g)) = v;
+    return v;
 }
 
 // F32IN: x holds the FP32 features (FEATURES per cell), else the packed bf16 input.
@@ -290,15 +294,12 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
             for (int m = 0; m < 2; ++m) {
                 const int tap = 2 * ks + g / 2;
                 w[ks][m] = tap < 7 ? *reinterpret_cast<const bf16x8 *>(
-                                         nw.wm[0] + (tap * 32 + m * 16 + l16) * 16 + (g % 2) * 8)
+                                         nw.wm[0] + (tap * 32 + row_channel(m, l16)) * 16 + (g % 2) * 8)
                                    : bf16x8{};
             }
-        float bb[2][4];
+        float bb[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            bb[0][j] = nw.bias[0][4 * g + j];
-            bb[1][j] = nw.bias[0][16 + 4 * g + j];
-        }
+        for (int j = 0; j < 8; ++j) bb[j] = nw.bias[0][8 * g + j];
         store_rows(ICH);
         // this lane's tap of K step ks is 2 ks or 2 ks + 1; its cell in a staged row
         const bool second = g >= 2;
@@ -346,12 +347,8 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
             }
             operands(u + 1);  // staged two rows ahead at least
             const bool ok = MASK || (qok && inside_r(r));
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const uint2 a = put_act(act[0][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
-                if (mine)
-                    *reinterpret_cast<uint2 *>(keep.act[0] + cell_at(r) * 32 + m * 16 + 4 * g) = a;
-            }
+            const uint4 a = put_act(act[0][u & 1], c, g, acc, bb, ok);
+            if (mine) *reinterpret_cast<uint4 *>(keep.act[0] + cell_at(r) * 32 + 8 * g) = a;
             if (u % ICH == ICH - 1) store_rows(u - (ICH - 1) + 2 * ICH);
             __syncthreads();
         }
@@ -405,13 +402,11 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
         for (int t = 0; t < 7; ++t)
 #pragma unroll
             for (int m = 0; m < 2; ++m)
-                w[t][m] = *reinterpret_cast<const bf16x8 *>(nw.wm[l] + (t * 32 + m * 16 + l16) * 32 + g * 8);
-        float bb[2][4];
+                w[t][m] = *reinterpret_cast<const bf16x8 *>(
+                    nw.wm[l] + (t * 32 + row_channel(m, l16)) * 32 + g * 8);
+        float bb[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            bb[0][j] = nw.bias[l][4 * g + j];
-            bb[1][j] = nw.bias[l][16 + 4 * g + j];
-        }
+        for (int j = 0; j < 8; ++j) bb[j] = nw.bias[l][8 * g + j];
         Taps tp{};
         __syncthreads();
         for (int u0 = 0; u0 < steps; u0 += UN)
@@ -434,12 +429,9 @@ __global__ __launch_bounds__(r4::NTH) void k_hexnet4(const void *__restrict__ x,
                 }
                 const int r = R0 - 3 + u - 2 * l;
                 const bool ok = MASK || (qok && inside_r(r));
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    const uint2 a = put_act(act[l][u & 1], c, m * 16 + 4 * g, acc[m], bb[m], ok);
-                    if (KEEP && own_q && own_r(r))
-                        *reinterpret_cast<uint2 *>(kept + cell_at(r) * 32 + m * 16 + 4 * g) = a;
-                }
+                const uint4 a = put_act(act[l][u & 1], c, g, acc, bb, ok);
+                if (KEEP && own_q && own_r(r))
+                    *reinterpret_cast<uint4 *>(kept + cell_at(r) * 32 + 8 * g) = a;
                 __syncthreads();
             }
     }
