@@ -82,7 +82,7 @@ __global__ __launch_bounds__(NT) void k_hexconv(const __bf16 *__restrict__ x,
 // sweeps a strip of columns row by row with the four layers two rows apart, so a hidden row
 // lives in LDS for one step and never leaves the CU.  The layer chain moves 540 bytes a cell,
 // most of them hidden activations, against the 56 this reads and writes; on 16 x 512 x 512
-// samples it takes 609 us, this 274 us (its MFMAs run at 0.9 PFLOP/s, where an 8192^3 library
+// samples it takes 609 us, this 273 us (its MFMAs run at 0.9 PFLOP/s, where an 8192^3 library
 // product reaches 1.2 on the card).
 //
 // All layers share a frame of 64 columns (four MFMA columns of 16 cells); layer l's outermost
