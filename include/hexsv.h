@@ -264,6 +264,13 @@ int hexsv_sim_set_state(hexsv_sim *sim, double t0, const double *d_h, const doub
  * ENUMERIC: a non-finite value appeared (state left at the failing step). */
 int hexsv_sim_run(hexsv_sim *sim, double t_end, int64_t max_steps, hipStream_t stream);
 
+/* May run() use on-chip launches of many steps where the raster fits (on = 1,
+ * how a simulation starts out), or only launches of one step (on = 0)?  State
+ * and books are the same bit for bit.  EINVAL: null handle or on not 0/1. */
+int hexsv_sim_set_resident(hexsv_sim *sim, int32_t on);
+/* On-chip launches run() has issued so far (-1 for a null handle). */
+int64_t hexsv_sim_resident_launches(const hexsv_sim *sim);
+
 /* Current state as FP64 device arrays (each nullable): h, v1, v2 and the
  * discharges q_a = theta*h*v_a. */
 int hexsv_sim_get_state(const hexsv_sim *sim, double *d_h, double *d_v1, double *d_v2,
@@ -344,6 +351,11 @@ int hexsv_ensemble_set_viscosity(hexsv_ensemble *ens, int32_t on);
  * the scenario's time.  ENUMERIC: a non-finite value appeared. */
 int hexsv_ensemble_run(hexsv_ensemble *ens, const double *t_end, int64_t max_steps,
                        hipStream_t stream);
+
+/* hexsv_sim_set_resident and hexsv_sim_resident_launches for an ensemble's
+ * batched mode. */
+int hexsv_ensemble_set_resident(hexsv_ensemble *ens, int32_t on);
+int64_t hexsv_ensemble_resident_launches(const hexsv_ensemble *ens);
 
 /* State (FP64 device arrays sized for scenario s, each nullable) and books. */
 int hexsv_ensemble_get_state(const hexsv_ensemble *ens, int32_t s, double *d_h, double *d_v1,

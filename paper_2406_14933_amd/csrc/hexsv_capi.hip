@@ -213,6 +213,8 @@ struct hexsv_sim {
     int tile, ntq, ntiles, nwg;
     int gsteps;
     int ncu;  // compute units: the most workgroups of a resident launch
+    bool res_on;          // hexsv_sim_set_resident
+    int64_t res_launches;  // resident launches so far
     // resident steps (k_resident): exchange memory sized for the current tiling, and the
     // next launch's tag
     char *d_res;
@@ -324,6 +326,7 @@ extern "C" int hexsv_sim_create(const hexsv_grid *grid, const hexsv_params *para
     tile_grid(s->tile, grid->kg.nq, grid->kg.nr, &s->ntq, &s->ntiles);
     s->gsteps = p.steps_per_graph > 0 ? p.steps_per_graph : 100;
     s->w_backoff = WIN_BACKOFF_MAX;
+    s->res_on = true;
     s->ring_len = s->gsteps < RING_MAX ? s->gsteps : RING_MAX;
     if (s->ring_len < SHORT_STEPS) s->ring_len = SHORT_STEPS;
     const double a = grid->edge;
@@ -683,7 +686,7 @@ struct ResPlan {
 };
 static bool resident_plan(const hexsv_sim *s, ResPlan *p) {
     const KGrid &g = s->grid->kg;
-    if (s->tile > 2 || g.perq || g.perr) return false;
+    if (!s->res_on || s->tile > 2 || g.perq || g.perr) return false;
     for (int sub = 1; sub <= RES_MAX_SUB; sub *= 2) {
         const int tr = TILES[s->tile].tr * sub;
         const int64_t nwg = (int64_t)s->ntq * ((g.nr + tr - 1) / tr);
@@ -728,6 +731,7 @@ static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, hipStream_t st
     const KClose cl = close_of(s);
     const uint32_t tag0 = s->res_tag;
     s->res_tag += (uint32_t)s->ring_len + 1;
+    s->res_launches += 1;
     hipError_t e =
         s->prec == HEXSV_FP64
             ? launch_resident<double>(s->tile, p.sub, dom_of<double>(s), s->grid->kg, s->kc, s->rn,
@@ -848,6 +852,15 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
     }
     return HEXSV_OK;
 }
+
+extern "C" int hexsv_sim_set_resident(hexsv_sim *s, int32_t on) {
+    if (!s) return fail(HEXSV_EINVAL, "set_resident: null sim");
+    if (on != 0 && on != 1) return fail(HEXSV_EINVAL, "set_resident: on must be 0 or 1");
+    s->res_on = on != 0;
+    return HEXSV_OK;
+}
+
+extern "C" int64_t hexsv_sim_resident_launches(const hexsv_sim *s) { return s ? s->res_launches : -1; }
 
 extern "C" int hexsv_sim_get_state(const hexsv_sim *sc, double *d_h, double *d_v1, double *d_v2,
                                    double *d_q1, double *d_q2, hipStream_t stream) {

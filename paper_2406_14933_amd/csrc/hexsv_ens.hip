@@ -32,6 +32,8 @@ struct hexsv_ensemble {
     // ensemble does not fit) and workgroups; exchange memory, step ring, group tables and the
     // proposed control blocks (allocated when first used), and the next launch's tag
     int res_sub, res_nwg, ncu;
+    bool res_on;           // hexsv_ensemble_set_resident
+    int64_t res_launches;  // resident launches so far
     char *d_res;
     ResSync res;
     Part *d_ring;
@@ -197,6 +199,7 @@ template <typename T>
 static hipError_t ens_resident_launch(hexsv_ensemble *e, hipStream_t st) {
     const uint32_t tag0 = e->res_tag;
     e->res_tag += ENS_RES_STEPS + 1;
+    e->res_launches += 1;
     hipError_t err = launch_ens_resident<T>(e->btile, e->res_sub, e->visc != 0, e->bc != 0,
                                             ens_base<T>(e), e->d_scen, e->d_wgs, e->d_ctl, e->d_out,
                                             e->d_ring, e->res, e->res_nwg, e->btotal, ENS_RES_STEPS,
@@ -303,6 +306,7 @@ extern "C" int hexsv_ensemble_create(int32_t n, const hexsv_grid *const *grids,
     e->prec = p.precision;
     e->esz = p.precision == HEXSV_FP64 ? sizeof(double) : sizeof(float);
     e->tile = 0;
+    e->res_on = true;
     e->ksteps = p.steps_per_graph > 0 ? p.steps_per_graph : 50;
     e->dt_max = p.dt_max;
     e->grids.assign(grids, grids + n);
@@ -567,7 +571,7 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
     HIP_TRY(hipMemcpyAsync(e->d_ctl, e->h_ctl, sizeof(Ctl) * e->n, hipMemcpyHostToDevice, stream));
     // an ensemble that fits on the chip steps in resident launches; scenarios whose part of
     // one was given up (see k_resident) are left to single launches
-    bool resident = e->mode == HEXSV_ENS_BATCHED && e->res_sub > 0 &&
+    bool resident = e->res_on && e->mode == HEXSV_ENS_BATCHED && e->res_sub > 0 &&
                     resident_fits(e->esz, e->btile, e->res_sub, e->visc != 0);
     if (resident) HIP_TRY(ens_ensure_resident(e, stream, &resident));
     bool prepared = false;
@@ -628,6 +632,17 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
     if (e->timing)
         for (int s = 0; s < e->n; ++s) e->timed_updates += (e->h_ctl[s].steps - steps0[s]) * e->active[s];
     return HEXSV_OK;
+}
+
+extern "C" int hexsv_ensemble_set_resident(hexsv_ensemble *e, int32_t on) {
+    if (!e) return fail(HEXSV_EINVAL, "ensemble_set_resident: null ensemble");
+    if (on != 0 && on != 1) return fail(HEXSV_EINVAL, "ensemble_set_resident: on must be 0 or 1");
+    e->res_on = on != 0;
+    return HEXSV_OK;
+}
+
+extern "C" int64_t hexsv_ensemble_resident_launches(const hexsv_ensemble *e) {
+    return e ? e->res_launches : -1;
 }
 
 extern "C" int hexsv_ensemble_get_state(const hexsv_ensemble *ec, int32_t s, double *d_h,

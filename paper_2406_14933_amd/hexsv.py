@@ -103,6 +103,10 @@ _SIGS = [
     ("hexsv_ensemble_info", C.c_int, [_VP, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                       C.POINTER(C.c_int64), C.POINTER(C.c_int32),
                                       C.POINTER(C.c_int32)]),
+    ("hexsv_sim_set_resident", C.c_int, [_VP, C.c_int32]),
+    ("hexsv_sim_resident_launches", C.c_int64, [_VP]),
+    ("hexsv_ensemble_set_resident", C.c_int, [_VP, C.c_int32]),
+    ("hexsv_ensemble_resident_launches", C.c_int64, [_VP]),
     ("hexsv_sim_autotune", C.c_int, [_VP, C.c_int32, C.c_char_p, C.POINTER(C.c_int32),
                                      C.POINTER(C.c_double), _VP]),
     ("hexsv_surrogate_create", C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(_VP)]),
@@ -357,6 +361,15 @@ class Sim:
         b = Books(**{k: d[k] for k, _ in Books._fields_})
         _check(lib().hexsv_sim_set_books(self._h, C.byref(b), _stream()))
 
+    def set_resident(self, on):
+        """Allow run() on-chip launches of many steps (the default) or only single steps; the
+        results are the same bit for bit."""
+        _check(lib().hexsv_sim_set_resident(self._h, int(bool(on))))
+
+    def resident_launches(self):
+        """On-chip launches run() has issued so far."""
+        return int(lib().hexsv_sim_resident_launches(self._h))
+
     def timing(self, enable=None):
         """Totals of the device-timed replays since the last reset; enable=True/False resets."""
         ms, st, rp = C.c_double(), C.c_int64(), C.c_int64()
@@ -482,6 +495,15 @@ class Ensemble:
         b = Books()
         _check(lib().hexsv_ensemble_get_books(self._h, int(s), C.byref(b), _stream()))
         return b.as_dict()
+
+    def set_resident(self, on):
+        """Allow run() on-chip launches of many steps (the default) or only single steps; the
+        results are the same bit for bit."""
+        _check(lib().hexsv_ensemble_set_resident(self._h, int(bool(on))))
+
+    def resident_launches(self):
+        """On-chip launches run() has issued so far."""
+        return int(lib().hexsv_ensemble_resident_launches(self._h))
 
     def timing(self, enable=None):
         ms, cu, ln = C.c_double(), C.c_int64(), C.c_int64()
