@@ -270,6 +270,12 @@ int hexsv_sim_run(hexsv_sim *sim, double t_end, int64_t max_steps, hipStream_t s
 int hexsv_sim_set_resident(hexsv_sim *sim, int32_t on);
 /* On-chip launches run() has issued so far (-1 for a null handle). */
 int64_t hexsv_sim_resident_launches(const hexsv_sim *sim);
+/* An on-chip launch whose workgroups do not all start in time (other streams hold
+ * compute units) is given up without any effect, and single launches do the rest of
+ * the run and of the next runs (1, then 3, 7 ... 63 of them while it goes on).  For
+ * tests of that: the on-chip launch `launch` launches from now (0: the next one) is
+ * given up.  EINVAL: null handle or launch < 0. */
+int hexsv_sim_drop_resident(hexsv_sim *sim, int64_t launch);
 
 /* Current state as FP64 device arrays (each nullable): h, v1, v2 and the
  * discharges q_a = theta*h*v_a. */
@@ -352,10 +358,11 @@ int hexsv_ensemble_set_viscosity(hexsv_ensemble *ens, int32_t on);
 int hexsv_ensemble_run(hexsv_ensemble *ens, const double *t_end, int64_t max_steps,
                        hipStream_t stream);
 
-/* hexsv_sim_set_resident and hexsv_sim_resident_launches for an ensemble's
- * batched mode. */
+/* hexsv_sim_set_resident, hexsv_sim_resident_launches and hexsv_sim_drop_resident
+ * (there by scenario s) for an ensemble's batched mode. */
 int hexsv_ensemble_set_resident(hexsv_ensemble *ens, int32_t on);
 int64_t hexsv_ensemble_resident_launches(const hexsv_ensemble *ens);
+int hexsv_ensemble_drop_resident(hexsv_ensemble *ens, int32_t s, int64_t launch);
 
 /* State (FP64 device arrays sized for scenario s, each nullable) and books. */
 int hexsv_ensemble_get_state(const hexsv_ensemble *ens, int32_t s, double *d_h, double *d_v1,

@@ -215,6 +215,8 @@ struct hexsv_sim {
     int ncu;  // compute units: the most workgroups of a resident launch
     bool res_on;          // hexsv_sim_set_resident
     int64_t res_launches;  // resident launches so far
+    int64_t res_drop;      // launches before the one a test wants given up (< 0: none)
+    ResBackoff res_wait;   // runs left to single launches after a give-up
     // resident steps (k_resident): exchange memory sized for the current tiling, and the
     // next launch's tag
     char *d_res;
@@ -327,6 +329,7 @@ extern "C" int hexsv_sim_create(const hexsv_grid *grid, const hexsv_params *para
     s->gsteps = p.steps_per_graph > 0 ? p.steps_per_graph : 100;
     s->w_backoff = WIN_BACKOFF_MAX;
     s->res_on = true;
+    s->res_drop = -1;
     s->ring_len = s->gsteps < RING_MAX ? s->gsteps : RING_MAX;
     if (s->ring_len < SHORT_STEPS) s->ring_len = SHORT_STEPS;
     const double a = grid->edge;
@@ -720,26 +723,31 @@ static int ensure_resident(hexsv_sim *s, const ResPlan &p, hipStream_t st) {
     s->res.halo = (unsigned long long *)s->d_res;
     s->res.flags = (unsigned long long *)(s->d_res + halo);
     s->res.abort_word = (uint32_t *)(s->d_res + halo + flags);
+    s->res.committed = s->res.abort_word + 32;
     s->res.done = s->res.abort_word + 64;
     s->res.flag_cap = p.nwg;
     s->res_tag = 1;
     return HEXSV_OK;
 }
 
-// One resident launch of up to ring_len steps and its commit.
-static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, hipStream_t st) {
+// One resident launch of up to ring_len steps and its commit.  *after: the tag of the launch
+// queued right before it (0: none), then its own.
+static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, uint32_t *after, hipStream_t st) {
     const KClose cl = close_of(s);
-    const uint32_t tag0 = s->res_tag;
+    const uint32_t tag0 = s->res_tag, prev = *after;
+    const bool drop = s->res_drop == 0;
+    if (s->res_drop >= 0) s->res_drop -= 1;
+    *after = tag0;
     s->res_tag += (uint32_t)s->ring_len + 1;
     s->res_launches += 1;
     hipError_t e =
         s->prec == HEXSV_FP64
             ? launch_resident<double>(s->tile, p.sub, dom_of<double>(s), s->grid->kg, s->kc, s->rn,
                                       s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles, s->ring_len,
-                                      tag0, st)
+                                      tag0, prev, drop, st)
             : launch_resident<float>(s->tile, p.sub, dom_of<float>(s), s->grid->kg, s->kc, s->rn,
                                      s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles, s->ring_len,
-                                     tag0, st);
+                                     tag0, prev, drop, st);
     if (e != hipSuccess) return e;
     return launch_fold_resident(s->d_ctl, cl, s->ntiles, s->kc, s->rn, s->ring_len, s->res, p.nwg,
                                 tag0, st);
@@ -770,19 +778,20 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
     const int64_t limit = c.step_limit;
     HIP_TRY(hipMemcpyAsync(s->d_ctl, s->h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, stream));
     // a raster that fits on the chip steps in resident launches; one that was given up
-    // (see k_resident) leaves the rest of the run to single launches
+    // (see k_resident) leaves the rest of the run, and some of the next runs, to single launches
     ResPlan plan_r;
-    bool resident = resident_plan(s, &plan_r);
-    if (resident) {
-        int rc = ensure_ring(s);
-        if (rc) return rc;
-        rc = ensure_resident(s, plan_r, stream);
-        if (rc == HEXSV_ENOMEM) resident = false;
-        else if (rc) return rc;
-    }
+    bool resident = resident_plan(s, &plan_r) && !s->res_wait.skip();
+    int64_t gave_up = -1;  // steps taken when a launch was given up
     int64_t last_steps = -1;
     for (;;) {
         const int64_t before = c.steps;
+        if (resident) {
+            int rc = ensure_ring(s);
+            if (rc) return rc;
+            rc = ensure_resident(s, plan_r, stream);
+            if (rc == HEXSV_ENOMEM) resident = false;
+            else if (rc) return rc;
+        }
         if (!resident && !s->graph_ok) {
             int rc = capture(s);
             if (rc) return rc;
@@ -817,10 +826,11 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         // live step the graph's hint is right while the steps before it were live (the
         // short graphs go longest first, so the odd ones come last)
         int64_t launched = 0;
+        uint32_t after = 0;
         for (int k = 0; k < reps; ++k) {
             const int p = (int)((c.parity + launched) & 1);
             if (resident) {
-                HIP_TRY(resident_launch(s, plan_r, stream));
+                HIP_TRY(resident_launch(s, plan_r, &after, stream));
             } else if (use_short) {
                 HIP_TRY(hipGraphLaunch(s->sexec[plan[k]][p], stream));
                 launched += SHORT_LEN[plan[k]];
@@ -842,14 +852,18 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         if (c.err)
             return fail(HEXSV_ENUMERIC, "run: non-finite value at cell %d in step %lld (t=%g)",
                         c.err_cell, (long long)c.steps + 1, c.t);
+        if (resident && (c.t >= t_end || c.steps >= limit)) s->res_wait.clear();
         if (c.t >= t_end || c.steps >= limit) break;
-        if (resident && c.steps == before) {
-            resident = false;
+        if (resident && c.steps - before < (int64_t)reps * s->ring_len) {
+            resident = false;  // a committed launch short of the run's end takes ring_len steps
+            gave_up = c.steps;
             continue;
         }
         if (c.steps == last_steps) break;
         last_steps = c.steps;
     }
+    // single launches got further: it was not the state that could not go on
+    if (gave_up >= 0 && c.steps > gave_up) s->res_wait.add();
     return HEXSV_OK;
 }
 
@@ -857,6 +871,13 @@ extern "C" int hexsv_sim_set_resident(hexsv_sim *s, int32_t on) {
     if (!s) return fail(HEXSV_EINVAL, "set_resident: null sim");
     if (on != 0 && on != 1) return fail(HEXSV_EINVAL, "set_resident: on must be 0 or 1");
     s->res_on = on != 0;
+    s->res_wait.clear();
+    return HEXSV_OK;
+}
+
+extern "C" int hexsv_sim_drop_resident(hexsv_sim *s, int64_t launch) {
+    if (!s || launch < 0) return fail(HEXSV_EINVAL, "drop_resident: bad argument");
+    s->res_drop = launch;
     return HEXSV_OK;
 }
 

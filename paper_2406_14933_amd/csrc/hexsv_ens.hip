@@ -34,6 +34,9 @@ struct hexsv_ensemble {
     int res_sub, res_nwg, ncu;
     bool res_on;           // hexsv_ensemble_set_resident
     int64_t res_launches;  // resident launches so far
+    int64_t res_drop;      // launches before the one a test wants given up (< 0: none) ...
+    int res_drop_s;        // ... by this scenario
+    ResBackoff res_wait;   // runs left to single launches after a give-up
     char *d_res;
     ResSync res;
     Part *d_ring;
@@ -152,7 +155,7 @@ static hipError_t ens_ensure_resident(hexsv_ensemble *e, hipStream_t st, bool *o
     const size_t halo = sizeof(unsigned long long) * e->res_nwg *
                         resident_halo_words(e->esz, e->btile, e->res_sub);
     const size_t flags = sizeof(unsigned long long) * 2 * (e->esz / 4) * e->res_nwg;
-    const size_t bytes = halo + flags + sizeof(uint32_t) * ((size_t)e->n + e->res_nwg);
+    const size_t bytes = halo + flags + sizeof(uint32_t) * (2 * (size_t)e->n + e->res_nwg);
     if (e->d_res && e->res_tag > 0xffff0000u) {  // tags start over on clean words
         const hipError_t err = hipMemsetAsync(e->d_res, 0, bytes, st);
         if (err != hipSuccess) return err;
@@ -188,22 +191,27 @@ static hipError_t ens_ensure_resident(hexsv_ensemble *e, hipStream_t st, bool *o
     e->res.halo = (unsigned long long *)e->d_res;
     e->res.flags = (unsigned long long *)(e->d_res + halo);
     e->res.abort_word = (uint32_t *)(e->d_res + halo + flags);
-    e->res.done = e->res.abort_word + e->n;
+    e->res.committed = e->res.abort_word + e->n;
+    e->res.done = e->res.committed + e->n;
     e->res.flag_cap = e->res_nwg;
     e->res_tag = 1;
     return hipSuccess;
 }
 
-// One resident launch and its commit.
+// One resident launch and its commit.  *after: the tag of the launch queued right before it
+// (0: none), then its own.
 template <typename T>
-static hipError_t ens_resident_launch(hexsv_ensemble *e, hipStream_t st) {
-    const uint32_t tag0 = e->res_tag;
+static hipError_t ens_resident_launch(hexsv_ensemble *e, uint32_t *after, hipStream_t st) {
+    const uint32_t tag0 = e->res_tag, prev = *after;
+    const int drop = e->res_drop == 0 ? e->res_drop_s : -1;
+    if (e->res_drop >= 0) e->res_drop -= 1;
+    *after = tag0;
     e->res_tag += ENS_RES_STEPS + 1;
     e->res_launches += 1;
     hipError_t err = launch_ens_resident<T>(e->btile, e->res_sub, e->visc != 0, e->bc != 0,
                                             ens_base<T>(e), e->d_scen, e->d_wgs, e->d_ctl, e->d_out,
                                             e->d_ring, e->res, e->res_nwg, e->btotal, ENS_RES_STEPS,
-                                            tag0, st);
+                                            tag0, prev, drop, st);
     if (err != hipSuccess) return err;
     return launch_ens_fold(e->d_scen, e->d_ctl, e->d_out, e->d_ring, e->res, e->d_groups, e->n,
                            e->btotal, tag0, st);
@@ -307,6 +315,7 @@ extern "C" int hexsv_ensemble_create(int32_t n, const hexsv_grid *const *grids,
     e->esz = p.precision == HEXSV_FP64 ? sizeof(double) : sizeof(float);
     e->tile = 0;
     e->res_on = true;
+    e->res_drop = -1;
     e->ksteps = p.steps_per_graph > 0 ? p.steps_per_graph : 50;
     e->dt_max = p.dt_max;
     e->grids.assign(grids, grids + n);
@@ -569,14 +578,15 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
         steps0[s] = c.steps;
     }
     HIP_TRY(hipMemcpyAsync(e->d_ctl, e->h_ctl, sizeof(Ctl) * e->n, hipMemcpyHostToDevice, stream));
-    // an ensemble that fits on the chip steps in resident launches; scenarios whose part of
-    // one was given up (see k_resident) are left to single launches
+    // an ensemble that fits on the chip steps in resident launches; after one that a scenario
+    // gave up (see k_resident), the rest of the run and some of the next runs are single ones
     bool resident = e->res_on && e->mode == HEXSV_ENS_BATCHED && e->res_sub > 0 &&
-                    resident_fits(e->esz, e->btile, e->res_sub, e->visc != 0);
-    if (resident) HIP_TRY(ens_ensure_resident(e, stream, &resident));
-    bool prepared = false;
+                    resident_fits(e->esz, e->btile, e->res_sub, e->visc != 0) &&
+                    !e->res_wait.skip();
+    bool prepared = false, gave_up = false;
     int64_t launched = 0;  // batched launches since the parities were set
     for (;;) {
+        if (resident) HIP_TRY(ens_ensure_resident(e, stream, &resident));
         if (!resident && !prepared) {
             if (!e->gexec[0]) {
                 int rc = ens_capture(e);
@@ -602,9 +612,10 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
         }
         if (e->timing) HIP_TRY(hipEventRecord(e->ev0, stream));
         if (resident) {
+            uint32_t after = 0;
             for (int k = 0; k < reps; ++k)
-                HIP_TRY(e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, stream)
-                                              : ens_resident_launch<float>(e, stream));
+                HIP_TRY(e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, &after, stream)
+                                              : ens_resident_launch<float>(e, &after, stream));
         } else {
             HIP_TRY(hipGraphLaunch(e->gexec[launched & 1], stream));
             launched += e->ksteps;
@@ -624,11 +635,18 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
                 return fail(HEXSV_ENUMERIC, "ensemble_run: non-finite value in scenario %d at cell %d",
                             s, e->h_ctl[s].err_cell);
             all = all && ens_done(e->h_ctl[s]);
-            stuck = stuck || (resident && !ens_done(e->h_ctl[s]) && e->h_ctl[s].steps == before[s]);
+            // a committed launch short of a scenario's end takes ENS_RES_STEPS steps
+            stuck = stuck || (resident && !ens_done(e->h_ctl[s]) &&
+                              e->h_ctl[s].steps - before[s] < (int64_t)reps * ENS_RES_STEPS);
         }
         if (all) break;
-        if (stuck) resident = false;
+        if (stuck) {
+            resident = false;
+            gave_up = true;
+        }
     }
+    if (resident) e->res_wait.clear();
+    if (gave_up) e->res_wait.add();  // single launches took every scenario to its end
     if (e->timing)
         for (int s = 0; s < e->n; ++s) e->timed_updates += (e->h_ctl[s].steps - steps0[s]) * e->active[s];
     return HEXSV_OK;
@@ -638,6 +656,15 @@ extern "C" int hexsv_ensemble_set_resident(hexsv_ensemble *e, int32_t on) {
     if (!e) return fail(HEXSV_EINVAL, "ensemble_set_resident: null ensemble");
     if (on != 0 && on != 1) return fail(HEXSV_EINVAL, "ensemble_set_resident: on must be 0 or 1");
     e->res_on = on != 0;
+    e->res_wait.clear();
+    return HEXSV_OK;
+}
+
+extern "C" int hexsv_ensemble_drop_resident(hexsv_ensemble *e, int32_t s, int64_t launch) {
+    if (!e || s < 0 || s >= e->n || launch < 0)
+        return fail(HEXSV_EINVAL, "ensemble_drop_resident: bad argument");
+    e->res_drop = launch;
+    e->res_drop_s = s;
     return HEXSV_OK;
 }
 

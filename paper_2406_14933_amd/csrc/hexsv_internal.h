@@ -86,10 +86,11 @@ hipError_t launch_step(int variant, const KDom<T> &d, const KGrid &g, const KCon
 
 // Exchange memory of the resident steps (k_resident): halo words of every tile and
 // wave-speed words of every workgroup (both twice, by the tag's parity), the word
-// that gives a launch up, and each workgroup's mark that it reached the end.
+// that gives a launch up, each workgroup's mark that it reached the end, and the tag of
+// the last launch whose steps were committed (an ensemble: one of the two words per scenario).
 struct ResSync {
     unsigned long long *halo, *flags;
-    uint32_t *abort_word, *done;
+    uint32_t *abort_word, *done, *committed;
     int flag_cap;  // workgroups the flags and marks are sized for
 };
 // The workgroups of a resident launch that advance one domain together: the first one's
@@ -102,6 +103,19 @@ struct ResGroup {
 // A workgroup of an ensemble's resident launch: its scenario and that scenario's group.
 struct ResEnsWg {
     int s, first, count;
+};
+// After a resident launch that was given up although single launches got further (another
+// stream's kernels held compute units), the wait at its roll call (about 4 ms) is not paid
+// again at once: the next 1 runs go without, after a second one in a row the next 3, then 7,
+// up to 63.  Back to none after a run that ended on chip.
+struct ResBackoff {
+    int fails = 0, left = 0;
+    bool skip() { return left > 0 && left-- > 0; }
+    void add() {
+        fails = fails < 6 ? fails + 1 : 6;
+        left = (1 << fails) - 1;
+    }
+    void clear() { fails = left = 0; }
 };
 constexpr int RES_MAX_SUB = 4;
 // Does a resident workgroup fit a CU: its LDS (records, codes, with the viscous flux wave
@@ -118,21 +132,23 @@ inline size_t resident_halo_words(size_t esz, int variant, int sub) {
     return (size_t)2 * 3 * (esz / 4) * 2 * (TILES[variant].tq + TILES[variant].tr * sub);
 }
 // Up to max_steps steps in one launch of nwg workgroups, each a stack of `sub` tiles of
-// `variant` (0, 1 or 2); the launch_fold_resident that follows commits them.
+// `variant` (0, 1 or 2); the launch_fold_resident that follows commits them.  after: the tag
+// of the launch queued right before this one, without whose commit it does nothing (0: there
+// is none).  drop: the launch is to give up at its roll call.
 template <typename T>
 hipError_t launch_resident(int variant, int sub, const KDom<T> &d, const KGrid &g,
                            const KConst &kc, const KRain &rn, Ctl *ctl, const KClose &cl,
                            const ResSync &rs, int ntq, int nwg, int ntiles, int max_steps,
-                           uint32_t tag0, hipStream_t stream);
+                           uint32_t tag0, uint32_t after, bool drop, hipStream_t stream);
 // The same for the scenarios of an ensemble, side by side: nwg workgroups (`wgs`, grouped by
 // scenario), control blocks in `ctl` and proposed ones in `out`, btotal records per ring slot;
 // variant 0 with any sub, or variant 2 with one.  launch_ens_fold commits the scenarios all of
-// whose workgroups reached the end.
+// whose workgroups reached the end.  drop: the scenario that is to give up (-1: none).
 template <typename T>
 hipError_t launch_ens_resident(int variant, int sub, bool visc, bool bc, const KDom<T> &base,
                                const EnsScen *scen, const ResEnsWg *wgs, const Ctl *ctl, Ctl *out,
                                Part *ring, const ResSync &rs, int nwg, int btotal, int max_steps,
-                               uint32_t tag0, hipStream_t stream);
+                               uint32_t tag0, uint32_t after, int drop, hipStream_t stream);
 hipError_t launch_ens_fold(const EnsScen *scen, Ctl *ctl, const Ctl *out, const Part *ring,
                            const ResSync &rs, const int2 *groups, int nscen, int btotal,
                            uint32_t tag0, hipStream_t stream);

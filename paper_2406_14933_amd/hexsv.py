@@ -105,6 +105,8 @@ _SIGS = [
                                       C.POINTER(C.c_int32)]),
     ("hexsv_sim_set_resident", C.c_int, [_VP, C.c_int32]),
     ("hexsv_sim_resident_launches", C.c_int64, [_VP]),
+    ("hexsv_sim_drop_resident", C.c_int, [_VP, C.c_int64]),
+    ("hexsv_ensemble_drop_resident", C.c_int, [_VP, C.c_int32, C.c_int64]),
     ("hexsv_ensemble_set_resident", C.c_int, [_VP, C.c_int32]),
     ("hexsv_ensemble_resident_launches", C.c_int64, [_VP]),
     ("hexsv_sim_autotune", C.c_int, [_VP, C.c_int32, C.c_char_p, C.POINTER(C.c_int32),
