@@ -683,9 +683,10 @@ static int short_plan(int n, int *plan, int cap) {
 // the fewest per workgroup that leave at most one workgroup per compute unit (all of them
 // then fit on the device at once, which the launch needs).  False: the raster is too large,
 // or periodic (a seam's ring cells need not lie on the rim of a ragged tile), or the tile
-// is not one of the 64-wide, 256-thread variants the kernel stacks.
+// is not one of the 64-wide, 256-thread variants the kernel stacks, or single launches are
+// faster however long the run.  min_steps: the shortest run for which they are not.
 struct ResPlan {
-    int sub, ntq, nwg;
+    int sub, ntq, nwg, min_steps;
 };
 static bool resident_plan(const hexsv_sim *s, ResPlan *p) {
     const KGrid &g = s->grid->kg;
@@ -695,8 +696,10 @@ static bool resident_plan(const hexsv_sim *s, ResPlan *p) {
         const int64_t nwg = (int64_t)s->ntq * ((g.nr + tr - 1) / tr);
         if (nwg > s->ncu) continue;
         if (!resident_fits(s->esz, s->tile, sub, s->kc.visc != 0)) return false;
-        *p = ResPlan{sub, s->ntq, (int)nwg};
-        return true;
+        const int least = resident_min_steps(s->esz, s->tile, sub, (int)nwg, s->ncu,
+                                             g.has_mask != 0, s->kc.visc != 0);
+        *p = ResPlan{sub, s->ntq, (int)nwg, least};
+        return least > 0;
     }
     return false;
 }
@@ -753,6 +756,16 @@ static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, uint32_t *afte
                                 tag0, st);
 }
 
+// Steps a run to t_end is expected to take from here: at the current dt bound, or up to the
+// step limit.
+static double steps_left(const hexsv_sim *s, double t_end) {
+    const Ctl &c = *s->h_ctl;
+    const double dt = c.tau < s->p.dt_max ? c.tau : s->p.dt_max;
+    const double need = dt > 0.0 ? (t_end - c.t) / dt + 1.0 : 1.0;
+    const double by_limit = (double)(c.step_limit - c.steps);
+    return by_limit < need ? by_limit : need;
+}
+
 static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, bool ctl_fresh,
                    hipStream_t stream);
 
@@ -780,7 +793,8 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
     // a raster that fits on the chip steps in resident launches; one that was given up
     // (see k_resident) leaves the rest of the run, and some of the next runs, to single launches
     ResPlan plan_r;
-    bool resident = resident_plan(s, &plan_r) && !s->res_wait.skip();
+    bool resident = resident_plan(s, &plan_r) && steps_left(s, t_end) >= plan_r.min_steps &&
+                    !s->res_wait.skip();
     int64_t gave_up = -1;  // steps taken when a launch was given up
     int64_t last_steps = -1;
     for (;;) {
@@ -803,11 +817,9 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         // span of a few steps costs one host round trip).
         // A step limit that leaves a whole number of long graphs before t_end (as a
         // benchmark's step count does) is replayed as exactly those graphs.
-        const double dt = c.tau < s->p.dt_max ? c.tau : s->p.dt_max;
-        double need = dt > 0.0 ? (t_end - c.t) / dt + 1.0 : 1.0;
+        const double need = steps_left(s, t_end);
         const int64_t by_limit = limit - c.steps;
-        const bool exact = !shortg && (double)by_limit < need && by_limit % s->gsteps == 0;
-        if ((double)by_limit < need) need = (double)by_limit;
+        const bool exact = !shortg && need == (double)by_limit && by_limit % s->gsteps == 0;
         const bool use_short = !exact && (shortg || need < 2.0 * s->gsteps);
         int reps;
         int plan[48];  // short graphs of this batch

@@ -127,6 +127,27 @@ constexpr bool resident_fits(size_t esz, int variant, int sub, bool visc) {
     const size_t ns = (size_t)(TILES[variant].tq + 2) * (TILES[variant].tr * sub + 2);
     return ns * (4 * esz + 1 + (visc ? esz : 0)) + 2048 <= 160 * 1024;
 }
+// Fewest steps of a run for which a resident launch of a single domain is the faster way (0:
+// none is): the tiling, its workgroups, and whether the raster has a mask or boundary cells.
+// Times of the same run on chip / in single launches, short and long (4 and 300 steps):
+//   one tile of 4 rows a workgroup: below 1 from the first step on (64 x 64: 0.8, 0.5)
+//   up to 16 rows: 300 x 300 FP32 0.89, 0.50; 512 x 512 FP64 0.97, 0.75, viscous 1.03, 0.81
+//   32 rows FP32: 600 x 600 0.90, 0.65, viscous 1.01, 0.76
+//   64 rows FP32: 1024 x 1024 0.99, 0.77, masked 1.05, 0.86, viscous 1.11, 0.94; viscous with
+//     idle compute units 2000 x 260 1.20, 1.08
+//   FP64 stacks of four 8- or 16-row tiles, two of which a thread stands for, keep up only
+//     where they fill the chip: 1000 x 1000 1.12, 0.87 (16 steps 0.94), 1024 x 800 1.18, 1.00,
+//     800 x 800 1.33, 1.17; with a mask, where the tiles inside it are too few to fill it,
+//     1000 x 1000 1.24, 1.02 and 600 x 600 1.13, 1.06
+inline int resident_min_steps(size_t esz, int variant, int sub, int nwg, int ncu, bool masked,
+                              bool visc) {
+    const int rows = TILES[variant].tr * sub;
+    if (esz == 8 && sub == 4 && variant > 0) return masked || 8 * nwg < 7 * ncu ? 0 : 16;
+    if (visc && rows == 64 && 4 * nwg < 3 * ncu) return 0;
+    if (rows <= 4) return 1;
+    const int n = rows >= 64 ? (masked ? 16 : 8) : rows >= 32 || esz == 8 ? 4 : 2;
+    return visc ? (4 * n < 16 ? 4 * n : 16) : n;
+}
 // 64-bit halo words of one tile (both parities).
 inline size_t resident_halo_words(size_t esz, int variant, int sub) {
     return (size_t)2 * 3 * (esz / 4) * 2 * (TILES[variant].tq + TILES[variant].tr * sub);

@@ -22,12 +22,13 @@ def run(sim, *steps):
 
 @pytest.mark.parametrize("launch", [0, 1, 3])
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
-@pytest.mark.parametrize("nq,nr,tile", [(200, 190, 0), (130, 1100, 0), (700, 1100, 2)])
-def test_single_launches_take_over(hx, nq, nr, tile, precision, launch):
+@pytest.mark.parametrize("nq,nr,tile,option", [(200, 190, 0, "masked"), (130, 1100, 0, "masked"),
+                                                (1000, 1000, 2, "plain")])
+def test_single_launches_take_over(hx, nq, nr, tile, option, precision, launch):
     """Launch 0, 1 or 3 of the five queued for 450 steps is given up: those behind it do
     nothing, so single steps continue from the odd or even buffer of the last commit."""
     print(f"[given up {nq}x{nr} tile {tile} {precision} launch {launch}]", flush=True)
-    sc = scene(nq, nr, "masked")
+    sc = scene(nq, nr, option)
     ref = hx.Sim.from_scenario(sc, precision, tile=tile)
     ref.set_resident(False)
     want = run(ref, 7, 450)

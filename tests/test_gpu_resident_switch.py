@@ -46,7 +46,7 @@ def same(a, b, what):
 # for, each with a ragged last workgroup; a device has 256 compute units
 TILINGS = [(200, 19, 0, 1), (64, 1029, 0, 2), (130, 1100, 0, 4), (64, 40, 1, 1),
            (250, 530, 1, 2), (450, 1003, 1, 4), (90, 50, 2, 1), (300, 1100, 2, 2),
-           (700, 1100, 2, 4)]
+           (1000, 1000, 2, 4)]
 
 
 @pytest.mark.parametrize("option", OPTIONS)
@@ -62,9 +62,12 @@ def test_many_steps_a_launch_equal_single_launches(hx, nq, nr, tile, sub, precis
         for n in (113, 40):  # two launches of up to 100 steps; then from the other buffer
             sim.run(1e9, max_steps=n)
         out.append((sim.state_numpy(), sim.books()))
-        # FP64 viscous cells in stacks too large for a thread's registers stay with single steps
-        built = not (option == "viscous" and precision == "fp64" and
-                     (tile == 2 or (tile == 1 and sub == 4)))
+        # FP64 viscous cells in stacks too large for a thread's registers stay with single
+        # steps, and so do masked FP64 rasters in stacks of four (slower on chip)
+        built = not (precision == "fp64" and
+                     ((option == "viscous" and tile == 2) or
+                      (option in ("masked", "viscous", "flux", "dirichlet") and tile > 0 and
+                       sub == 4)))
         assert (sim.resident_launches() > 0) == (on and built)
         del sim
     same(out[0], out[1], (nq, nr, tile, sub))
@@ -120,6 +123,37 @@ def test_run_shape_does_not_change_results(hx, precision, on):
     sim.run(sc.t_end)
     same((sim.state_numpy(), sim.books()), want, "pieces")
     assert (sim.resident_launches() > 0) == on
+
+
+# (raster, precision, option, steps of a run): a run goes on chip only where that is faster
+ROUTES = [
+    ((64, 64), "fp32", "plain", 1, True),
+    ((64, 64), "fp64", "viscous", 1, True),
+    ((300, 300), "fp32", "plain", 1, False),      # two tiles a workgroup: set up for one step
+    ((300, 300), "fp64", "plain", 3, False),
+    ((300, 300), "fp64", "plain", 4, True),
+    ((512, 512), "fp64", "viscous", 15, False),
+    ((512, 512), "fp64", "viscous", 16, True),
+    ((1000, 1000), "fp32", "plain", 7, False),
+    ((1000, 1000), "fp32", "plain", 8, True),
+    ((1000, 1000), "fp32", "masked", 8, False),
+    ((1000, 1000), "fp32", "masked", 16, True),
+    ((2000, 260), "fp32", "viscous", 200, False),  # idle compute units
+    ((1000, 1000), "fp64", "plain", 15, False),
+    ((1000, 1000), "fp64", "infiltration", 16, True),
+    ((1000, 1000), "fp64", "masked", 200, False),
+    ((750, 750), "fp64", "plain", 200, False),
+    ((500, 600), "fp64", "flux", 200, False),
+]
+
+
+@pytest.mark.parametrize("size,precision,option,steps,on_chip", ROUTES)
+def test_runs_take_the_faster_path(hx, size, precision, option, steps, on_chip):
+    print(f"[route {size} {precision} {option} {steps} steps]", flush=True)
+    sim = hx.Sim.from_scenario(scene(*size, option), precision)
+    sim.run(1e9, max_steps=steps)
+    assert sim.books()["steps"] == steps
+    assert (sim.resident_launches() > 0) == on_chip
 
 
 def test_switch_arguments(hx):
