@@ -422,9 +422,10 @@ int64_t hexsv_surrogate_num_params(const hexsv_surrogate *sur);
 /* k of create: the solver steps one window spans (EINVAL at create if k < 1).
  * The window calls below take it when their own k is <= 0.  -1 for a null handle. */
 int32_t hexsv_surrogate_steps(const hexsv_surrogate *sur);
-/* Forward of the 4-layer, 32-channel network as one fused kernel (on = 1, the
- * default: activations stay on chip, a workgroup sweeps 58 columns row by row
- * with the layers two rows apart) or one launch per layer (on = 0).  Both give
+/* Forward of the 4-layer, 32-channel network as one fused kernel (on = 1:
+ * activations stay on chip, a workgroup sweeps 58 columns row by row with the
+ * layers two rows apart) or one launch per layer (on = 0).  Until this is
+ * called each forward takes the one that is faster for its samples.  Both give
  * the same outputs bit for bit; other depths always run per layer.  EINVAL:
  * null handle or on not 0/1. */
 int hexsv_surrogate_set_fused(hexsv_surrogate *sur, int32_t on);

@@ -48,6 +48,10 @@ struct Net4 {
 struct Net4Keep {
     __bf16 *x0, *act[3];
 };
+// Does that beat the layer chain on these samples?  (a forward call, a gradient's forward, a
+// surrogate window)
+enum Net4Use { NET4_FORWARD, NET4_KEEP, NET4_WINDOW };
+bool net4_pays(int nq, int nr, int batch, bool masked, Net4Use use);
 hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bool w4, int nq,
                        int nr, int batch, const ConvMask &cm, hipStream_t st,
                        const int32_t *live = nullptr, const Net4Keep *keep = nullptr);

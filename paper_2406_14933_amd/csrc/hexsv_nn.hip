@@ -900,6 +900,33 @@ static int net4_segments(int nq, int nr, int batch) {
     return best;
 }
 
+// Is the one launch the faster way, against the layer chain?  It recomputes margins (nine rows
+// of a segment, six columns of a strip) and fills a CU with one strip of one sample, so many
+// small samples are the chain's, and so are narrow masked ones.  Estimates in us, from both
+// sides measured over 1 to 20000 samples of 1 x 1 to 1000 x 1000 cells: a step of the sweep,
+// with a domain mask, with a mask and activations to keep; the chain by its tiles beyond those
+// of one round and by its cells.  In a window the chain's last layer forms the predicted state
+// as well, worth 6 us.  Measured, fused / chain: forward 4096 x 8 x 8 282 / 166 us, 512 x 16 x
+// 16 65 / 74, masked 64 x 64 x 64 89 / 77 and 64 x 58 x 58 63 / 71; masked gradient 1 x 512 x
+// 512 275 / 255; masked window 512 x 512 84 / 73, 2048 x 1024 373 / 453.
+bool net4_pays(int nq, int nr, int batch, bool masked, Net4Use use) {
+    const int64_t strips = (int64_t)((nq + r4::OW - 1) / r4::OW) * batch;
+    const int nseg = net4_segments(nq, nr, batch), rh = (nr + nseg - 1) / nseg;
+    const double rounds = (double)((strips * nseg + 255) / 256);
+    const double cells = (double)batch * nq * nr;
+    const double tiles = (double)((nq + TQ - 1) / TQ) * ((nr + TR - 1) / TR) * batch;
+    const double more = tiles > 512 ? tiles - 512 : 0;
+    double fused, chain;
+    if (masked) {
+        fused = 20 + (use == NET4_KEEP ? 1.9 : 1.3) * rounds * (rh + 11) + 4.8e-5 * cells;
+        chain = 42 + 0.0177 * more + 1e-4 * cells;
+    } else {
+        fused = 18 + 0.72 * rounds * (rh + 15) + 1e-5 * cells;
+        chain = 38 + 0.0133 * more + 9e-5 * cells;
+    }
+    return fused <= (use == NET4_WINDOW ? chain - 6 : chain);
+}
+
 hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bool w4, int nq,
                        int nr, int batch, const ConvMask &cm, hipStream_t st,
                        const int32_t *live, const Net4Keep *keep) {

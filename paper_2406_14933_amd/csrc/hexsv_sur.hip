@@ -24,7 +24,8 @@ struct SurLayer {
 struct hexsv_surrogate {
     int layers, channels;
     int k;  // solver steps a window spans (its rain sub-steps)
-    bool fused;  // forward of the 4-layer, 32-channel network in one kernel (k_hexnet4)
+    int fused;  // forward of the 4-layer, 32-channel network in one kernel (k_hexnet4): 1 always,
+                // 0 never, -1 where that is faster
     int64_t nparams;
     float *d_p, *d_m, *d_v, *d_g;
     std::vector<SurLayer> L;
@@ -113,9 +114,7 @@ extern "C" int hexsv_surrogate_create(int32_t layers, int32_t channels, int32_t 
     s->layers = layers;
     s->channels = channels;
     s->k = k;
-    // 273 us against the layer chain's 609 on 16 x 512 x 512 samples, 22 against 34 on one of
-    // 100 x 75 cells with a domain mask, 26 against 47 in a 512 x 512 window
-    s->fused = true;
+    s->fused = -1;
     int64_t off = 0;
     for (int l = 0; l < layers; ++l) {
         SurLayer y{};
@@ -171,7 +170,7 @@ extern "C" int32_t hexsv_surrogate_steps(const hexsv_surrogate *s) { return s ? 
 extern "C" int hexsv_surrogate_set_fused(hexsv_surrogate *s, int32_t on) {
     if (!s) return fail(HEXSV_EINVAL, "surrogate_set_fused: null surrogate");
     if (on != 0 && on != 1) return fail(HEXSV_EINVAL, "surrogate_set_fused: on must be 0 or 1");
-    s->fused = on != 0;
+    s->fused = on;
     return HEXSV_OK;
 }
 
@@ -229,15 +228,18 @@ static int conv_mask(const hexsv_grid *g, int nq, int nr, nn::ConvMask *cm, cons
 }
 
 // Does the forward run as one kernel (k_hexnet4)?  Rasters too wide for its launch do not.
-static bool runs_fused(const hexsv_surrogate *s, int nq) {
-    return s->fused && s->layers == 4 && s->channels == 32 && nq <= 1 << 26;
+static bool runs_fused(const hexsv_surrogate *s, int nq, int nr, int batch,
+                       const nn::ConvMask &cm, nn::Net4Use use) {
+    if (!s->fused || s->layers != 4 || s->channels != 32 || nq > 1 << 26) return false;
+    return s->fused > 0 || nn::net4_pays(nq, nr, batch, cm.active != nullptr, use);
 }
 // From the features straight to the caller's output, unless they overlap (the kernel reads
 // features while it writes outputs).
-static bool runs_direct(const hexsv_surrogate *s, int nq, int64_t cells, const float *f,
-                        const float *out) {
-    return runs_fused(s, nq) &&
-           (out + cells * nn::OUT_STRIDE <= f || f + cells * nn::FEATURES <= out);
+static bool runs_direct(const hexsv_surrogate *s, int nq, int nr, int batch,
+                        const nn::ConvMask &cm, const float *f, const float *out) {
+    const int64_t cells = (int64_t)batch * nq * nr;
+    return (out + cells * nn::OUT_STRIDE <= f || f + cells * nn::FEATURES <= out) &&
+           runs_fused(s, nq, nr, batch, cm, nn::NET4_FORWARD);
 }
 static nn::Net4 net4_of(const hexsv_surrogate *s) {
     nn::Net4 nw;
@@ -248,13 +250,12 @@ static nn::Net4 net4_of(const hexsv_surrogate *s) {
     return nw;
 }
 
-// Forward over the packed features already in s->x0; output in s->out.  With
-// fusion switched on, the 4-layer, 32-channel network runs as one kernel unless
-// the hidden activations are wanted (keep_act: the gradient reads them); both
-// paths give the same output bit for bit.
+// Forward over the packed features already in s->x0; output in s->out, in one kernel or (with
+// the hidden activations, which the gradient reads) as the layer chain; the same output bit
+// for bit.
 static int forward_packed(hexsv_surrogate *s, int nq, int nr, int batch, const nn::ConvMask &cm,
-                          hipStream_t st, const int32_t *live = nullptr, bool keep_act = false) {
-    if (!keep_act && runs_fused(s, nq)) {
+                          hipStream_t st, bool fused, const int32_t *live = nullptr) {
+    if (fused) {
         HIP_TRY(nn::launch_net4(s->x0, false, net4_of(s), s->out, true, nq, nr, batch, cm, st, live));
         return HEXSV_OK;
     }
@@ -292,7 +293,7 @@ extern "C" int hexsv_surrogate_forward(hexsv_surrogate *s, const hexsv_grid *gri
     if (rc) return rc;
     rc = check_call(s, batch, nq, nr);
     if (rc) return rc;
-    if (runs_direct(s, nq, (int64_t)batch * nq * nr, d_features, d_out)) {  // no workspace
+    if (runs_direct(s, nq, nr, batch, cm, d_features, d_out)) {  // no workspace
         HIP_TRY(nn::launch_net4(d_features, true, net4_of(s), d_out, true, nq, nr, batch, cm, st));
         return HEXSV_OK;
     }
@@ -300,7 +301,8 @@ extern "C" int hexsv_surrogate_forward(hexsv_surrogate *s, const hexsv_grid *gri
     rc = check_shape(s, batch, nq, nr, &cells);
     if (rc) return rc;
     HIP_TRY(nn::launch_pack_features(d_features, cells, s->x0, st));
-    rc = forward_packed(s, nq, nr, batch, cm, st);
+    rc = forward_packed(s, nq, nr, batch, cm, st,
+                        runs_fused(s, nq, nr, batch, cm, nn::NET4_FORWARD));
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(d_out, s->out, sizeof(float) * nn::OUT_STRIDE * cells,
                            hipMemcpyDeviceToDevice, st));
@@ -325,15 +327,17 @@ int sur_forward_x0(hexsv_surrogate *s, const hexsv_grid *grid, hipStream_t st,
     nn::ConvMask cm;
     int rc = conv_mask(grid, grid->kg.nq, grid->kg.nr, &cm, "run_surrogate");
     if (rc) return rc;
-    return forward_packed(s, grid->kg.nq, grid->kg.nr, 1, cm, st, live);
+    const int nq = grid->kg.nq, nr = grid->kg.nr;
+    return forward_packed(s, nq, nr, 1, cm, st, runs_fused(s, nq, nr, 1, cm, nn::NET4_WINDOW), live);
 }
 
 int sur_forward_hidden(hexsv_surrogate *s, const hexsv_grid *grid, hipStream_t st,
                        const int32_t *live, SurLast *last) {
-    if (runs_fused(s, grid->kg.nq) || s->channels != 32) return HEXSV_EUNSUPPORTED;
     nn::ConvMask cm;
     int rc = conv_mask(grid, grid->kg.nq, grid->kg.nr, &cm, "run_surrogate");
     if (rc) return rc;
+    if (s->channels != 32 || runs_fused(s, grid->kg.nq, grid->kg.nr, 1, cm, nn::NET4_WINDOW))
+        return HEXSV_EUNSUPPORTED;
     const int nq = grid->kg.nq, nr = grid->kg.nr;
     const __bf16 *x = s->x0;
     for (int l = 0; l + 1 < s->layers; ++l) {
@@ -356,13 +360,13 @@ static int gradient(hexsv_surrogate *s, const hexsv_grid *grid, int batch, int n
     int64_t cells;
     rc = check_shape(s, batch, nq, nr, &cells);
     if (rc) return rc;
-    if (runs_fused(s, nq)) {
+    if (runs_fused(s, nq, nr, batch, cm, nn::NET4_KEEP)) {
         const nn::Net4Keep keep{s->x0, {s->act[0], s->act[1], s->act[2]}};
         HIP_TRY(nn::launch_net4(feat, true, net4_of(s), s->out, false, nq, nr, batch, cm, st, nullptr,
                                 &keep));
     } else {
         HIP_TRY(nn::launch_pack_features(feat, cells, s->x0, st));
-        rc = forward_packed(s, nq, nr, batch, cm, st, nullptr, true);
+        rc = forward_packed(s, nq, nr, batch, cm, st, false);
         if (rc) return rc;
     }
     const double inv_count = 1.0 / (3.0 * (double)cells);
@@ -471,7 +475,7 @@ extern "C" int hexsv_surrogate_forward_noalloc(hexsv_surrogate *s, const hexsv_g
     nn::ConvMask cm;
     int rc = conv_mask(grid, nq, nr, &cm, "surrogate_forward_noalloc");
     if (rc) return rc;
-    if (runs_direct(s, nq, cells, d_features, d_out)) {
+    if (runs_direct(s, nq, nr, batch, cm, d_features, d_out)) {
         HIP_TRY(nn::launch_net4(d_features, true, net4_of(s), d_out, false, nq, nr, batch, cm, st));
         return HEXSV_OK;
     }

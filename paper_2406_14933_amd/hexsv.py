@@ -578,8 +578,9 @@ class Surrogate:
         return n // (nq * nr)
 
     def set_fused(self, on=True):
-        """Forward of the 4-layer, 32-channel network as one fused kernel (how a surrogate
-        starts out) or one launch per layer; the outputs are the same bit for bit."""
+        """Forward of the 4-layer, 32-channel network always as one fused kernel, or always one
+        launch per layer (a surrogate starts out with the faster of the two for each call); the
+        outputs are the same bit for bit."""
         _check(lib().hexsv_surrogate_set_fused(self._h, 1 if on else 0))
 
     # grid (optional): the raster whose neighbour rule the taps follow (periodic sides, the
