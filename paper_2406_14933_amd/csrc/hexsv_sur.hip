@@ -170,6 +170,7 @@ extern "C" int32_t hexsv_surrogate_steps(const hexsv_surrogate *s) { return s ? 
 extern "C" int hexsv_surrogate_set_fused(hexsv_surrogate *s, int32_t on) {
     if (!s) return fail(HEXSV_EINVAL, "surrogate_set_fused: null surrogate");
     if (on != 0 && on != 1) return fail(HEXSV_EINVAL, "surrogate_set_fused: on must be 0 or 1");
+    if (s->fused != on) s->ws_gen += 1;  // captured windows hold the other kernels
     s->fused = on;
     return HEXSV_OK;
 }

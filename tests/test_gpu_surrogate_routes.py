@@ -105,3 +105,14 @@ def test_windows_take_the_faster_route(hx, nq, nr, masked, fused):
     seen = kernels(lambda: windows(sc, sim, sur))
     assert seen["k_win_probe"] == 16
     assert (seen.get("k_hexnet4", 0), seen.get("k_win_last", 0)) == ((16, 0) if fused else (0, 16))
+
+
+def test_windows_follow_set_fused(hx):
+    """The windows' graphs are captured on the first call; set_fused afterwards holds for them."""
+    sc, sim, sur = still(hx, 100, 75, False)
+    windows(sc, sim, sur)
+    for on in (False, True, False):
+        sur.set_fused(on)
+        seen = kernels(lambda: windows(sc, sim, sur))
+        got = tuple(seen.get(k, 0) for k in ("k_hexnet4", "k_win_apply", "k_hexconv<", "k_win_last"))
+        assert got == ((16, 16, 0, 0) if on else (0, 0, 48, 16))
