@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -32,8 +33,8 @@ struct hexsv_surrogate {
     int adam_step;
     bool weights_ready;
     float scales[8];
-    // workspace sized for ws_cells cells and ws_tiles conv tiles; ws_gen
-    // counts reallocations (a captured graph holds the buffer addresses)
+    // workspace sized for ws_cells cells and ws_tiles conv tiles; ws_gen names it
+    // (a captured graph holds the buffer addresses and the kernels chosen)
     int64_t ws_cells;
     int ws_tiles;
     uint64_t ws_gen;
@@ -49,6 +50,13 @@ struct hexsv_surrogate {
 static const int LOSS_PARTS = 1024;
 
 extern "C" void hexsv_surrogate_destroy(hexsv_surrogate *s);
+
+// Generations are never used twice in a process: a simulation keeps the windows it captured
+// by surrogate and generation, and a later surrogate may get a destroyed one's address.
+static uint64_t next_gen() {
+    static std::atomic<uint64_t> last{0};
+    return ++last;
+}
 
 static void free_ws(hexsv_surrogate *s) {
     auto F = [](void *p) { if (p) (void)hipFree(p); };
@@ -98,7 +106,7 @@ static int ensure_ws(hexsv_surrogate *s, int64_t cells, int tiles) {
     }
     s->ws_cells = cells;
     s->ws_tiles = tiles;
-    s->ws_gen += 1;
+    s->ws_gen = next_gen();
     return HEXSV_OK;
 }
 
@@ -170,7 +178,7 @@ extern "C" int32_t hexsv_surrogate_steps(const hexsv_surrogate *s) { return s ? 
 extern "C" int hexsv_surrogate_set_fused(hexsv_surrogate *s, int32_t on) {
     if (!s) return fail(HEXSV_EINVAL, "surrogate_set_fused: null surrogate");
     if (on != 0 && on != 1) return fail(HEXSV_EINVAL, "surrogate_set_fused: on must be 0 or 1");
-    if (s->fused != on) s->ws_gen += 1;  // captured windows hold the other kernels
+    if (s->fused != on) s->ws_gen = next_gen();  // captured windows hold the other kernels
     s->fused = on;
     return HEXSV_OK;
 }

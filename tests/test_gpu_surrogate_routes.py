@@ -116,3 +116,29 @@ def test_windows_follow_set_fused(hx):
         seen = kernels(lambda: windows(sc, sim, sur))
         got = tuple(seen.get(k, 0) for k in ("k_hexnet4", "k_win_apply", "k_hexconv<", "k_win_last"))
         assert got == ((16, 16, 0, 0) if on else (0, 0, 48, 16))
+
+
+def test_a_new_surrogate_at_an_old_address(hx):
+    """A simulation that captured windows with a surrogate since destroyed uses the next one's
+    weights and buffers, also where the allocator hands its address out again."""
+    sc, sim, sur = still(hx, 100, 75, False)
+    windows(sc, sim, sur)
+    old, kept = sur._h.value, []
+    del sur
+    for _ in range(16):
+        kept.append(hx.Surrogate(4, 32))
+        if kept[-1]._h.value == old:
+            break
+    sur = kept[-1]
+    p = np.zeros(sur.num_params, np.float32)
+    p[-3:] = 0.01, 0.002, -0.001  # the last layer's biases: a constant change per window
+    sur.set_params(p)
+    sur.set_scales([0.05, 0.01, 1.0, 0.001, 0.001, 0.05])
+    windows(sc, sim, sur)
+    got = sim.state_numpy()
+    fresh = hx.Sim.from_scenario(sc, "fp32")
+    windows(sc, fresh, sur)
+    want = fresh.state_numpy()
+    assert not np.array_equal(want["h"], sc.h0.astype(np.float32))
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
