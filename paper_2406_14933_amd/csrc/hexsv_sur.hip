@@ -302,7 +302,8 @@ extern "C" int hexsv_surrogate_forward(hexsv_surrogate *s, const hexsv_grid *gri
     if (rc) return rc;
     rc = check_call(s, batch, nq, nr);
     if (rc) return rc;
-    if (runs_direct(s, nq, nr, batch, cm, d_features, d_out)) {  // no workspace
+    // straight to the caller's cells (no workspace) where they take 16-byte stores
+    if (((uintptr_t)d_out & 15) == 0 && runs_direct(s, nq, nr, batch, cm, d_features, d_out)) {
         HIP_TRY(nn::launch_net4(d_features, true, net4_of(s), d_out, true, nq, nr, batch, cm, st));
         return HEXSV_OK;
     }

@@ -75,6 +75,33 @@ def test_calls_take_the_faster_route(hx, batch, nq, nr, masked, forward, gradien
         assert loss == out["g"][0] and torch.equal(g, out["g"][1])
 
 
+@pytest.mark.parametrize("shift", [0, 1, 2, 3, 4])
+def test_forward_to_any_float_address(hx, shift):
+    """Outputs that are no multiple of 16 bytes: the four floats of a cell are one store only
+    where they are."""
+    nq, nr = 100, 75
+    sur, _, f, _ = network(hx, 1, nq, nr, False)
+    want = sur.forward(f, nq, nr)
+    buf = torch.full((4 * nq * nr + 8,), 7.0, device="cuda")
+    out = buf[shift:shift + 4 * nq * nr]
+    assert (out.data_ptr() % 16 == 0) == (shift % 4 == 0)
+
+    def call():
+        hx._check(hx.lib().hexsv_surrogate_forward(sur._h, None, 1, nq, nr, hx._ptr(f),
+                                                   hx._ptr(out), hx._stream()))
+
+    call()
+    assert torch.equal(out.view(-1, 4)[:, :3], want[:, :3])
+    assert bool((buf[:shift] == 7).all()) and bool((buf[shift + 4 * nq * nr:] == 7).all())
+    # the general route: packed input, the workspace's output, a copy
+    seen = kernels(call)
+    assert seen == {"k_hexnet4": 1}
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    assert any("k_pack_features" in e.name for e in p.events()) == (shift % 4 != 0)
+
+
 def still(hx, nq, nr, masked):
     """Still water in a closed basin: a network of zeros is kept in every window."""
     sc = synth.c1_planar(nq, nr, t_end=1e9)
