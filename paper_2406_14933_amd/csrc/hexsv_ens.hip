@@ -136,6 +136,16 @@ static void ens_plan_resident(hexsv_ensemble *e) {
     }
 }
 
+// Batched tile of an ensemble that neither its caller nor the tuning cache gives one.  A small
+// FP64 ensemble takes 64 x 4 tiles if four of them per workgroup then fit on the chip at once:
+// one cell per thread, where 64 x 16 tiles leave four to each thread of a quarter of the waves
+// (100 steps on chip, 64 x 16 -> 64 x 4: 8 rasters of 64 x 64 835 -> 413 us, one of 64 x 4000
+// 912 -> 933; in single launches, which periodic rasters take, 1513 -> 989 and 1571 -> 1305).
+// FP32 keeps the default tile, whose rounding its runs have.
+static int ens_default_btile(const hexsv_ensemble *e) {
+    return e->prec == HEXSV_FP64 && ens_res_wgs(e, 0, RES_MAX_SUB) <= e->ncu ? 0 : DEFAULT_TILE;
+}
+
 static void ens_free_resident(hexsv_ensemble *e) {
     if (e->d_res) (void)hipFree(e->d_res);
     if (e->d_ring) (void)hipFree(e->d_ring);
@@ -350,17 +360,13 @@ extern "C" int hexsv_ensemble_create(int32_t n, const hexsv_grid *const *grids,
     {
         int64_t cells = 0;
         for (int s = 0; s < n; ++s) cells += grids[s]->n_active;
-        const int tuned = tuned_tile("ensemble", p.precision, cells, 100 * HEXSV_ENS_BATCHED + DEFAULT_TILE);
-        e->mode = p.ensemble_mode == HEXSV_ENS_AUTO ? tuned / 100 : p.ensemble_mode;
+        const int tuned = p.ensemble_mode == HEXSV_ENS_AUTO
+                              ? tuned_tile("ensemble", p.precision, cells, -1) : -1;
+        e->mode = p.ensemble_mode;
+        if (e->mode == HEXSV_ENS_AUTO) e->mode = tuned >= 0 ? tuned / 100 : HEXSV_ENS_BATCHED;
         if (e->mode != HEXSV_ENS_PERSISTENT && e->mode != HEXSV_ENS_BATCHED) e->mode = HEXSV_ENS_BATCHED;
-        int v = p.tile >= 0 ? p.tile : (p.ensemble_mode == HEXSV_ENS_AUTO ? tuned % 100 : 0);
-        if (p.tile < 0 && p.ensemble_mode == HEXSV_ENS_BATCHED) v = DEFAULT_TILE;
-        // a small FP64 ensemble takes 64 x 4 tiles if four of them per workgroup then fit on the
-        // chip at once: one cell per thread, where 64 x 16 tiles leave four to each thread of a
-        // quarter of the waves.  FP32 keeps the default tile, whose rounding its runs have.
-        if (p.tile < 0 && e->mode == HEXSV_ENS_BATCHED && v == DEFAULT_TILE &&
-            p.precision == HEXSV_FP64 && ens_res_wgs(e, 0, RES_MAX_SUB) <= e->ncu)
-            v = 0;
+        int v = p.tile >= 0 ? p.tile : tuned >= 0 ? tuned % 100 : 0;
+        if (p.tile < 0 && tuned < 0 && e->mode == HEXSV_ENS_BATCHED) v = ens_default_btile(e);
         const int lim = e->mode == HEXSV_ENS_PERSISTENT ? NUM_ENS_TILES : NUM_TILES;
         if (v < 0 || v >= lim) {
             delete e;
