@@ -304,8 +304,9 @@ int hexsv_sim_timing(hexsv_sim *sim, int32_t enable, double *gpu_ms, int64_t *st
 int hexsv_sim_time_kernel(hexsv_sim *sim, int32_t nlaunch, double *avg_ms, hipStream_t stream);
 
 /* Autotuner: time every tile variant of the step kernel on this simulation's
- * raster and current state (nlaunch launches each, as hexsv_sim_time_kernel,
- * leaving state and books unchanged), switch the simulation to the fastest
+ * raster and current state (nlaunch steps each, in the launches that run()
+ * would take with that variant: on chip, or single ones as
+ * hexsv_sim_time_kernel; state and books are left unchanged), switch the simulation to the fastest
  * and, if cache_path is non-null, record the result there (JSON keyed by
  * architecture, kernel, precision and size bucket).  hexsv_sim_create
  * consults the file named by $HEXSV_TUNE_CACHE when params->tile < 0. */
@@ -375,7 +376,8 @@ int hexsv_ensemble_get_books(hexsv_ensemble *ens, int32_t s, hexsv_books *out, h
 int hexsv_ensemble_timing(hexsv_ensemble *ens, int32_t enable, double *gpu_ms,
                           int64_t *cell_updates, int64_t *launches);
 /* Autotuner of the ensemble: ksteps steps of every tile variant of both modes
- * from the current state (state and books are restored afterwards); switch
+ * from the current state (variants that run() takes on chip: a whole on-chip
+ * launch, scaled to ksteps; state and books are restored afterwards); switch
  * to the fastest mode and variant; record it in cache_path when non-null. */
 int hexsv_ensemble_autotune(hexsv_ensemble *ens, int32_t ksteps, const char *cache_path,
                             int32_t *best_tile, double *best_ms, hipStream_t stream);

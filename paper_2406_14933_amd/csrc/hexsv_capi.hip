@@ -733,16 +733,13 @@ static int ensure_resident(hexsv_sim *s, const ResPlan &p, hipStream_t st) {
     return HEXSV_OK;
 }
 
-// One resident launch of up to ring_len steps and its commit.  *after: the tag of the launch
-// queued right before it (0: none), then its own.
-static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, uint32_t *after, hipStream_t st) {
+// A resident launch of up to ring_len steps and its fold, which commits them only if `commit`
+// (no workgroup ever marks tag0 + 1).  prev: the tag of the launch queued right before it.
+static hipError_t resident_issue(hexsv_sim *s, const ResPlan &p, uint32_t prev, bool drop,
+                                 bool commit, hipStream_t st) {
     const KClose cl = close_of(s);
-    const uint32_t tag0 = s->res_tag, prev = *after;
-    const bool drop = s->res_drop == 0;
-    if (s->res_drop >= 0) s->res_drop -= 1;
-    *after = tag0;
+    const uint32_t tag0 = s->res_tag;
     s->res_tag += (uint32_t)s->ring_len + 1;
-    s->res_launches += 1;
     hipError_t e =
         s->prec == HEXSV_FP64
             ? launch_resident<double>(s->tile, p.sub, dom_of<double>(s), s->grid->kg, s->kc, s->rn,
@@ -753,7 +750,17 @@ static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, uint32_t *afte
                                      tag0, prev, drop, st);
     if (e != hipSuccess) return e;
     return launch_fold_resident(s->d_ctl, cl, s->ntiles, s->kc, s->rn, s->ring_len, s->res, p.nwg,
-                                tag0, st);
+                                commit ? tag0 : tag0 + 1, st);
+}
+
+// One of a run's.  *after: the tag of the launch queued right before it (0: none), then its own.
+static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, uint32_t *after, hipStream_t st) {
+    const uint32_t prev = *after;
+    const bool drop = s->res_drop == 0;
+    if (s->res_drop >= 0) s->res_drop -= 1;
+    *after = s->res_tag;
+    s->res_launches += 1;
+    return resident_issue(s, p, prev, drop, true, st);
 }
 
 // Steps a run to t_end is expected to take from here: at the current dt bound, or up to the
@@ -969,6 +976,52 @@ extern "C" int hexsv_sim_time_kernel(hexsv_sim *s, int32_t nlaunch, double *avg_
     return HEXSV_OK;
 }
 
+// Time per step of the launches that run() would issue with the current tile: on-chip launches
+// of ring_len steps and their folds where the raster takes those, else time_kernel's.  The
+// launches take the same steps from the current state each time and none is committed, so the
+// state is untouched afterwards; if one was given up, single launches are timed.
+static int time_run(hexsv_sim *s, int nlaunch, double *ms_step, hipStream_t st) {
+    ResPlan plan;
+    if (!resident_plan(s, &plan)) return hexsv_sim_time_kernel(s, nlaunch, ms_step, st);
+    int rc = ensure_ring(s);
+    if (rc == HEXSV_OK) rc = ensure_resident(s, plan, st);
+    if (rc == HEXSV_ENOMEM) return hexsv_sim_time_kernel(s, nlaunch, ms_step, st);
+    if (rc) return rc;
+    HIP_TRY(hipMemcpyAsync(s->h_ctl, s->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    Ctl &c = *s->h_ctl;
+    const Ctl c0 = c;
+    c.t_end = INFINITY;
+    c.step_limit = c.steps + s->ring_len;
+    HIP_TRY(hipMemcpyAsync(s->d_ctl, s->h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, st));
+    if (!s->ev0) {
+        HIP_TRY(hipEventCreate(&s->ev0));
+        HIP_TRY(hipEventCreate(&s->ev1));
+    }
+    const int reps = (nlaunch + s->ring_len - 1) / s->ring_len;
+    HIP_TRY(hipEventRecord(s->ev0, st));
+    for (int k = 0; k < reps; ++k) HIP_TRY(resident_issue(s, plan, 0, false, false, st));
+    HIP_TRY(hipEventRecord(s->ev1, st));
+    // the launches' proposed control block and marks: did every workgroup reach the end?
+    std::vector<uint32_t> done(plan.nwg);
+    HIP_TRY(hipMemcpyAsync(done.data(), s->res.done, sizeof(uint32_t) * plan.nwg,
+                           hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(s->h_ctl, s->d_ctl + 1, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    const int steps = c.open;
+    const uint32_t last = s->res_tag - (uint32_t)s->ring_len - 1;
+    bool all = steps == s->ring_len;
+    for (uint32_t d : done) all = all && d == last;
+    float ms = 0.f;
+    HIP_TRY(hipEventElapsedTime(&ms, s->ev0, s->ev1));
+    c = c0;
+    HIP_TRY(hipMemcpyAsync(s->d_ctl, s->h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (!all) return hexsv_sim_time_kernel(s, nlaunch, ms_step, st);
+    *ms_step = ms / ((double)reps * steps);
+    return HEXSV_OK;
+}
+
 static int set_tile(hexsv_sim *s, int v) {
     s->tile = v;
     tile_grid(v, s->grid->kg.nq, s->grid->kg.nr, &s->ntq, &s->ntiles);
@@ -987,8 +1040,8 @@ extern "C" int hexsv_sim_autotune(hexsv_sim *s, int32_t nlaunch, const char *cac
     for (int v = 0; v < NUM_TILES; ++v) {
         set_tile(s, v);
         double ms = 0.0;
-        int rc = hexsv_sim_time_kernel(s, 2, &ms, stream);  // warm-up
-        if (rc == HEXSV_OK) rc = hexsv_sim_time_kernel(s, nlaunch, &ms, stream);
+        int rc = time_run(s, 2, &ms, stream);  // warm-up
+        if (rc == HEXSV_OK) rc = time_run(s, nlaunch, &ms, stream);
         if (rc != HEXSV_OK) return rc;
         times[v] = ms;
         if (ms < bms) {

@@ -208,6 +208,11 @@ static hipError_t ens_ensure_resident(hexsv_ensemble *e, hipStream_t st, bool *o
     return hipSuccess;
 }
 
+// Do batched steps go on chip with the tile in use?
+static bool ens_on_chip(const hexsv_ensemble *e) {
+    return e->res_on && e->res_sub > 0 && resident_fits(e->esz, e->btile, e->res_sub, e->visc != 0);
+}
+
 // One resident launch and its commit.  *after: the tag of the launch queued right before it
 // (0: none), then its own.
 template <typename T>
@@ -586,9 +591,7 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
     HIP_TRY(hipMemcpyAsync(e->d_ctl, e->h_ctl, sizeof(Ctl) * e->n, hipMemcpyHostToDevice, stream));
     // an ensemble that fits on the chip steps in resident launches; after one that a scenario
     // gave up (see k_resident), the rest of the run and some of the next runs are single ones
-    bool resident = e->res_on && e->mode == HEXSV_ENS_BATCHED && e->res_sub > 0 &&
-                    resident_fits(e->esz, e->btile, e->res_sub, e->visc != 0) &&
-                    !e->res_wait.skip();
+    bool resident = e->mode == HEXSV_ENS_BATCHED && ens_on_chip(e) && !e->res_wait.skip();
     bool prepared = false, gave_up = false;
     int64_t launched = 0;  // batched launches since the parities were set
     for (;;) {
@@ -787,11 +790,39 @@ extern "C" int hexsv_ensemble_autotune(hexsv_ensemble *e, int32_t ksteps, const 
         if (he == hipSuccess) he = hipEventSynchronize(b);
         float ms = 0.f;
         if (he == hipSuccess) he = hipEventElapsedTime(&ms, a, b);
+        if (he == hipSuccess) he = hipMemcpyAsync(e->buf, save, sbytes, hipMemcpyDeviceToDevice, stream);
+        // run() steps on chip with this tile: a launch's full number of steps, scaled to
+        // ksteps, if every scenario took them
+        bool on_chip = he == hipSuccess && mode == HEXSV_ENS_BATCHED && ens_on_chip(e);
+        if (on_chip) he = ens_ensure_resident(e, stream, &on_chip);
+        if (on_chip && he == hipSuccess) {
+            const int64_t launches = e->res_launches;  // these are not a run's
+            for (int take : {0, ENS_RES_STEPS}) {      // a first one loads the code
+                for (auto &x : cc) x.step_limit = x.steps + take;
+                uint32_t after = 0;
+                if (he == hipSuccess) he = hipMemcpyAsync(e->d_ctl, cc.data(), sizeof(Ctl) * e->n, hipMemcpyHostToDevice, stream);
+                if (he == hipSuccess) he = hipEventRecord(a, stream);
+                if (he == hipSuccess)
+                    he = e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, &after, stream)
+                                               : ens_resident_launch<float>(e, &after, stream);
+                if (he == hipSuccess) he = hipEventRecord(b, stream);
+                if (he == hipSuccess) he = hipStreamSynchronize(stream);
+            }
+            e->res_launches = launches;
+            if (he == hipSuccess)
+                he = hipMemcpyAsync(cc.data(), e->d_ctl, sizeof(Ctl) * e->n, hipMemcpyDeviceToHost, stream);
+            if (he == hipSuccess) he = hipStreamSynchronize(stream);
+            bool all = true;
+            for (int s = 0; s < e->n; ++s) all = all && cc[s].steps == c0[s].steps + ENS_RES_STEPS;
+            float msr = 0.f;
+            if (he == hipSuccess) he = hipEventElapsedTime(&msr, a, b);
+            if (all) ms = msr * (float)ksteps / ENS_RES_STEPS;
+            if (he == hipSuccess) he = hipMemcpyAsync(e->buf, save, sbytes, hipMemcpyDeviceToDevice, stream);
+        }
         if (he == hipSuccess) {
             times[c] = ms;
             if (ms < bms) { bms = ms; best = c; }
         }
-        if (he == hipSuccess) he = hipMemcpyAsync(e->buf, save, sbytes, hipMemcpyDeviceToDevice, stream);
     }
     if (he == hipSuccess) he = hipMemcpyAsync(e->d_ctl, c0.data(), sizeof(Ctl) * e->n, hipMemcpyHostToDevice, stream);
     if (he == hipSuccess) he = hipStreamSynchronize(stream);
@@ -799,9 +830,9 @@ extern "C" int hexsv_ensemble_autotune(hexsv_ensemble *e, int32_t ksteps, const 
     if (b) (void)hipEventDestroy(b);
     (void)hipFree(save);
     if (he != hipSuccess) return fail(HEXSV_EHIP, "ensemble_autotune: %s", hipGetErrorString(he));
-    // the default (batched steps, DEFAULT_TILE) unless a variant beats it by more than 3 %:
-    // trial launches of a few steps differ by about that much from run to run
-    const int def = NUM_ENS_TILES + DEFAULT_TILE;
+    // the default (batched steps, the tile of an untuned ensemble) unless a variant beats it by
+    // more than 3 %: trial launches of a few steps differ by about that much from run to run
+    const int def = NUM_ENS_TILES + ens_default_btile(e);
     if (best >= 0 && times[def] <= 1.03 * bms) {
         best = def;
         bms = times[def];
