@@ -137,8 +137,11 @@ constexpr int RES_NT = 256 * SUB / RES_PER<T, SUB>;
 //
 // The edge sums of a step do not depend on its dt, so they are formed as soon as the
 // neighbours' rim cells are there, while the wave speeds that dt needs are on their way.
+//
+// Inlined by force: where both kernels below have the instance, the viscous FP32 64 x 16 tile
+// became a function of its own, with its arguments and arrays in scratch memory.
 template <typename T, int VAR, int SUB, bool VISC, bool EXT>
-__device__ inline void resident_steps(const KDom<T> &dd, const KGrid &g, const KConst &kc,
+__device__ __attribute__((always_inline)) inline void resident_steps(const KDom<T> &dd, const KGrid &g, const KConst &kc,
                                       const KRain &rn, const Ctl *in, Ctl *out, Part *ring,
                                       const ResSync &rs, const ResGroup &grp, int max_steps,
                                       uint32_t tag0, int roll_polls) {

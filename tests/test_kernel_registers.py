@@ -54,3 +54,9 @@ def test_plain_fp64_steps_keep_their_waves(kernels, kernel, tile, vgprs):
 def test_persistent_fp64_ensemble_spills_little(kernels, tile, scratch):
     """1024 threads leave 128 registers; 200 to 436 bytes of scratch a lane cost up to 46 %."""
     assert kernels[f"k_ensemble<double, {tile}>"]["scratch"] <= scratch
+
+
+@pytest.mark.parametrize("kernel", ["k_resident", "k_ens_resident"])
+def test_viscous_fp32_on_chip_tile_is_inlined(kernels, kernel):
+    """As a function of its own the step took its arguments and arrays through scratch memory."""
+    assert kernels[f"{kernel}<float, 2, 1, true, true>"]["scratch"] == 0
