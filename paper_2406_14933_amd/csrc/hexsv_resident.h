@@ -314,7 +314,7 @@ __device__ __attribute__((always_inline)) inline void resident_steps(const KDom<
         for (int i = 1; i < NW; ++i) c = fmax[i] > c ? fmax[i] : c;
         return c;
     };
-    TileCells<T, TQ, TR, NT, VISC, EXT, SUB> cells(L, R, dd, g, kc, tq, tr);
+    TileCells<T, TQ, TR, NT, VISC, EXT, SUB, true> cells(L, R, dd, g, kc, tq, tr);
     cells.G = uniform(cells.G);
     cells.l = uniform(cells.l);
     cells.half_l = uniform(cells.half_l);

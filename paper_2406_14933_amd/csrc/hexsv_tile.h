@@ -324,8 +324,13 @@ struct Partial32 {
     float cmax = 0.f, m = 0.f, any = 0.f;
 };
 
-// The step of thread tid's cells of the tile staged in L: edges, then finish.
-template <typename T, int TQ, int TR, int NT, bool V, bool EXT, int SUB>
+// The step of thread tid's cells of the tile staged in L: edges, then finish.  SHORT: FP64
+// leaves the products by 0 and 1 of edges 0 and 3 out (same results).  That is less arithmetic,
+// which the on-chip kernels (1024 x 1024: 2582 -> 2541 us per 100 steps) and the viscous steps
+// gain from; in the launches of one step it costs registers: the plain 64 x 16 step takes 131,
+// three waves per SIMD, against 121 and four, and the persistent ensemble kernel spills 61
+// against 27 (256 rasters of 128 x 128: 181 against 119 us a step).
+template <typename T, int TQ, int TR, int NT, bool V, bool EXT, int SUB, bool SHORT>
 struct TileCells {
     using Regs = TileRegs<T, TQ, TR, NT, SUB>;
     static constexpr int W = TQ + 2;
@@ -452,15 +457,17 @@ struct TileCells {
                 if (GEN && (EXT ? cd != CODE_INTERIOR : cd == CODE_OUTFLOW))
                     Fout = __builtin_fmaf(msel, vn, Fout);  // outflow or Dirichlet edge
             } else {
-                // one selected mass, as above: at vn = 0 the flux vanishes whatever it is.
-                // Without viscosity the products by 0 and 1 of edges 0 and 3 stay: the plain
-                // 64 x 16 step then takes 121 registers, four waves per SIMD, against 131, and
-                // the persistent ensemble kernel spills 27 instead of 61 (256 rasters of
-                // 128 x 128: 181 -> 119 us a step); the viscous one is better off without
-                const bool flat = V && (e == 0 || e == 3);
+                const bool flat = SHORT && (e == 0 || e == 3);
                 const T vn = flat ? (e == 0 ? vb1 : -vb1) : vb1 * NX[e] + vb2 * NY[e];
-                const T key = vn != T(0) ? vn : wi - wj;
-                const T msel = key > T(0) ? mi : mj;
+                // one selected mass, as above: at vn = 0 the flux vanishes whatever it is
+                bool own;
+                if constexpr (SHORT) {
+                    own = vn > T(0) || (vn == T(0) && wi > wj);
+                } else {
+                    const T key = vn != T(0) ? vn : wi - wj;
+                    own = key > T(0);
+                }
+                const T msel = own ? mi : mj;
                 const T F = l * msel * vn;
                 Ls -= F;
                 A1 -= F * vb1;
@@ -800,7 +807,7 @@ __device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRe
     using Regs = TileRegs<T, TQ, TR, NT>;
     StoreSink<T, NT_STORE> sink{d.buf(par ^ 1, 0), d.buf(par ^ 1, 1), d.buf(par ^ 1, 2), err_flag,
                                 err_cell};
-    const TileCells<T, TQ, TR, NT, V, EXT, 1> cells(L, R, d, g, kc, tq, tr);
+    const TileCells<T, TQ, TR, NT, V, EXT, 1, V> cells(L, R, d, g, kc, tq, tr);
     const StepConst<T> sc = step_const<T>(kc, dt, r_next);
     Partial32 p32;
     const int tid = threadIdx.x;
