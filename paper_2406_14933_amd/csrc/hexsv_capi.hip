@@ -726,41 +726,40 @@ static int ensure_resident(hexsv_sim *s, const ResPlan &p, hipStream_t st) {
     s->res.halo = (unsigned long long *)s->d_res;
     s->res.flags = (unsigned long long *)(s->d_res + halo);
     s->res.abort_word = (uint32_t *)(s->d_res + halo + flags);
-    s->res.committed = s->res.abort_word + 32;
     s->res.done = s->res.abort_word + 64;
     s->res.flag_cap = p.nwg;
     s->res_tag = 1;
     return HEXSV_OK;
 }
 
-// A resident launch of up to ring_len steps and its fold, which commits them only if `commit`
-// (no workgroup ever marks tag0 + 1).  prev: the tag of the launch queued right before it.
-static hipError_t resident_issue(hexsv_sim *s, const ResPlan &p, uint32_t prev, bool drop,
-                                 bool commit, hipStream_t st) {
+// A resident launch of up to ring_len steps and its fold, which commits them (trial: does not).
+// drop: it is to be given up: a workgroup is missing, or all of it.
+static hipError_t resident_issue(hexsv_sim *s, const ResPlan &p, bool drop, bool trial,
+                                 hipStream_t st) {
     const KClose cl = close_of(s);
     const uint32_t tag0 = s->res_tag;
     s->res_tag += (uint32_t)s->ring_len + 1;
-    hipError_t e =
-        s->prec == HEXSV_FP64
-            ? launch_resident<double>(s->tile, p.sub, dom_of<double>(s), s->grid->kg, s->kc, s->rn,
-                                      s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles, s->ring_len,
-                                      tag0, prev, drop, st)
-            : launch_resident<float>(s->tile, p.sub, dom_of<float>(s), s->grid->kg, s->kc, s->rn,
-                                     s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles, s->ring_len,
-                                     tag0, prev, drop, st);
+    const int grid = drop ? p.nwg - 1 : p.nwg;
+    hipError_t e = hipSuccess;
+    if (grid > 0)
+        e = s->prec == HEXSV_FP64
+                ? launch_resident<double>(s->tile, p.sub, dom_of<double>(s), s->grid->kg, s->kc,
+                                          s->rn, s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles,
+                                          s->ring_len, tag0, grid, st)
+                : launch_resident<float>(s->tile, p.sub, dom_of<float>(s), s->grid->kg, s->kc,
+                                         s->rn, s->d_ctl, cl, s->res, p.ntq, p.nwg, s->ntiles,
+                                         s->ring_len, tag0, grid, st);
     if (e != hipSuccess) return e;
     return launch_fold_resident(s->d_ctl, cl, s->ntiles, s->kc, s->rn, s->ring_len, s->res, p.nwg,
-                                commit ? tag0 : tag0 + 1, st);
+                                trial ? 0 : tag0, st);
 }
 
-// One of a run's.  *after: the tag of the launch queued right before it (0: none), then its own.
-static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, uint32_t *after, hipStream_t st) {
-    const uint32_t prev = *after;
+// One of a run's.
+static hipError_t resident_launch(hexsv_sim *s, const ResPlan &p, hipStream_t st) {
     const bool drop = s->res_drop == 0;
     if (s->res_drop >= 0) s->res_drop -= 1;
-    *after = s->res_tag;
     s->res_launches += 1;
-    return resident_issue(s, p, prev, drop, true, st);
+    return resident_issue(s, p, drop, false, st);
 }
 
 // Steps a run to t_end is expected to take from here: at the current dt bound, or up to the
@@ -845,11 +844,10 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         // live step the graph's hint is right while the steps before it were live (the
         // short graphs go longest first, so the odd ones come last)
         int64_t launched = 0;
-        uint32_t after = 0;
         for (int k = 0; k < reps; ++k) {
             const int p = (int)((c.parity + launched) & 1);
             if (resident) {
-                HIP_TRY(resident_launch(s, plan_r, &after, stream));
+                HIP_TRY(resident_launch(s, plan_r, stream));
             } else if (use_short) {
                 HIP_TRY(hipGraphLaunch(s->sexec[plan[k]][p], stream));
                 launched += SHORT_LEN[plan[k]];
@@ -871,10 +869,14 @@ static int sim_run(hexsv_sim *s, double t_end, int64_t max_steps, bool shortg, b
         if (c.err)
             return fail(HEXSV_ENUMERIC, "run: non-finite value at cell %d in step %lld (t=%g)",
                         c.err_cell, (long long)c.steps + 1, c.t);
-        if (resident && (c.t >= t_end || c.steps >= limit)) s->res_wait.clear();
-        if (c.t >= t_end || c.steps >= limit) break;
-        if (resident && c.steps - before < (int64_t)reps * s->ring_len) {
-            resident = false;  // a committed launch short of the run's end takes ring_len steps
+        // (a committed launch short of the run's end takes ring_len steps)
+        const bool dropped = resident && c.steps - before < (int64_t)reps * s->ring_len;
+        if (c.t >= t_end || c.steps >= limit) {
+            if (resident) s->res_wait.clear();
+            break;
+        }
+        if (dropped) {
+            resident = false;
             gave_up = c.steps;
             continue;
         }
@@ -1000,7 +1002,7 @@ static int time_run(hexsv_sim *s, int nlaunch, double *ms_step, hipStream_t st) 
     }
     const int reps = (nlaunch + s->ring_len - 1) / s->ring_len;
     HIP_TRY(hipEventRecord(s->ev0, st));
-    for (int k = 0; k < reps; ++k) HIP_TRY(resident_issue(s, plan, 0, false, false, st));
+    for (int k = 0; k < reps; ++k) HIP_TRY(resident_issue(s, plan, false, true, st));
     HIP_TRY(hipEventRecord(s->ev1, st));
     // the launches' proposed control block and marks: did every workgroup reach the end?
     std::vector<uint32_t> done(plan.nwg);

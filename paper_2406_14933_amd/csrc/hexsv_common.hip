@@ -49,15 +49,19 @@ __global__ __launch_bounds__(1024) void k_fold_slots(const Ctl *ctl, KClose cl, 
 // The pending step of slot `in` closed into ctl[0], the slots' books added in
 // step order, the ring emptied and every accumulator cleared.  One wave.  done: the
 // marks of a resident launch; unless all nwg of them hold tag0, nothing is committed
-// (else *committed becomes tag0).
+// and the abort word becomes next, the next launch's tag (for tag0 = 0 not even that).
 __global__ __launch_bounds__(64) void k_fold_close(Ctl *ctl, KClose cl, KConst kc, KRain rn,
                                                    int in, int set, const uint32_t *done, int nwg,
-                                                   uint32_t tag0, uint32_t *committed) {
+                                                   uint32_t tag0, uint32_t *abort_word,
+                                                   uint32_t next) {
     if (done) {
+        if (tag0 == 0) return;
         bool all = true;
         for (int i = threadIdx.x; i < nwg; i += 64) all = all && done[i] == tag0;
-        if (!__all(all)) return;
-        if (threadIdx.x == 0) *committed = tag0;
+        if (!__all(all)) {
+            if (threadIdx.x == 0) *abort_word = next;
+            return;
+        }
     }
     const OpenStep o = open_step(ctl, in, cl.acc + set * ACC_SET_WORDS, kc);
     // the slots' totals come in with one load per lane (one thread reading them one behind
@@ -103,7 +107,7 @@ hipError_t launch_fold(Ctl *ctl, const KClose &cl, int ntiles, const KConst &kc,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fold_close, dim3(1), dim3(64), 0, stream, ctl, cl, kc, rn, in, set,
-                       nullptr, 0, 0u, nullptr);
+                       nullptr, 0, 0u, nullptr, 0u);
     return hipGetLastError();
 }
 
@@ -114,7 +118,7 @@ hipError_t launch_fold_resident(Ctl *ctl, const KClose &cl, int ntiles, const KC
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fold_close, dim3(1), dim3(64), 0, stream, ctl, cl, kc, rn, 1, 0, rs.done,
-                       nwg, tag0, rs.committed);
+                       nwg, tag0, rs.abort_word, tag0 + (uint32_t)slots + 1);
     return hipGetLastError();
 }
 
@@ -263,21 +267,24 @@ hipError_t launch_ens_finalize(const EnsScen *scen, Ctl *ctl, const Part *part, 
 }
 
 // Commit of an ensemble's resident launch, one workgroup per scenario: nothing unless all
-// workgroups of its group (groups[s]: first, count) reached the end, else (committed[s] holds
-// tag0 and) the proposed control block with the steps' water books added in order.  A wave sums a step's records in
+// workgroups of its group (groups[s]: first, count) reached the end (but the abort word is set
+// for the next launch, tag `next`), else the proposed control block with the steps' water books
+// added in order.  A wave sums a step's records in
 // reduce_parts' order (64 consecutive records at a time, the totals in turn; a scenario has
 // at most 1024, one per thread there).
 constexpr int ENS_FOLD_STEPS = 128;
 __global__ __launch_bounds__(256) void k_ens_fold(const EnsScen *scen, Ctl *ctl, const Ctl *out,
                                                   const Part *ring, const uint32_t *done,
-                                                  uint32_t *committed, const int2 *groups,
-                                                  int btotal, uint32_t tag0) {
+                                                  const int2 *groups, int btotal, uint32_t tag0,
+                                                  uint32_t *abort_word, uint32_t next) {
     const int s = blockIdx.x;
     const int2 grp = groups[s];
     bool all = true;
     for (int i = threadIdx.x; i < grp.y; i += 256) all = all && done[grp.x + i] == tag0;
-    if (!__syncthreads_and(all)) return;
-    if (threadIdx.x == 0) committed[s] = tag0;
+    if (!__syncthreads_and(all)) {
+        if (threadIdx.x == 0) abort_word[s] = next;
+        return;
+    }
     const Ctl o = out[s];
     const int n = o.open < ENS_FOLD_STEPS ? o.open : ENS_FOLD_STEPS;
     if (n <= 0) return;
@@ -316,9 +323,9 @@ __global__ __launch_bounds__(256) void k_ens_fold(const EnsScen *scen, Ctl *ctl,
 
 hipError_t launch_ens_fold(const EnsScen *scen, Ctl *ctl, const Ctl *out, const Part *ring,
                            const ResSync &rs, const int2 *groups, int nscen, int btotal,
-                           uint32_t tag0, hipStream_t stream) {
+                           uint32_t tag0, uint32_t next, hipStream_t stream) {
     hipLaunchKernelGGL(k_ens_fold, dim3(nscen), dim3(256), 0, stream, scen, ctl, out, ring, rs.done,
-                       rs.committed, groups, btotal, tag0);
+                       groups, btotal, tag0, rs.abort_word, next);
     return hipGetLastError();
 }
 

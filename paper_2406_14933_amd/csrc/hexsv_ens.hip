@@ -165,7 +165,7 @@ static hipError_t ens_ensure_resident(hexsv_ensemble *e, hipStream_t st, bool *o
     const size_t halo = sizeof(unsigned long long) * e->res_nwg *
                         resident_halo_words(e->esz, e->btile, e->res_sub);
     const size_t flags = sizeof(unsigned long long) * 2 * (e->esz / 4) * e->res_nwg;
-    const size_t bytes = halo + flags + sizeof(uint32_t) * (2 * (size_t)e->n + e->res_nwg);
+    const size_t bytes = halo + flags + sizeof(uint32_t) * ((size_t)e->n + e->res_nwg);
     if (e->d_res && e->res_tag > 0xffff0000u) {  // tags start over on clean words
         const hipError_t err = hipMemsetAsync(e->d_res, 0, bytes, st);
         if (err != hipSuccess) return err;
@@ -201,8 +201,7 @@ static hipError_t ens_ensure_resident(hexsv_ensemble *e, hipStream_t st, bool *o
     e->res.halo = (unsigned long long *)e->d_res;
     e->res.flags = (unsigned long long *)(e->d_res + halo);
     e->res.abort_word = (uint32_t *)(e->d_res + halo + flags);
-    e->res.committed = e->res.abort_word + e->n;
-    e->res.done = e->res.committed + e->n;
+    e->res.done = e->res.abort_word + e->n;
     e->res.flag_cap = e->res_nwg;
     e->res_tag = 1;
     return hipSuccess;
@@ -213,23 +212,28 @@ static bool ens_on_chip(const hexsv_ensemble *e) {
     return e->res_on && e->res_sub > 0 && resident_fits(e->esz, e->btile, e->res_sub, e->visc != 0);
 }
 
-// One resident launch and its commit.  *after: the tag of the launch queued right before it
-// (0: none), then its own.
+// One resident launch and its commit.
 template <typename T>
-static hipError_t ens_resident_launch(hexsv_ensemble *e, uint32_t *after, hipStream_t st) {
-    const uint32_t tag0 = e->res_tag, prev = *after;
-    const int drop = e->res_drop == 0 ? e->res_drop_s : -1;
+static hipError_t ens_resident_launch(hexsv_ensemble *e, hipStream_t st) {
+    const uint32_t tag0 = e->res_tag;
+    const bool drop = e->res_drop == 0;
     if (e->res_drop >= 0) e->res_drop -= 1;
-    *after = tag0;
     e->res_tag += ENS_RES_STEPS + 1;
     e->res_launches += 1;
     hipError_t err = launch_ens_resident<T>(e->btile, e->res_sub, e->visc != 0, e->bc != 0,
                                             ens_base<T>(e), e->d_scen, e->d_wgs, e->d_ctl, e->d_out,
                                             e->d_ring, e->res, e->res_nwg, e->btotal, ENS_RES_STEPS,
-                                            tag0, prev, drop, st);
+                                            tag0, st);
+    if (err == hipSuccess && drop) {  // as if the scenario's first workgroup had left early
+        int first = 0;
+        const int tr = TILES[e->btile].tr * e->res_sub;
+        for (int s = 0; s < e->res_drop_s; ++s)
+            first += e->scen[s].bntq * ((e->scen[s].g.nr + tr - 1) / tr);
+        err = hipMemsetAsync(e->res.done + first, 0, sizeof(uint32_t), st);
+    }
     if (err != hipSuccess) return err;
     return launch_ens_fold(e->d_scen, e->d_ctl, e->d_out, e->d_ring, e->res, e->d_groups, e->n,
-                           e->btotal, tag0, st);
+                           e->btotal, tag0, e->res_tag, st);
 }
 
 static void ens_set_tile(hexsv_ensemble *e, int v) {
@@ -621,10 +625,9 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
         }
         if (e->timing) HIP_TRY(hipEventRecord(e->ev0, stream));
         if (resident) {
-            uint32_t after = 0;
             for (int k = 0; k < reps; ++k)
-                HIP_TRY(e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, &after, stream)
-                                              : ens_resident_launch<float>(e, &after, stream));
+                HIP_TRY(e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, stream)
+                                              : ens_resident_launch<float>(e, stream));
         } else {
             HIP_TRY(hipGraphLaunch(e->gexec[launched & 1], stream));
             launched += e->ksteps;
@@ -638,18 +641,18 @@ extern "C" int hexsv_ensemble_run(hexsv_ensemble *e, const double *t_end, int64_
             e->timed_ms += ms;
             e->timed_launches += reps;
         }
-        bool all = true, stuck = false;
+        bool all = true, dropped = false;
         for (int s = 0; s < e->n; ++s) {
             if (e->h_ctl[s].err)
                 return fail(HEXSV_ENUMERIC, "ensemble_run: non-finite value in scenario %d at cell %d",
                             s, e->h_ctl[s].err_cell);
             all = all && ens_done(e->h_ctl[s]);
-            // a committed launch short of a scenario's end takes ENS_RES_STEPS steps
-            stuck = stuck || (resident && !ens_done(e->h_ctl[s]) &&
-                              e->h_ctl[s].steps - before[s] < (int64_t)reps * ENS_RES_STEPS);
+            // (a committed launch short of a scenario's end takes ENS_RES_STEPS steps)
+            dropped = dropped || (resident && !ens_done(e->h_ctl[s]) &&
+                                  e->h_ctl[s].steps - before[s] < (int64_t)reps * ENS_RES_STEPS);
         }
         if (all) break;
-        if (stuck) {
+        if (dropped) {
             resident = false;
             gave_up = true;
         }
@@ -799,12 +802,11 @@ extern "C" int hexsv_ensemble_autotune(hexsv_ensemble *e, int32_t ksteps, const 
             const int64_t launches = e->res_launches;  // these are not a run's
             for (int take : {0, ENS_RES_STEPS}) {      // a first one loads the code
                 for (auto &x : cc) x.step_limit = x.steps + take;
-                uint32_t after = 0;
                 if (he == hipSuccess) he = hipMemcpyAsync(e->d_ctl, cc.data(), sizeof(Ctl) * e->n, hipMemcpyHostToDevice, stream);
                 if (he == hipSuccess) he = hipEventRecord(a, stream);
                 if (he == hipSuccess)
-                    he = e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, &after, stream)
-                                               : ens_resident_launch<float>(e, &after, stream);
+                    he = e->prec == HEXSV_FP64 ? ens_resident_launch<double>(e, stream)
+                                               : ens_resident_launch<float>(e, stream);
                 if (he == hipSuccess) he = hipEventRecord(b, stream);
                 if (he == hipSuccess) he = hipStreamSynchronize(stream);
             }

@@ -86,11 +86,10 @@ hipError_t launch_step(int variant, const KDom<T> &d, const KGrid &g, const KCon
 
 // Exchange memory of the resident steps (k_resident): halo words of every tile and
 // wave-speed words of every workgroup (both twice, by the tag's parity), the word
-// that gives a launch up, each workgroup's mark that it reached the end, and the tag of
-// the last launch whose steps were committed (an ensemble: one of the two words per scenario).
+// that gives a launch up, and each workgroup's mark that it reached the end.
 struct ResSync {
     unsigned long long *halo, *flags;
-    uint32_t *abort_word, *done, *committed;
+    uint32_t *abort_word, *done;
     int flag_cap;  // workgroups the flags and marks are sized for
 };
 // The workgroups of a resident launch that advance one domain together: the first one's
@@ -153,28 +152,28 @@ inline size_t resident_halo_words(size_t esz, int variant, int sub) {
     return (size_t)2 * 3 * (esz / 4) * 2 * (TILES[variant].tq + TILES[variant].tr * sub);
 }
 // Up to max_steps steps in one launch of nwg workgroups, each a stack of `sub` tiles of
-// `variant` (0, 1 or 2); the launch_fold_resident that follows commits them.  after: the tag
-// of the launch queued right before this one, without whose commit it does nothing (0: there
-// is none).  drop: the launch is to give up at its roll call.
+// `variant` (0, 1 or 2); the launch_fold_resident that follows commits them.  grid: nwg, or one
+// fewer, which leaves the others to wait for the missing one in vain (a test's launch).
 template <typename T>
 hipError_t launch_resident(int variant, int sub, const KDom<T> &d, const KGrid &g,
                            const KConst &kc, const KRain &rn, Ctl *ctl, const KClose &cl,
                            const ResSync &rs, int ntq, int nwg, int ntiles, int max_steps,
-                           uint32_t tag0, uint32_t after, bool drop, hipStream_t stream);
+                           uint32_t tag0, int grid, hipStream_t stream);
 // The same for the scenarios of an ensemble, side by side: nwg workgroups (`wgs`, grouped by
 // scenario), control blocks in `ctl` and proposed ones in `out`, btotal records per ring slot;
 // variant 0 with any sub, or variant 2 with one.  launch_ens_fold commits the scenarios all of
-// whose workgroups reached the end.  drop: the scenario that is to give up (-1: none).
+// whose workgroups reached the end.
 template <typename T>
 hipError_t launch_ens_resident(int variant, int sub, bool visc, bool bc, const KDom<T> &base,
                                const EnsScen *scen, const ResEnsWg *wgs, const Ctl *ctl, Ctl *out,
                                Part *ring, const ResSync &rs, int nwg, int btotal, int max_steps,
-                               uint32_t tag0, uint32_t after, int drop, hipStream_t stream);
+                               uint32_t tag0, hipStream_t stream);
 hipError_t launch_ens_fold(const EnsScen *scen, Ctl *ctl, const Ctl *out, const Part *ring,
                            const ResSync &rs, const int2 *groups, int nscen, int btotal,
-                           uint32_t tag0, hipStream_t stream);
+                           uint32_t tag0, uint32_t next, hipStream_t stream);
 // Commit the resident launch of tag0 (control slot 1, up to `slots` steps in the ring)
-// if all nwg workgroups reached its end; otherwise change nothing.
+// if all nwg workgroups reached its end; otherwise only set the abort word of the next launch
+// (whose tag0 is `slots` + 1 on).  tag0 = 0: neither (a timed trial).
 hipError_t launch_fold_resident(Ctl *ctl, const KClose &cl, int ntiles, const KConst &kc,
                                 const KRain &rn, int slots, const ResSync &rs, int nwg,
                                 uint32_t tag0, hipStream_t stream);

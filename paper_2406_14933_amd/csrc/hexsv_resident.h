@@ -20,8 +20,9 @@
 // finds a non-finite value, or a wave speed that overflows) marks the launch as given up and
 // leaves, and so do all others.  The launch's start state is never written: the result goes
 // to the other buffer, and the fold that follows commits it only if every workgroup has
-// reached the end.  Launches queued behind one that was not committed leave at once (they
-// would only wait again).  The host then repeats the steps with one launch each, which also
+// reached the end.  Otherwise it sets the abort word of the launch queued behind this one, whose
+// roll call then fails at the first look at that word (256 polls) if it has to wait again; a test
+// of a flag at the kernel's start cost 1 to 3 % of a small raster's step.  The host then repeats the steps with one launch each, which also
 // names a non-finite cell.  Every wait is bounded.
 //
 // The arithmetic, the tiles whose books are recorded and the threads that sum them are those
@@ -119,7 +120,7 @@ struct KeepSink {
 
 // Polls before a wait is given up (a poll takes about a microsecond): the roll call, which
 // other kernels on the device can delay, and a step's exchange, which nothing can once
-// everybody has answered.  (A roll call of no polls gives up for certain: a test's launch.)
+// everybody has answered.
 constexpr int RES_ROLL_POLLS = 1 << 12;
 constexpr int RES_STEP_POLLS = 1 << 20;
 
@@ -144,7 +145,7 @@ template <typename T, int VAR, int SUB, bool VISC, bool EXT>
 __device__ __attribute__((always_inline)) inline void resident_steps(const KDom<T> &dd, const KGrid &g, const KConst &kc,
                                       const KRain &rn, const Ctl *in, Ctl *out, Part *ring,
                                       const ResSync &rs, const ResGroup &grp, int max_steps,
-                                      uint32_t tag0, int roll_polls) {
+                                      uint32_t tag0) {
     // FP64 time and books: rounded as written in every translation unit (the cells' own
     // arithmetic is in TileCells, under the unit's setting)
 #pragma clang fp contract(off)
@@ -278,7 +279,6 @@ __device__ __attribute__((always_inline)) inline void resident_steps(const KDom<
     auto wait_speeds = [&](uint32_t tag, int limit) -> T {
         T c = T(0);
         polls = 0;
-        ok = ok && limit > 0;
         for (int f = flag0; f < nwg; f += NT) {
             const unsigned long long *p = rs.flags + (tag & 1) * fstride + grp.first + f;
             uint32_t b[W];
@@ -374,7 +374,7 @@ __device__ __attribute__((always_inline)) inline void resident_steps(const KDom<
     }
     edges(tid);
     ask_speeds(tag0);
-    if (!__builtin_isfinite(wait_speeds(tag0, roll_polls))) return;
+    if (!__builtin_isfinite(wait_speeds(tag0, RES_ROLL_POLLS))) return;
 
     // time and CFL bound, the same in every workgroup; the rain book and the time steps'
     // range are kept by the first one
@@ -533,8 +533,7 @@ __device__ __attribute__((always_inline)) inline void resident_steps(const KDom<
 template <typename T, int VAR, int SUB, bool VISC, bool EXT>
 __global__ __launch_bounds__((RES_NT<T, SUB>)) void k_resident(
     KDom<T> d, KGrid g, KConst kc, KRain rn, Ctl *ctl, KClose cl, ResSync rs, int ntq, int nwg,
-    int ntiles, int max_steps, uint32_t tag0, uint32_t after, int roll_polls) {
-    if (after && *rs.committed != after) return;  // the launch before this one was given up
+    int ntiles, int max_steps, uint32_t tag0) {
     const int par = ctl->parity;
     KDom<T> dd = d;
     if (par)
@@ -544,39 +543,34 @@ __global__ __launch_bounds__((RES_NT<T, SUB>)) void k_resident(
         }
     const ResGroup grp{0, nwg, xcd_tile(blockIdx.x, gridDim.x, nwg, 0), ntq, ntiles, rs.abort_word};
     resident_steps<T, VAR, SUB, VISC, EXT>(dd, g, kc, rn, ctl, ctl + 1, cl.ring, rs, grp, max_steps,
-                                           tag0, roll_polls);
+                                           tag0);
 }
 
 // The resident steps of an ensemble: the workgroups of a scenario are a group of their own,
 // which meets only its own members, so scenarios advance side by side at their own pace.
-// drop: the scenario whose roll call is to fail (a test's; -1: none).
 template <typename T, int VAR, int SUB, bool VISC, bool EXT>
 __global__ __launch_bounds__((RES_NT<T, SUB>)) void k_ens_resident(
     KDom<T> base, const EnsScen *__restrict__ scen, const ResEnsWg *__restrict__ wgs,
     const Ctl *__restrict__ ctl, Ctl *out, Part *ring, ResSync rs, int btotal, int max_steps,
-    uint32_t tag0, uint32_t after, int drop) {
+    uint32_t tag0) {
     const ResEnsWg w = wgs[blockIdx.x];
-    if (after && rs.committed[w.s] != after) return;
     const KGrid &g = scen[w.s].g;  // by reference (see k_ensemble)
     const ResGroup grp{w.first, w.count, (int)blockIdx.x - w.first, scen[w.s].bntq, btotal,
                        rs.abort_word + w.s};
     resident_steps<T, VAR, SUB, VISC, EXT>(dom_at(base, scen[w.s].off, ctl[w.s].parity), g,
                                            scen[w.s].kc, scen[w.s].rn, ctl + w.s, out + w.s,
-                                           ring + scen[w.s].bbase, rs, grp, max_steps, tag0,
-                                           w.s == drop ? 0 : RES_ROLL_POLLS);
+                                           ring + scen[w.s].bbase, rs, grp, max_steps, tag0);
 }
 
 template <typename T, int VAR, int SUB>
 static hipError_t launch_resident_vs(const KDom<T> &d, const KGrid &g, const KConst &kc,
                                      const KRain &rn, Ctl *ctl, const KClose &cl,
                                      const ResSync &rs, int ntq, int nwg, int ntiles,
-                                     int max_steps, uint32_t tag0, uint32_t after, bool drop,
+                                     int max_steps, uint32_t tag0, int grid,
                                      hipStream_t stream) {
-    const int polls = drop ? 0 : RES_ROLL_POLLS;
 #define HEXSV_RES(VI, EX)                                                                      \
-    hipLaunchKernelGGL((k_resident<T, VAR, SUB, VI, EX>), dim3(nwg), dim3(RES_NT<T, SUB>), 0,  \
-                       stream, d, g, kc, rn, ctl, cl, rs, ntq, nwg, ntiles, max_steps, tag0,   \
-                       after, polls)
+    hipLaunchKernelGGL((k_resident<T, VAR, SUB, VI, EX>), dim3(grid), dim3(RES_NT<T, SUB>), 0, \
+                       stream, d, g, kc, rn, ctl, cl, rs, ntq, nwg, ntiles, max_steps, tag0)
     if (kc.visc) {
         if constexpr (resident_fits(sizeof(T), VAR, SUB, true)) HEXSV_RES(true, true);
         else return hipErrorInvalidValue;
@@ -593,11 +587,11 @@ template <typename T>
 hipError_t launch_resident(int variant, int sub, const KDom<T> &d, const KGrid &g,
                            const KConst &kc, const KRain &rn, Ctl *ctl, const KClose &cl,
                            const ResSync &rs, int ntq, int nwg, int ntiles, int max_steps,
-                           uint32_t tag0, uint32_t after, bool drop, hipStream_t stream) {
+                           uint32_t tag0, int grid, hipStream_t stream) {
 #define HEXSV_CASE(V, S)                                                                       \
     if (variant == V && sub == S)                                                              \
         return launch_resident_vs<T, V, S>(d, g, kc, rn, ctl, cl, rs, ntq, nwg, ntiles,        \
-                                           max_steps, tag0, after, drop, stream);
+                                           max_steps, tag0, grid, stream);
     HEXSV_CASE(0, 1) HEXSV_CASE(0, 2) HEXSV_CASE(0, 4)
     HEXSV_CASE(1, 1) HEXSV_CASE(1, 2) HEXSV_CASE(1, 4)
     HEXSV_CASE(2, 1) HEXSV_CASE(2, 2) HEXSV_CASE(2, 4)
@@ -610,11 +604,10 @@ static hipError_t launch_ens_resident_vs(bool visc, bool bc, const KDom<T> &base
                                          const EnsScen *scen, const ResEnsWg *wgs, const Ctl *ctl,
                                          Ctl *out, Part *ring, const ResSync &rs, int nwg,
                                          int btotal, int max_steps, uint32_t tag0,
-                                         uint32_t after, int drop, hipStream_t stream) {
+                                         hipStream_t stream) {
 #define HEXSV_RES(VI, EX)                                                                      \
     hipLaunchKernelGGL((k_ens_resident<T, VAR, SUB, VI, EX>), dim3(nwg), dim3(RES_NT<T, SUB>), \
-                       0, stream, base, scen, wgs, ctl, out, ring, rs, btotal, max_steps,      \
-                       tag0, after, drop)
+                       0, stream, base, scen, wgs, ctl, out, ring, rs, btotal, max_steps, tag0)
     if (visc) {
         if constexpr (resident_fits(sizeof(T), VAR, SUB, true)) HEXSV_RES(true, true);
         else return hipErrorInvalidValue;
@@ -628,11 +621,11 @@ template <typename T>
 hipError_t launch_ens_resident(int variant, int sub, bool visc, bool bc, const KDom<T> &base,
                                const EnsScen *scen, const ResEnsWg *wgs, const Ctl *ctl, Ctl *out,
                                Part *ring, const ResSync &rs, int nwg, int btotal, int max_steps,
-                               uint32_t tag0, uint32_t after, int drop, hipStream_t stream) {
+                               uint32_t tag0, hipStream_t stream) {
 #define HEXSV_CASE(V, S)                                                                       \
     if (variant == V && sub == S)                                                              \
         return launch_ens_resident_vs<T, V, S>(visc, bc, base, scen, wgs, ctl, out, ring, rs,  \
-                                               nwg, btotal, max_steps, tag0, after, drop, stream);
+                                               nwg, btotal, max_steps, tag0, stream);
     HEXSV_CASE(0, 1) HEXSV_CASE(0, 2) HEXSV_CASE(0, 4) HEXSV_CASE(2, 1)
 #undef HEXSV_CASE
     return hipErrorInvalidValue;
@@ -642,10 +635,10 @@ hipError_t launch_ens_resident(int variant, int sub, bool visc, bool bc, const K
     template hipError_t launch_resident<T>(int, int, const KDom<T> &, const KGrid &,           \
                                            const KConst &, const KRain &, Ctl *,               \
                                            const KClose &, const ResSync &, int, int, int, int, \
-                                           uint32_t, uint32_t, bool, hipStream_t);             \
+                                           uint32_t, int, hipStream_t);                        \
     template hipError_t launch_ens_resident<T>(int, int, bool, bool, const KDom<T> &,          \
                                                const EnsScen *, const ResEnsWg *, const Ctl *, \
                                                Ctl *, Part *, const ResSync &, int, int, int,  \
-                                               uint32_t, uint32_t, int, hipStream_t);
+                                               uint32_t, hipStream_t);
 
 }  // namespace hexsv

@@ -1,4 +1,4 @@
-"""On-chip launches that are given up: nothing of them is kept, single launches take over from
+"""On-chip launches that are given up: nothing of them is kept, single launches take over after
 the last committed step, and the failing cell is the one that single launches name (needs an
 MI355X)."""
 import threading
@@ -25,8 +25,8 @@ def run(sim, *steps):
 @pytest.mark.parametrize("nq,nr,tile,option", [(200, 190, 0, "masked"), (130, 1100, 0, "masked"),
                                                 (1000, 1000, 2, "plain")])
 def test_single_launches_take_over(hx, nq, nr, tile, option, precision, launch):
-    """Launch 0, 1 or 3 of the five queued for 450 steps is given up: those behind it do
-    nothing, so single steps continue from the odd or even buffer of the last commit."""
+    """Launch 0, 1 or 3 of the five queued for 450 steps misses a workgroup: the others' waits
+    run out, nothing of it is kept, and single steps do what is left after the five."""
     print(f"[given up {nq}x{nr} tile {tile} {precision} launch {launch}]", flush=True)
     sc = scene(nq, nr, option)
     ref = hx.Sim.from_scenario(sc, precision, tile=tile)
