@@ -424,13 +424,18 @@ int64_t hexsv_surrogate_num_params(const hexsv_surrogate *sur);
 /* k of create: the solver steps one window spans (EINVAL at create if k < 1).
  * The window calls below take it when their own k is <= 0.  -1 for a null handle. */
 int32_t hexsv_surrogate_steps(const hexsv_surrogate *sur);
-/* Forward of the 4-layer, 32-channel network as one fused kernel (on = 1:
- * activations stay on chip, a workgroup sweeps 58 columns row by row with the
- * layers two rows apart) or one launch per layer (on = 0).  Until this is
- * called each forward takes the one that is faster for its samples.  Both give
- * the same outputs bit for bit; other depths always run per layer.  EINVAL:
- * null handle or on not 0/1. */
+/* Forward of the 4-layer, 32-channel network as one kernel (on = 1: activations
+ * stay on chip; a workgroup sweeps 58 columns row by row with the layers two
+ * rows apart, or takes a 16 x 16 tile with its margins, whichever is faster) or
+ * one launch per layer (on = 0).  Until this is called each forward takes the
+ * fastest of the three for its samples.  All give the same outputs bit for bit;
+ * other depths always run per layer.  EINVAL: null handle or on not 0/1. */
 int hexsv_surrogate_set_fused(hexsv_surrogate *sur, int32_t on);
+/* The way a forward of these samples runs (use = 0), the one inside a gradient
+ * (1) or a window on that raster (2): 0 layer by layer, 1 as a sweep, 2 by
+ * tiles.  Host code only.  EINVAL: null handle, sizes below 1, use not 0 to 2. */
+int hexsv_surrogate_route(const hexsv_surrogate *sur, const hexsv_grid *grid, int32_t batch,
+                          int32_t nq, int32_t nr, int32_t use);
 /* Copy parameters in (device FP32, n == num_params; resets Adam) or out. */
 int hexsv_surrogate_set_params(hexsv_surrogate *sur, const float *d_params, int64_t n,
                                hipStream_t stream);
@@ -453,10 +458,10 @@ int hexsv_surrogate_forward(hexsv_surrogate *sur, const hexsv_grid *grid, int32_
 /* hexsv_surrogate_forward for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * kernels and result (outputs 0..2 of each cell; the fourth float of d_out is
- * not written), where the network runs layer by layer with the packed input and
- * the hidden activations in a static device workspace of 40 MiB that every GPU
- * the library runs on holds until the process ends, instead of the surrogate's
- * own workspace (the fused kernel needs neither).  It calls no hipMalloc,
+ * not written), with the packed input and the hidden activations in a static
+ * device workspace of 40 MiB that every GPU the library runs on holds until the
+ * process ends, instead of the surrogate's own workspace (the sweep needs
+ * neither, the tiles only the packed input).  It calls no hipMalloc,
  * hipFree or allocating library routine.  The caller passes inputs and outputs
  * as for hexsv_surrogate_forward.  Every call on one GPU shares
  * that GPU's workspace: calls that overlap on one GPU (other streams or host
@@ -534,6 +539,9 @@ int hexsv_sim_run_surrogate(hexsv_sim *sim, hexsv_surrogate *sur, double t_end, 
  * tried).  EINVAL: null sim or max_spans < 0. */
 int hexsv_sim_set_surrogate_backoff(hexsv_sim *sim, int32_t max_spans);
 
+/* Kernels in the captured graph of one window (0: run_surrogate has captured
+ * none yet): six where the network is one kernel, eight layer by layer. */
+int hexsv_sim_window_kernels(const hexsv_sim *sim);
 /* Window counts of every run_surrogate call on this simulation so far:
  * counts[0] kept, counts[1] refused for the water-balance residual, counts[2]
  * refused for the wave-speed growth, counts[3] refused as non-finite. */

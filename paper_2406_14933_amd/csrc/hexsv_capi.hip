@@ -1474,6 +1474,13 @@ extern "C" int hexsv_sim_set_surrogate_backoff(hexsv_sim *s, int32_t max_spans) 
     return HEXSV_OK;
 }
 
+extern "C" int hexsv_sim_window_kernels(const hexsv_sim *s) {
+    if (!s) return fail(HEXSV_EINVAL, "window_kernels: null sim");
+    size_t n = 0;
+    if (s->wgraph[0]) HIP_TRY(hipGraphGetNodes(s->wgraph[0], nullptr, &n));
+    return (int)n;
+}
+
 extern "C" int hexsv_sim_surrogate_stats(const hexsv_sim *s, int64_t *counts) {
     if (!s || !counts) return fail(HEXSV_EINVAL, "surrogate_stats: null argument");
     for (int j = 0; j < 4; ++j) counts[j] = s->w_stats[j];

@@ -34,11 +34,11 @@ int conv_tiles(int nq, int nr, int batch);
 hipError_t launch_conv(int cinp, int coutp, int epi, const __bf16 *x, const __bf16 *wm,
                        const float *bias, void *out, int nq, int nr, int batch, int cout_real,
                        const ConvMask &cm, hipStream_t st, const int32_t *live = nullptr);
-// The 4-layer network with 32 hidden channels in one launch (k_hexnet4): weights
+// The 4-layer network with 32 hidden channels in one launch, a sweep (k_hexnet4): weights
 // and biases of each layer as for launch_conv (layer 0: 16 -> 32, layers 1-2:
 // 32 -> 32, layer 3: 32 -> 16 with 3 outputs written, FP32, OUT_STRIDE per cell;
 // w4: and a zero); x: the FP32 features (f32in) or the packed bf16 input; keep
-// (with f32in): also what the gradient reads.  All equal the layer-by-layer
+// (with f32in, no mask): also what the gradient reads.  All equal the layer-by-layer
 // launch_conv chain's bit for bit.
 struct Net4 {
     const __bf16 *wm[4];
@@ -48,13 +48,17 @@ struct Net4 {
 struct Net4Keep {
     __bf16 *x0, *act[3];
 };
-// Does that beat the layer chain on these samples?  (a forward call, a gradient's forward, a
-// surrogate window)
-enum Net4Use { NET4_FORWARD, NET4_KEEP, NET4_WINDOW };
-bool net4_pays(int nq, int nr, int batch, bool masked, Net4Use use);
 hipError_t launch_net4(const void *x, bool f32in, const Net4 &nw, float *out, bool w4, int nq,
                        int nr, int batch, const ConvMask &cm, hipStream_t st,
                        const int32_t *live = nullptr, const Net4Keep *keep = nullptr);
+// The same network by 16 x 16 tiles (k_hexnet4_tile) from the packed input; three floats a cell.
+hipError_t launch_net4_tiles(const __bf16 *x, const Net4 &nw, float *out, int nq, int nr, int batch,
+                             const ConvMask &cm, hipStream_t st, const int32_t *live = nullptr);
+// Which way is the fastest for these samples (of a forward call, a gradient's forward, a surrogate
+// window)?  chain_too: the layers may also run one by one.
+enum Net4Use { NET4_FORWARD, NET4_KEEP, NET4_WINDOW };
+enum Net4Route { NET4_CHAIN, NET4_SWEEP, NET4_TILES };
+Net4Route net4_route(int nq, int nr, int batch, bool masked, Net4Use use, bool chain_too);
 // Weight-gradient partials: one record (7*coutp*cinp + coutp floats) per workgroup of
 // the launch, which sweeps the tiles with its sums in registers.  WGRAD_WGS workgroups
 // are two per CU, all resident: more would only add records to reduce (half as many with the

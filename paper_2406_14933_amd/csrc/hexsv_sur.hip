@@ -25,8 +25,8 @@ struct SurLayer {
 struct hexsv_surrogate {
     int layers, channels;
     int k;  // solver steps a window spans (its rain sub-steps)
-    int fused;  // forward of the 4-layer, 32-channel network in one kernel (k_hexnet4): 1 always,
-                // 0 never, -1 where that is faster
+    int fused;  // forward of the 4-layer, 32-channel network in one kernel: 1 always, 0 never,
+                // -1 where that is faster
     int64_t nparams;
     float *d_p, *d_m, *d_v, *d_g;
     std::vector<SurLayer> L;
@@ -236,19 +236,16 @@ static int conv_mask(const hexsv_grid *g, int nq, int nr, nn::ConvMask *cm, cons
     return HEXSV_OK;
 }
 
-// Does the forward run as one kernel (k_hexnet4)?  Rasters too wide for its launch do not.
-static bool runs_fused(const hexsv_surrogate *s, int nq, int nr, int batch,
-                       const nn::ConvMask &cm, nn::Net4Use use) {
-    if (!s->fused || s->layers != 4 || s->channels != 32 || nq > 1 << 26) return false;
-    return s->fused > 0 || nn::net4_pays(nq, nr, batch, cm.active != nullptr, use);
+// How a forward runs.  A gradient's has all ways whatever set_fused says, but for 0.
+static nn::Net4Route route_of(const hexsv_surrogate *s, int nq, int nr, int batch,
+                              const nn::ConvMask &cm, nn::Net4Use use, bool chain_too) {
+    if (!s->fused || s->layers != 4 || s->channels != 32) return nn::NET4_CHAIN;
+    return nn::net4_route(nq, nr, batch, cm.active != nullptr, use, chain_too || s->fused < 0);
 }
-// From the features straight to the caller's output, unless they overlap (the kernel reads
-// features while it writes outputs).
-static bool runs_direct(const hexsv_surrogate *s, int nq, int nr, int batch,
-                        const nn::ConvMask &cm, const float *f, const float *out) {
-    const int64_t cells = (int64_t)batch * nq * nr;
-    return (out + cells * nn::OUT_STRIDE <= f || f + cells * nn::FEATURES <= out) &&
-           runs_fused(s, nq, nr, batch, cm, nn::NET4_FORWARD);
+// May the sweep go from the features straight to the caller's output?  Not if they overlap (it
+// reads features while it writes outputs).
+static bool apart(const float *f, const float *out, int64_t cells) {
+    return out + cells * nn::OUT_STRIDE <= f || f + cells * nn::FEATURES <= out;
 }
 static nn::Net4 net4_of(const hexsv_surrogate *s) {
     nn::Net4 nw;
@@ -259,13 +256,16 @@ static nn::Net4 net4_of(const hexsv_surrogate *s) {
     return nw;
 }
 
-// Forward over the packed features already in s->x0; output in s->out, in one kernel or (with
-// the hidden activations, which the gradient reads) as the layer chain; the same output bit
-// for bit.
+// Forward over the packed features already in s->x0; output in s->out, by any route (the chain
+// leaves the hidden activations, which the gradient reads); the same output bit for bit.
 static int forward_packed(hexsv_surrogate *s, int nq, int nr, int batch, const nn::ConvMask &cm,
-                          hipStream_t st, bool fused, const int32_t *live = nullptr) {
-    if (fused) {
+                          hipStream_t st, nn::Net4Route route, const int32_t *live = nullptr) {
+    if (route == nn::NET4_SWEEP) {
         HIP_TRY(nn::launch_net4(s->x0, false, net4_of(s), s->out, true, nq, nr, batch, cm, st, live));
+        return HEXSV_OK;
+    }
+    if (route == nn::NET4_TILES) {
+        HIP_TRY(nn::launch_net4_tiles(s->x0, net4_of(s), s->out, nq, nr, batch, cm, st, live));
         return HEXSV_OK;
     }
     const __bf16 *x = s->x0;
@@ -302,8 +302,10 @@ extern "C" int hexsv_surrogate_forward(hexsv_surrogate *s, const hexsv_grid *gri
     if (rc) return rc;
     rc = check_call(s, batch, nq, nr);
     if (rc) return rc;
+    const nn::Net4Route route = route_of(s, nq, nr, batch, cm, nn::NET4_FORWARD, false);
     // straight to the caller's cells (no workspace) where they take 16-byte stores
-    if (((uintptr_t)d_out & 15) == 0 && runs_direct(s, nq, nr, batch, cm, d_features, d_out)) {
+    if (route == nn::NET4_SWEEP && ((uintptr_t)d_out & 15) == 0 &&
+        apart(d_features, d_out, (int64_t)batch * nq * nr)) {
         HIP_TRY(nn::launch_net4(d_features, true, net4_of(s), d_out, true, nq, nr, batch, cm, st));
         return HEXSV_OK;
     }
@@ -311,12 +313,26 @@ extern "C" int hexsv_surrogate_forward(hexsv_surrogate *s, const hexsv_grid *gri
     rc = check_shape(s, batch, nq, nr, &cells);
     if (rc) return rc;
     HIP_TRY(nn::launch_pack_features(d_features, cells, s->x0, st));
-    rc = forward_packed(s, nq, nr, batch, cm, st,
-                        runs_fused(s, nq, nr, batch, cm, nn::NET4_FORWARD));
+    rc = forward_packed(s, nq, nr, batch, cm, st, route);
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(d_out, s->out, sizeof(float) * nn::OUT_STRIDE * cells,
                            hipMemcpyDeviceToDevice, st));
     return HEXSV_OK;
+}
+
+extern "C" int hexsv_surrogate_route(const hexsv_surrogate *s, const hexsv_grid *grid, int32_t batch,
+                                     int32_t nq, int32_t nr, int32_t use) {
+    if (!s || batch < 1 || nq < 1 || nr < 1 || use < 0 || use > 2)
+        return fail(HEXSV_EINVAL, "surrogate_route: bad argument");
+    nn::ConvMask cm;
+    const int rc = conv_mask(grid, nq, nr, &cm, "surrogate_route");
+    if (rc) return rc;
+    const nn::Net4Use uses[3] = {nn::NET4_FORWARD, nn::NET4_KEEP, nn::NET4_WINDOW};
+    switch (route_of(s, nq, nr, batch, cm, uses[use], use == 1)) {
+        case nn::NET4_SWEEP: return 1;
+        case nn::NET4_TILES: return 2;
+        default: return 0;
+    }
 }
 
 // ---- interface for the solver's surrogate windows (hexsv_capi.hip)
@@ -338,7 +354,7 @@ int sur_forward_x0(hexsv_surrogate *s, const hexsv_grid *grid, hipStream_t st,
     int rc = conv_mask(grid, grid->kg.nq, grid->kg.nr, &cm, "run_surrogate");
     if (rc) return rc;
     const int nq = grid->kg.nq, nr = grid->kg.nr;
-    return forward_packed(s, nq, nr, 1, cm, st, runs_fused(s, nq, nr, 1, cm, nn::NET4_WINDOW), live);
+    return forward_packed(s, nq, nr, 1, cm, st, route_of(s, nq, nr, 1, cm, nn::NET4_WINDOW, false), live);
 }
 
 int sur_forward_hidden(hexsv_surrogate *s, const hexsv_grid *grid, hipStream_t st,
@@ -346,7 +362,8 @@ int sur_forward_hidden(hexsv_surrogate *s, const hexsv_grid *grid, hipStream_t s
     nn::ConvMask cm;
     int rc = conv_mask(grid, grid->kg.nq, grid->kg.nr, &cm, "run_surrogate");
     if (rc) return rc;
-    if (s->channels != 32 || runs_fused(s, grid->kg.nq, grid->kg.nr, 1, cm, nn::NET4_WINDOW))
+    if (s->channels != 32 ||
+        route_of(s, grid->kg.nq, grid->kg.nr, 1, cm, nn::NET4_WINDOW, false) != nn::NET4_CHAIN)
         return HEXSV_EUNSUPPORTED;
     const int nq = grid->kg.nq, nr = grid->kg.nr;
     const __bf16 *x = s->x0;
@@ -370,13 +387,13 @@ static int gradient(hexsv_surrogate *s, const hexsv_grid *grid, int batch, int n
     int64_t cells;
     rc = check_shape(s, batch, nq, nr, &cells);
     if (rc) return rc;
-    if (runs_fused(s, nq, nr, batch, cm, nn::NET4_KEEP)) {
+    if (route_of(s, nq, nr, batch, cm, nn::NET4_KEEP, true) == nn::NET4_SWEEP) {
         const nn::Net4Keep keep{s->x0, {s->act[0], s->act[1], s->act[2]}};
         HIP_TRY(nn::launch_net4(feat, true, net4_of(s), s->out, false, nq, nr, batch, cm, st, nullptr,
                                 &keep));
     } else {
         HIP_TRY(nn::launch_pack_features(feat, cells, s->x0, st));
-        rc = forward_packed(s, nq, nr, batch, cm, st, false);
+        rc = forward_packed(s, nq, nr, batch, cm, st, nn::NET4_CHAIN);
         if (rc) return rc;
     }
     const double inv_count = 1.0 / (3.0 * (double)cells);
@@ -485,7 +502,8 @@ extern "C" int hexsv_surrogate_forward_noalloc(hexsv_surrogate *s, const hexsv_g
     nn::ConvMask cm;
     int rc = conv_mask(grid, nq, nr, &cm, "surrogate_forward_noalloc");
     if (rc) return rc;
-    if (runs_direct(s, nq, nr, batch, cm, d_features, d_out)) {
+    const nn::Net4Route route = route_of(s, nq, nr, batch, cm, nn::NET4_FORWARD, true);
+    if (route == nn::NET4_SWEEP && apart(d_features, d_out, cells)) {
         HIP_TRY(nn::launch_net4(d_features, true, net4_of(s), d_out, false, nq, nr, batch, cm, st));
         return HEXSV_OK;
     }
@@ -496,6 +514,10 @@ extern "C" int hexsv_surrogate_forward_noalloc(hexsv_surrogate *s, const hexsv_g
     __bf16 *act[2] = {(__bf16 *)(ws + NOALLOC_X0), (__bf16 *)(ws + NOALLOC_X0 + NOALLOC_ACT)};
     // every buffer is written in full before it is read: nothing needs clearing
     HIP_TRY(nn::launch_pack_features(d_features, cells, x0, st));
+    if (route == nn::NET4_TILES) {
+        HIP_TRY(nn::launch_net4_tiles(x0, net4_of(s), d_out, nq, nr, batch, cm, st));
+        return HEXSV_OK;
+    }
     const __bf16 *x = x0;
     for (int l = 0; l < s->layers; ++l) {
         const SurLayer &y = s->L[l];

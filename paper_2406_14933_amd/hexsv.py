@@ -120,6 +120,8 @@ _SIGS = [
     ("hexsv_surrogate_set_scales", C.c_int, [_VP, C.POINTER(C.c_float), C.c_int32]),
     ("hexsv_surrogate_get_scales", C.c_int, [_VP, C.POINTER(C.c_float), C.c_int32]),
     ("hexsv_surrogate_set_fused", C.c_int, [_VP, C.c_int32]),
+    ("hexsv_surrogate_route", C.c_int, [_VP, _VP, C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
+    ("hexsv_sim_window_kernels", C.c_int, [_VP]),
     ("hexsv_surrogate_forward", C.c_int, [_VP, _VP, C.c_int32, C.c_int32, C.c_int32, _VP, _VP,
                                           _VP]),
     ("hexsv_surrogate_forward_noalloc", C.c_int, [_VP, _VP, C.c_int32, C.c_int32, C.c_int32,
@@ -582,6 +584,15 @@ class Surrogate:
         launch per layer (a surrogate starts out with the faster of the two for each call); the
         outputs are the same bit for bit."""
         _check(lib().hexsv_surrogate_set_fused(self._h, 1 if on else 0))
+
+    def route(self, batch, nq, nr, grid=None, use="forward"):
+        """How the network runs on such samples: "chain", "sweep" or "tiles"; use: "forward",
+        "gradient" or "window"."""
+        rc = lib().hexsv_surrogate_route(self._h, grid._h if grid else None, int(batch), int(nq),
+                                         int(nr), ("forward", "gradient", "window").index(use))
+        if rc < 0:
+            _check(rc)
+        return ("chain", "sweep", "tiles")[rc]
 
     # grid (optional): the raster whose neighbour rule the taps follow (periodic sides, the
     # domain mask); without it the raster is a walled nq x nr parallelogram

@@ -1,29 +1,14 @@
-"""Which kernels a surrogate call launches: the one-launch network or the layer chain, whichever
-is faster for the samples, with the same outputs bit for bit (needs an MI355X)."""
+"""How a surrogate call runs its network: as a sweep, by tiles or layer by layer, whichever is
+fastest for the samples, with the same outputs bit for bit (needs an MI355X)."""
 import numpy as np
 import pytest
 import torch
-from torch.profiler import ProfilerActivity, profile
 
 import oracle.surrogate as so
 import synth
 from tests.test_gpu_parity import hx  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
-
-
-def kernels(call):
-    """Names of the kernels that call() launches, from graphs too, in a Counter-like dict."""
-    torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
-        call()
-        torch.cuda.synchronize()
-    count = {}
-    for e in p.events():
-        for k in ("k_hexnet4", "k_hexconv<", "k_win_apply", "k_win_last", "k_win_probe"):
-            if k in e.name:
-                count[k] = count.get(k, 0) + 1
-    return count
 
 
 def network(hx, batch, nq, nr, masked, seed=3):
@@ -44,35 +29,73 @@ def network(hx, batch, nq, nr, masked, seed=3):
     return sur, grid, f, t
 
 
-# (samples, raster, mask, one launch for a forward, for a gradient)
+# (samples, raster, mask, a forward's route, a forced one-kernel forward's, a gradient's)
 CALLS = [
-    (1, 100, 75, False, True, True),
-    (1, 100, 75, True, True, False),
-    (16, 128, 120, False, True, True),
-    (512, 16, 16, False, True, True),
-    (4096, 8, 8, False, False, False),   # mostly margins
-    (4096, 1, 1, False, False, False),
-    (512, 16, 16, True, False, False),
-    (64, 64, 64, True, False, False),    # two strips for 64 columns, with predicates
-    (8, 60, 1000, True, False, False),
-    (2, 512, 512, True, True, False),    # activations to keep as well
+    (1, 100, 75, False, "sweep", "sweep", "sweep"),
+    (1, 100, 75, True, "sweep", "sweep", "chain"),   # masked activations are not kept on the way
+    (16, 128, 120, False, "sweep", "sweep", "sweep"),
+    (2, 512, 512, True, "sweep", "sweep", "chain"),
+    (64, 58, 58, True, "sweep", "sweep", "chain"),
+    (512, 16, 16, False, "tiles", "tiles", "sweep"),  # a sweep would be mostly margins
+    (512, 16, 16, True, "tiles", "tiles", "chain"),
+    (8, 3, 1000, True, "tiles", "tiles", "chain"),
+    (4096, 8, 8, False, "chain", "tiles", "chain"),
+    (4096, 1, 1, False, "chain", "sweep", "chain"),
+    (64, 128, 128, True, "chain", "sweep", "chain"),
+    (8, 60, 1000, True, "chain", "tiles", "chain"),
 ]
 
 
-@pytest.mark.parametrize("batch,nq,nr,masked,forward,gradient", CALLS)
-def test_calls_take_the_faster_route(hx, batch, nq, nr, masked, forward, gradient):
+@pytest.mark.parametrize("batch,nq,nr,masked,forward,forced,gradient", CALLS)
+def test_calls_take_the_fastest_route(hx, batch, nq, nr, masked, forward, forced, gradient):
     print(f"[route {batch}x{nq}x{nr} masked {masked}]", flush=True)
     sur, grid, f, t = network(hx, batch, nq, nr, masked)
-    out = {}
-    seen = kernels(lambda: out.update(o=sur.forward(f, nq, nr, grid)))
-    assert (seen.get("k_hexnet4", 0), seen.get("k_hexconv<", 0)) == ((1, 0) if forward else (0, 4))
-    seen = kernels(lambda: out.update(g=sur.gradient(f, t, nq, nr, grid)))
-    assert (seen.get("k_hexnet4", 0), seen.get("k_hexconv<", 0)) == ((1, 0) if gradient else (0, 4))
+    shape = (batch, nq, nr, grid)
+    assert sur.route(*shape) == forward and sur.route(*shape, "gradient") == gradient
+    o, (loss, g) = sur.forward(f, nq, nr, grid), sur.gradient(f, t, nq, nr, grid)
     for on in (True, False):
         sur.set_fused(on)
-        assert torch.equal(sur.forward(f, nq, nr, grid)[:, :3], out["o"][:, :3])
-        loss, g = sur.gradient(f, t, nq, nr, grid)
-        assert loss == out["g"][0] and torch.equal(g, out["g"][1])
+        assert sur.route(*shape) == (forced if on else "chain")
+        assert sur.route(*shape, "gradient") == (gradient if on else "chain")
+        assert torch.equal(sur.forward(f, nq, nr, grid)[:, :3], o[:, :3])
+        loss1, g1 = sur.gradient(f, t, nq, nr, grid)
+        assert loss1 == loss and torch.equal(g1, g)
+
+
+# parts of a tile, whole ones, and remainders in either direction, with every kind of border;
+# as many samples as it takes for a forced one-kernel forward to choose the tiles
+TILED = [(b, k) for k in ("walls", "masked", "periodic", "periodic masked")
+         for b in [(512, 5, 6), (512, 16, 16), (512, 14, 30), (1500, 15, 13)] +
+         ([(560, 17, 9), (512, 20, 16)] if "masked" in k else [])]
+
+
+@pytest.mark.parametrize("size,kind", TILED)
+def test_tiles_equal_the_chain(hx, size, kind):
+    batch, nq, nr = size
+    print(f"[tiles {batch}x{nq}x{nr} {kind}]", flush=True)
+    sur, _, f, _ = network(hx, batch, nq, nr, False, seed=nq)
+    rng = np.random.default_rng(nr)
+    active = None
+    if "masked" in kind:
+        active = (rng.random((nr, nq)) < 0.7).astype(np.uint8)
+        active[0, 0], active[-1, -1] = 1, 0
+    side = (hx.PERIODIC if "periodic" in kind else hx.WALL,) * 4
+    grid = hx.Grid(nq, nr, 1.0, side=side, active=active)
+    sur.set_fused(True)
+    assert sur.route(batch, nq, nr, grid) == "tiles"
+    out = sur.forward(f, nq, nr, grid)
+    sur.set_fused(False)
+    assert torch.equal(sur.forward(f, nq, nr, grid)[:, :3], out[:, :3])
+
+
+def test_noalloc_takes_the_tiles(hx):
+    batch, nq, nr = 512, 16, 16
+    sur, _, f, _ = network(hx, batch, nq, nr, False)
+    want = sur.forward(f, nq, nr)
+    out = torch.full((batch * nq * nr, 4), 7.0, device="cuda")
+    assert sur.route(batch, nq, nr) == "tiles"
+    sur.forward_noalloc(f, nq, nr, out)
+    assert torch.equal(out[:, :3], want[:, :3]) and bool((out[:, 3] == 7).all())
 
 
 @pytest.mark.parametrize("shift", [0, 1, 2, 3, 4])
@@ -86,20 +109,10 @@ def test_forward_to_any_float_address(hx, shift):
     out = buf[shift:shift + 4 * nq * nr]
     assert (out.data_ptr() % 16 == 0) == (shift % 4 == 0)
 
-    def call():
-        hx._check(hx.lib().hexsv_surrogate_forward(sur._h, None, 1, nq, nr, hx._ptr(f),
-                                                   hx._ptr(out), hx._stream()))
-
-    call()
+    hx._check(hx.lib().hexsv_surrogate_forward(sur._h, None, 1, nq, nr, hx._ptr(f), hx._ptr(out),
+                                               hx._stream()))
     assert torch.equal(out.view(-1, 4)[:, :3], want[:, :3])
     assert bool((buf[:shift] == 7).all()) and bool((buf[shift + 4 * nq * nr:] == 7).all())
-    # the general route: packed input, the workspace's output, a copy
-    seen = kernels(call)
-    assert seen == {"k_hexnet4": 1}
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
-        call()
-        torch.cuda.synchronize()
-    assert any("k_pack_features" in e.name for e in p.events()) == (shift % 4 != 0)
 
 
 def still(hx, nq, nr, masked):
@@ -125,24 +138,31 @@ def windows(sc, sim, sur, n=16):
     assert kept == (n, 0)
 
 
-@pytest.mark.parametrize("nq,nr,masked,fused", [(100, 75, False, True), (512, 512, False, True),
-                                                (60, 1000, True, False)])
-def test_windows_take_the_faster_route(hx, nq, nr, masked, fused):
+@pytest.mark.parametrize("nq,nr,masked,way", [
+    (100, 75, False, "sweep"), (512, 512, False, "sweep"), (60, 1000, True, "chain"),
+    (512, 512, True, "chain")])
+def test_windows_take_the_fastest_route(hx, nq, nr, masked, way):
     sc, sim, sur = still(hx, nq, nr, masked)
-    seen = kernels(lambda: windows(sc, sim, sur))
-    assert seen["k_win_probe"] == 16
-    assert (seen.get("k_hexnet4", 0), seen.get("k_win_last", 0)) == ((16, 0) if fused else (0, 16))
+    assert sur.route(1, nq, nr, sim.grid, "window") == way
+    windows(sc, sim, sur)
+    got = sim.state_numpy()
+    assert hx.lib().hexsv_sim_window_kernels(sim._h) == (8 if way == "chain" else 6)
+    for on in (True, False):
+        sur.set_fused(on)
+        windows(sc, sim, sur)
+        again = sim.state_numpy()
+        assert all(np.array_equal(got[k], again[k]) for k in got)
 
 
 def test_windows_follow_set_fused(hx):
     """The windows' graphs are captured on the first call; set_fused afterwards holds for them."""
     sc, sim, sur = still(hx, 100, 75, False)
+    assert hx.lib().hexsv_sim_window_kernels(sim._h) == 0
     windows(sc, sim, sur)
     for on in (False, True, False):
         sur.set_fused(on)
-        seen = kernels(lambda: windows(sc, sim, sur))
-        got = tuple(seen.get(k, 0) for k in ("k_hexnet4", "k_win_apply", "k_hexconv<", "k_win_last"))
-        assert got == ((16, 16, 0, 0) if on else (0, 0, 48, 16))
+        windows(sc, sim, sur)
+        assert hx.lib().hexsv_sim_window_kernels(sim._h) == (6 if on else 8)
 
 
 def test_a_new_surrogate_at_an_old_address(hx):
@@ -169,3 +189,12 @@ def test_a_new_surrogate_at_an_old_address(hx):
     assert not np.array_equal(want["h"], sc.h0.astype(np.float32))
     for k in want:
         assert np.array_equal(got[k], want[k]), k
+
+
+def test_route_arguments(hx):
+    L = hx.lib()
+    sur = hx.Surrogate(4, 32)
+    for args in ((None, None, 1, 8, 8, 0), (sur._h, None, 0, 8, 8, 0), (sur._h, None, 1, 8, 8, 3)):
+        assert L.hexsv_surrogate_route(*args) == hx.EINVAL
+    assert L.hexsv_sim_window_kernels(None) == hx.EINVAL
+    assert hx.Surrogate(3, 32).route(16, 512, 512) == "chain"
