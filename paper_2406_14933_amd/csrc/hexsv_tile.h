@@ -814,7 +814,12 @@ __device__ inline void tile_compute(const TileLDS<T, TQ, TR, V> &L, const TileRe
     auto cell = [&](int k, auto gen) {
         constexpr bool GEN = decltype(gen)::value;
         const EdgeSums<T> es = cells.template edges<GEN>(tid, k);
-        cells.template finish<GEN>(tid, k, es, sc, dt, acc, p32, sink);
+        // FP32 with 1024 threads (128 registers each): the cell's place is formed again after its
+        // edges rather than kept through them: 27 registers spill instead of 33 with two
+        // cells a thread (FP64 would spill 63 instead of 27 with one)
+        int again = tid;
+        if constexpr (NT == 1024 && sizeof(T) == 4) asm volatile("" : "+v"(again));
+        cells.template finish<GEN>(again, k, es, sc, dt, acc, p32, sink);
     };
     if (general) {
 #pragma unroll

@@ -56,6 +56,13 @@ def test_persistent_fp64_ensemble_spills_little(kernels, tile, scratch):
     assert kernels[f"k_ensemble<double, {tile}>"]["scratch"] <= scratch
 
 
+@pytest.mark.parametrize("tile,scratch", [("64, 16, 1024", 24), ("64, 32, 1024", 108),
+                                          ("128, 16, 1024", 108)])
+def test_persistent_fp32_ensemble_spills_little(kernels, tile, scratch):
+    """124 bytes a lane cost 5 %."""
+    assert kernels[f"k_ensemble<float, {tile}>"]["scratch"] <= scratch
+
+
 @pytest.mark.parametrize("kernel", ["k_resident", "k_ens_resident"])
 def test_viscous_fp32_on_chip_tile_is_inlined(kernels, kernel):
     """As a function of its own the step took its arguments and arrays through scratch memory."""
