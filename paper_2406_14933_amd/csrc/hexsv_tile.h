@@ -413,17 +413,18 @@ struct TileCells {
                 // given mass flux: the discharge h_j v_j crosses the edge whatever the cell
                 // holds; the pressure term sees the cell's own depth over the neighbour's
                 // bed (wj holds that bed level)
-                const T vn = vb1 * NX[e] + vb2 * NY[e];
                 if constexpr (F32) {
-                    const T F = mj * vn;  // mj holds l h_j
-                    Ls -= F;
-                    A1 -= F * vb1;
-                    A2 -= F * vb2;
-                    const T Q = (G * (wj + hi) - wi) * Mi;
-                    A1 -= Q * NXh[e];
-                    A2 -= Q * NYh[e];
-                    Fout += F;
+                    const T vn = edge_vn(e, vb1, vb2);
+                    T F = mj * vn;  // mj holds l h_j
+                    edge_mass(Ls, F, mj, vn);
+                    A1 = __builtin_fmaf(-F, vb1, A1);
+                    A2 = __builtin_fmaf(-F, vb2, A2);
+                    const T Q = __builtin_fmaf(G, wj + hi, -wi) * Mi;
+                    A1 = __builtin_fmaf(-Q, NXh[e], A1);
+                    if (e != 0 && e != 3) A2 = __builtin_fmaf(-Q, NYh[e], A2);
+                    Fout = __builtin_fmaf(mj, vn, Fout);
                 } else {
+                    const T vn = vb1 * NX[e] + vb2 * NY[e];
                     const T F = l * mj * vn;
                     Ls -= F;
                     A1 -= F * vb1;
@@ -438,7 +439,7 @@ struct TileCells {
             if constexpr (F32) {
                 // mj holds l*theta_j*h_j
                 T vn;
-                if constexpr (LIKE_GEN) vn = edge_vn(e, vb1, vb2);
+                if constexpr (GEN || LIKE_GEN) vn = edge_vn(e, vb1, vb2);
                 else vn = (e == 0) ? vb1 : ((e == 3) ? -vb1 : vb1 * NX[e] + vb2 * NY[e]);
                 const T dw = wj - wi;
                 // one selected mass serves both terms: the upwind mass of the flux
@@ -447,13 +448,20 @@ struct TileCells {
                 const T key = (vn != T(0)) ? vn : -dw;  // w_i > w_j decides at vn = 0
                 const T msel = key > T(0) ? Mi : mj;
                 T F = msel * vn;
-                if constexpr (LIKE_GEN) edge_mass(Ls, F, msel, vn);
-                else Ls -= F;
-                A1 -= F * vb1;
-                A2 -= F * vb2;
                 const T Q = dw * msel;
-                A1 -= Q * NXh[e];
-                if (e != 0 && e != 3) A2 -= Q * NYh[e];
+                if constexpr (GEN || LIKE_GEN) {
+                    edge_mass(Ls, F, msel, vn);
+                    A1 = __builtin_fmaf(-F, vb1, A1);
+                    A2 = __builtin_fmaf(-F, vb2, A2);
+                    A1 = __builtin_fmaf(-Q, NXh[e], A1);
+                    if (e != 0 && e != 3) A2 = __builtin_fmaf(-Q, NYh[e], A2);
+                } else {
+                    Ls -= F;
+                    A1 -= F * vb1;
+                    A2 -= F * vb2;
+                    A1 -= Q * NXh[e];
+                    if (e != 0 && e != 3) A2 -= Q * NYh[e];
+                }
                 if (GEN && (EXT ? cd != CODE_INTERIOR : cd == CODE_OUTFLOW))
                     Fout = __builtin_fmaf(msel, vn, Fout);  // outflow or Dirichlet edge
             } else {
@@ -538,8 +546,9 @@ struct TileCells {
         return ec;
     }
 
-    // The normal velocity of edge e and the flux's part in the mass sum, with FP32's fused
-    // multiply-adds where the compiler places them in edges<true>.
+    // The normal velocity of edge e and the flux's part in the mass sum of the general path.
+    // FP32's fused multiply-adds are written out there, so that all its forms (edges<true>,
+    // edges_fixed, edges<false, true>) round alike whatever the compiler would fuse.
     __device__ static inline T edge_vn(int e, T vb1, T vb2) {
         const T S3H = (T)0.86602540378443864676;
         const T NX[6] = {T(1), T(0.5), T(-0.5), T(-1), T(-0.5), T(0.5)};
