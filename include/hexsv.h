@@ -256,8 +256,10 @@ int hexsv_sim_set_state(hexsv_sim *sim, double t0, const double *d_h, const doub
  * books of the new state; the last step lands on t_end exactly.  A raster
  * whose tiles (or stacks of 2 or 4 of them) number no more than the device's
  * compute units, with no periodic side, runs as launches that each hold it on
- * chip for up to steps_per_graph steps; others, and what such a launch gave
- * up, run as replays of captured graphs of steps_per_graph (and of 8) steps.
+ * chip for up to steps_per_graph steps (8 at least, 128 at most).  Others, runs
+ * of too few steps and rasters that single steps are faster for, and what an
+ * on-chip launch gave up run as replays of captured graphs of steps_per_graph
+ * (and of 8) steps.
  * Both give the same state and books bit for bit, go to `stream` in batches
  * sized by the steps expected to remain, and read the 256-byte control block
  * back after each batch.  EDOMAIN: t_end < t.
@@ -270,11 +272,12 @@ int hexsv_sim_run(hexsv_sim *sim, double t_end, int64_t max_steps, hipStream_t s
 int hexsv_sim_set_resident(hexsv_sim *sim, int32_t on);
 /* On-chip launches run() has issued so far (-1 for a null handle). */
 int64_t hexsv_sim_resident_launches(const hexsv_sim *sim);
-/* An on-chip launch whose workgroups do not all start in time (other streams hold
- * compute units) is given up without any effect, and single launches do the rest of
- * the run and of the next runs (1, then 3, 7 ... 63 of them while it goes on).  For
- * tests of that: the on-chip launch `launch` launches from now (0: the next one) is
- * given up.  EINVAL: null handle or launch < 0. */
+/* An on-chip launch whose workgroups do not all start in time (about 4 ms; other
+ * streams hold compute units) is given up without any effect, those queued behind it
+ * wait a sixteenth of that, and single launches do the rest of the run and of the next
+ * runs (1, then 3, 7 ... 63 of them while it goes on).  For tests of that: the on-chip
+ * launch `launch` launches from now (0: the next one) lacks a workgroup, so that the
+ * others' waits expire.  EINVAL: null handle or launch < 0. */
 int hexsv_sim_drop_resident(hexsv_sim *sim, int64_t launch);
 
 /* Current state as FP64 device arrays (each nullable): h, v1, v2 and the
@@ -290,10 +293,11 @@ int hexsv_sim_set_books(hexsv_sim *sim, const hexsv_books *books, hipStream_t st
 
 /* Device timing of run(): while enabled, run() brackets every batch of graph
  * replays (or of launches of many steps, counted as replays) with hipEvents on
- * its stream and accumulates their GPU time and the steps they took.  Reads the totals since the last reset; enable >= 0
- * switches timing on (1) or off (0) and resets the totals, enable < 0 only
- * reads.  In a graph each step is one kernel launch, so gpu_ms/steps is the
- * step kernel's average duration including launch gaps inside the graph. */
+ * its stream and accumulates their GPU time and the steps they took.  Reads the
+ * totals since the last reset; enable >= 0 switches timing on (1) or off (0) and
+ * resets the totals, enable < 0 only reads.  In a graph each step is one kernel
+ * launch, so gpu_ms/steps is the step kernel's average duration including launch
+ * gaps inside the graph; on chip it is the launch's share of one step. */
 int hexsv_sim_timing(hexsv_sim *sim, int32_t enable, double *gpu_ms, int64_t *steps,
                      int64_t *replays);
 
@@ -306,10 +310,11 @@ int hexsv_sim_time_kernel(hexsv_sim *sim, int32_t nlaunch, double *avg_ms, hipSt
 /* Autotuner: time every tile variant of the step kernel on this simulation's
  * raster and current state (nlaunch steps each, in the launches that run()
  * would take with that variant: on chip, or single ones as
- * hexsv_sim_time_kernel; state and books are left unchanged), switch the simulation to the fastest
- * and, if cache_path is non-null, record the result there (JSON keyed by
- * architecture, kernel, precision and size bucket).  hexsv_sim_create
- * consults the file named by $HEXSV_TUNE_CACHE when params->tile < 0. */
+ * hexsv_sim_time_kernel; state and books are left unchanged), switch the
+ * simulation to the fastest and, if cache_path is non-null, record the result
+ * there (JSON keyed by architecture, kernel, precision and size bucket).
+ * hexsv_sim_create consults the file named by $HEXSV_TUNE_CACHE when
+ * params->tile < 0. */
 int hexsv_sim_autotune(hexsv_sim *sim, int32_t nlaunch, const char *cache_path,
                        int32_t *best_tile, double *best_ms, hipStream_t stream);
 
@@ -360,7 +365,8 @@ int hexsv_ensemble_run(hexsv_ensemble *ens, const double *t_end, int64_t max_ste
                        hipStream_t stream);
 
 /* hexsv_sim_set_resident, hexsv_sim_resident_launches and hexsv_sim_drop_resident
- * (there by scenario s) for an ensemble's batched mode. */
+ * for an ensemble's batched mode; drop_resident leaves scenario s's part of that launch
+ * without its mark of completion (EINVAL also for s out of range). */
 int hexsv_ensemble_set_resident(hexsv_ensemble *ens, int32_t on);
 int64_t hexsv_ensemble_resident_launches(const hexsv_ensemble *ens);
 int hexsv_ensemble_drop_resident(hexsv_ensemble *ens, int32_t s, int64_t launch);

@@ -909,8 +909,8 @@ __global__ __launch_bounds__(WG_NT<DX>, 2) void k_hexconv_wgrad(const __bf16 *__
 // scatter them into the flat parameter-gradient layout W[o][c][t] (o < cout, c < cin),
 // b[o].  16 threads share an element, each adding every 16th record with eight loads
 // in flight, then a tree over the 16: one launch for all layers, 15 us at 512
-// records of 4 layers (10 with half the records of three), where one thread per element over 2048 records took 635 us a
-// layer (its loads one behind the other).
+// records of 4 layers (10 with half the records of three), where one thread per element
+// over 2048 records took 635 us a layer (its loads one behind the other).
 constexpr int RED_GRP = 16, RED_EL = 256 / RED_GRP;
 __global__ __launch_bounds__(256) void k_wgrad_reduce(WgradTable tab,
                                                       float *__restrict__ grad) {

@@ -22,19 +22,22 @@
 // to the other buffer, and the fold that follows commits it only if every workgroup has
 // reached the end.  Otherwise it sets the abort word of the launch queued behind this one, whose
 // roll call then fails at the first look at that word (256 polls) if it has to wait again; a test
-// of a flag at the kernel's start cost 1 to 3 % of a small raster's step.  The host then repeats the steps with one launch each, which also
-// names a non-finite cell.  Every wait is bounded.
+// of a flag at the kernel's start cost 1 to 3 % of a small raster's step.  The host then repeats
+// the steps with one launch each, which also names a non-finite cell.  Every wait is bounded.
 //
 // The arithmetic, the tiles whose books are recorded and the threads that sum them are those
 // of k_step with the same tile variant, so state and books are the same bit for bit.
 //
 // Bound by the chain of a step: rim words out, a poll that sees them (about 1.5 us across
 // XCDs), edges, wave speeds out and polled again, cells, two barriers; for 1024 x 1024 by the
-// arithmetic of four tiles per CU.  Per step of a whole run, setup and books included, single
-// launches -> resident: 64 x 64 FP64 8.3 -> 4.2 us, 1159 x 72 viscous 10.6 -> 5.4, 512 x 512
-// FP32 10.7 -> 5.6, 1024 x 1024 FP32 16.2 -> 12.3 and FP64 28.1 -> 25.5; 45 flumes in FP64, a
-// group of workgroups each, 25.1 -> 11.7.  Of that, edge codes kept in registers and the early
-// first read of the wave speeds gave 15 % on 64 x 64 and 7 % on 512 x 512 cells.
+// arithmetic of four tiles per CU as well.  Share of a SIMD's cycles in which it issues vector
+// arithmetic, and of the waves' time spent waiting: 64 x 64 FP64 0.37 and 0.42 (one wave per
+// SIMD), 1024 x 1024 FP32 0.66 and 0.63 (four), FP64 0.48 and 0.53 (two).
+// Per step of a whole run, setup and books included, single launches -> resident: 64 x 64 FP64
+// 8.3 -> 4.2 us, 1159 x 72 viscous 10.6 -> 5.4, 512 x 512 FP32 10.6 -> 5.5, 1024 x 1024 FP32
+// 16.1 -> 12.6 and FP64 27.8 -> 25.4; 45 flumes in FP64, a group of workgroups each,
+// 24.9 -> 11.7.  Of that, edge codes kept in registers and the early first read of the wave
+// speeds gave 15 % on 64 x 64 and 7 % on 512 x 512 cells.
 #pragma once
 
 #include "hexsv_ensemble.h"
@@ -142,10 +145,9 @@ constexpr int RES_NT = 256 * SUB / RES_PER<T, SUB>;
 // Inlined by force: where both kernels below have the instance, the viscous FP32 64 x 16 tile
 // became a function of its own, with its arguments and arrays in scratch memory.
 template <typename T, int VAR, int SUB, bool VISC, bool EXT>
-__device__ __attribute__((always_inline)) inline void resident_steps(const KDom<T> &dd, const KGrid &g, const KConst &kc,
-                                      const KRain &rn, const Ctl *in, Ctl *out, Part *ring,
-                                      const ResSync &rs, const ResGroup &grp, int max_steps,
-                                      uint32_t tag0) {
+__device__ __attribute__((always_inline)) inline void resident_steps(
+    const KDom<T> &dd, const KGrid &g, const KConst &kc, const KRain &rn, const Ctl *in, Ctl *out,
+    Part *ring, const ResSync &rs, const ResGroup &grp, int max_steps, uint32_t tag0) {
     // FP64 time and books: rounded as written in every translation unit (the cells' own
     // arithmetic is in TileCells, under the unit's setting)
 #pragma clang fp contract(off)
