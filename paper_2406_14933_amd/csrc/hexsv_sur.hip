@@ -236,6 +236,10 @@ static int conv_mask(const hexsv_grid *g, int nq, int nr, nn::ConvMask *cm, cons
     return HEXSV_OK;
 }
 
+// May a forward sweep?  Rasters too wide for its launch do not.
+static bool can_sweep(const hexsv_surrogate *s, int nq) {
+    return s->fused && s->layers == 4 && s->channels == 32 && nq <= 1 << 26;
+}
 // How a forward runs.  A gradient's has all ways whatever set_fused says, but for 0.
 static nn::Net4Route route_of(const hexsv_surrogate *s, int nq, int nr, int batch,
                               const nn::ConvMask &cm, nn::Net4Use use, bool chain_too) {
@@ -246,6 +250,15 @@ static nn::Net4Route route_of(const hexsv_surrogate *s, int nq, int nr, int batc
 // reads features while it writes outputs).
 static bool apart(const float *f, const float *out, int64_t cells) {
     return out + cells * nn::OUT_STRIDE <= f || f + cells * nn::FEATURES <= out;
+}
+// Is the stream being captured?  A captured forward takes the sweep whatever is faster: the
+// workspace that the other ways use can not be allocated then, and may be another one by the
+// time the graph is replayed.
+static bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
 }
 static nn::Net4 net4_of(const hexsv_surrogate *s) {
     nn::Net4 nw;
@@ -302,11 +315,15 @@ extern "C" int hexsv_surrogate_forward(hexsv_surrogate *s, const hexsv_grid *gri
     if (rc) return rc;
     rc = check_call(s, batch, nq, nr);
     if (rc) return rc;
-    const nn::Net4Route route = route_of(s, nq, nr, batch, cm, nn::NET4_FORWARD, false);
-    // straight to the caller's cells (no workspace) where they take 16-byte stores
-    if (route == nn::NET4_SWEEP && ((uintptr_t)d_out & 15) == 0 &&
+    nn::Net4Route route = route_of(s, nq, nr, batch, cm, nn::NET4_FORWARD, false);
+    // straight to the caller's cells (no workspace) where they take 16-byte stores, or may not
+    // be taken through the workspace (three floats a cell)
+    const bool wide = ((uintptr_t)d_out & 15) == 0;
+    const bool captured = !(route == nn::NET4_SWEEP && wide) && can_sweep(s, nq) && capturing(st);
+    if (captured) route = nn::NET4_SWEEP;
+    if (route == nn::NET4_SWEEP && (wide || captured) &&
         apart(d_features, d_out, (int64_t)batch * nq * nr)) {
-        HIP_TRY(nn::launch_net4(d_features, true, net4_of(s), d_out, true, nq, nr, batch, cm, st));
+        HIP_TRY(nn::launch_net4(d_features, true, net4_of(s), d_out, wide, nq, nr, batch, cm, st));
         return HEXSV_OK;
     }
     int64_t cells;

@@ -115,6 +115,36 @@ def test_forward_to_any_float_address(hx, shift):
     assert bool((buf[:shift] == 7).all()) and bool((buf[shift + 4 * nq * nr:] == 7).all())
 
 
+@pytest.mark.parametrize("batch,nq,nr,masked,shift", [
+    (512, 16, 16, False, 0), (4096, 8, 8, False, 0), (64, 128, 128, True, 0), (1, 100, 75, False, 0),
+    (512, 16, 16, False, 1), (1, 100, 75, True, 3)])
+def test_a_captured_forward_needs_no_workspace(hx, batch, nq, nr, masked, shift):
+    """Capture as the first call of a surrogate; later calls move its workspace."""
+    print(f"[capture {batch}x{nq}x{nr} masked {masked} shift {shift}]", flush=True)
+    sur, grid, f, _ = network(hx, batch, nq, nr, masked)
+    other, _, f2, _ = network(hx, batch, nq, nr, masked)
+    x = f.clone()
+    buf = torch.full((4 * batch * nq * nr + 8,), 7.0, device="cuda")
+    out = buf[shift:shift + 4 * batch * nq * nr]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        hx._check(hx.lib().hexsv_surrogate_forward(sur._h, grid._h if grid else None, batch, nq, nr,
+                                                   hx._ptr(x), hx._ptr(out), hx._stream()))
+    for k in range(3):
+        x.copy_((f if k != 1 else -f2))
+        buf.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        want = other.forward(x, nq, nr, grid)
+        assert torch.equal(out.view(-1, 4)[:, :3], want[:, :3]), k
+        assert bool((buf[:shift] == 7).all()) and bool((buf[shift + out.numel():] == 7).all())
+        many = batch * (k + 2)  # a workspace of another size, at another address
+        sur.set_fused(False)
+        sur.forward(torch.zeros((many * nq * nr, so.FEATURES), device="cuda"), nq, nr, grid)
+        sur.set_fused(True)
+
+
 def still(hx, nq, nr, masked):
     """Still water in a closed basin: a network of zeros is kept in every window."""
     sc = synth.c1_planar(nq, nr, t_end=1e9)
